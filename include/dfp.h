@@ -110,7 +110,10 @@ typedef enum dfp_direction { DFP_FWD = 0, DFP_BWD_DATA = 1, DFP_BWD_WT = 2 } dfp
  * same results; AUTO also weighs the work size when it picks the kernel (a
  * filter of more than 36 blocks of 32 reduction indices takes the
  * four-waves-per-SIMD kernel in phases only when the layer has enough output
- * pixels), MFMA takes that kernel whenever its operand layout fits. */
+ * pixels), MFMA takes that kernel whenever its operand layout fits.  P = 16
+ * convolutions take the matrix cores too when they are given a workspace of
+ * dfp_workspace_bytes (without one, or recording partials, the VALU kernels);
+ * operands with integers above 32639 are recomputed on the VALU on the device. */
 typedef enum dfp_path {
   DFP_PATH_AUTO = 0, /* byte-split int8 MFMA, kernel by shape and work size     */
   DFP_PATH_MFMA = 1, /* byte-split int8 MFMA, four-waves-per-SIMD kernel first  */
@@ -244,7 +247,8 @@ dfp_status dfp_downconvert_i32(const dfp_desc* d, int32_t role, const int32_t* s
                                int16_t* dst, dfp_scale* sout, int32_t amax_ready, void* stream);
 
 /* Device workspace needed by a convolution direction (bytes, 0 if none);
- * 0 also for an invalid descriptor. */
+ * 0 also for an invalid descriptor.  At P = 16 it may be left out (NULL):
+ * the call then runs on the VALU kernels. */
 size_t dfp_workspace_bytes(const dfp_desc* d, int32_t direction);
 
 /* Number of chunks J = ceil(T / L) of a direction; -1 for an invalid descriptor. */

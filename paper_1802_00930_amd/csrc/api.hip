@@ -136,15 +136,16 @@ dfp_status conv_checks(const dfp_desc* d, Geom* g, const void* a, const void* sa
 }
 
 // The byte-digit split is exact for integers in [-32768, 32639], which holds
-// for every DFP15 tensor; 16-bit tensors (up to +-32767) take the VALU path.
-bool use_mfma(const Geom& g, int32_t path, int32_t bits, int32_t dir) {
-  if (path == DFP_PATH_VALU || bits != 15) return false;
+// for every DFP15 tensor; 16-bit tensors reach 32767 and take the MFMA path
+// with the VALU kernels gated behind it (launch_p16_scan).
+bool mfma_shape(const Geom& g, int32_t path, int32_t dir) {
+  if (path == DFP_PATH_VALU) return false;
   if (dir == DFP_BWD_WT) return bwdw_mfma_supported(g);
   return conv_mfma_supported(g, dir);
 }
+bool use_mfma(const Geom& g, int32_t path, int32_t bits, int32_t dir) { return bits == 15 && mfma_shape(g, path, dir); }
 
-size_t workspace_bytes(const Geom& g, int32_t dir, int32_t path, int32_t bits) {
-  if (!use_mfma(g, path, bits, dir)) return 0;
+size_t mfma_workspace_bytes(const Geom& g, int32_t dir) {
   if (dir == DFP_BWD_DATA)  // room for either route (partials take the general one)
     return (size_t)std::max(std::max<int64_t>(plan_conv_mfma(g, dir).bytes, conv_bwd_data_sub_bytes(g)),
                             conv_bwd_data_phase_bytes(g));
@@ -152,7 +153,22 @@ size_t workspace_bytes(const Geom& g, int32_t dir, int32_t path, int32_t bits) {
   return (size_t)plan_bwdw_mfma(g).bytes;
 }
 
+// At P = 16 the gate's words follow the MFMA path's workspace.
+size_t p16_gate_offset(const Geom& g, int32_t dir) { return (mfma_workspace_bytes(g, dir) + 255) / 256 * 256; }
+
+size_t workspace_bytes(const Geom& g, int32_t dir, int32_t path, int32_t bits) {
+  if (!mfma_shape(g, path, dir)) return 0;
+  return bits == 15 ? mfma_workspace_bytes(g, dir) : p16_gate_offset(g, dir) + kP16GateBytes;
+}
+
+// P = 16 needs no workspace (the VALU kernels then run alone), but with one of
+// workspace_bytes it takes the matrix cores.
+bool p16_on_mfma(const Geom& g, int32_t dir, int32_t path, const void* ws, size_t ws_bytes) {
+  return mfma_shape(g, path, dir) && ws && aligned(ws, 256) && ws_bytes >= workspace_bytes(g, dir, path, 16);
+}
+
 dfp_status ws_check(const Geom& g, int32_t dir, int32_t path, int32_t bits, const void* ws, size_t ws_bytes) {
+  if (bits != 15) return DFP_OK;
   const size_t need = workspace_bytes(g, dir, path, bits);
   if (need == 0) return DFP_OK;
   if (!ws || ws_bytes < need || !aligned(ws, 256)) return DFP_ERR_WORKSPACE;
@@ -266,6 +282,36 @@ dfp_status dfp_downconvert(const dfp_desc* d, int32_t role, const float* src, in
   return launch_quant_convert(src, dst, n, s, d->bits, d->rounding, d->seed, (uint32_t)role, st);
 }
 
+// One convolution on the matrix cores.
+static dfp_status conv_mfma(int32_t dir, const Geom& g, int32_t path, const int16_t* a, const dfp_scale* sa,
+                            const int16_t* b, const dfp_scale* sb, float* out, dfp_scale* so, void* ws,
+                            int32_t* partials, hipStream_t st, bool i32) {
+  const bool w16 = path == DFP_PATH_MFMA;
+  if (i32) return launch_conv_mfma(dir, g, a, sa, b, sb, out, so, nullptr, ws, st, true);
+  if (dir == DFP_BWD_WT) return launch_bwdw_mfma(g, a, sa, b, sb, out, partials, ws, st);
+  if (dir == DFP_BWD_DATA && !partials && conv_bwd_data_sub_bytes(g) > 0)
+    return launch_conv_bwd_data_sub(g, a, sa, b, sb, out, so, ws, st, w16);
+  if (dir == DFP_BWD_DATA && !partials && conv_bwd_data_phase_bytes(g) > 0)
+    return launch_conv_bwd_data_phases(g, a, sa, b, sb, out, so, ws, st, w16);
+  // the filter prep kernel clears so before the main kernel raises it
+  return launch_conv_mfma(dir, g, a, sa, b, sb, out, so, partials, ws, st, false, w16);
+}
+
+// P = 16: scan, the MFMA path into a scale of its own, the gated VALU launch.
+static dfp_status conv_p16(int32_t dir, const Geom& g, int32_t path, const int16_t* a, const dfp_scale* sa,
+                           const int16_t* b, const dfp_scale* sb, float* out, dfp_scale* so, void* ws,
+                           hipStream_t st, bool i32) {
+  void* gate = reinterpret_cast<uint8_t*>(ws) + p16_gate_offset(g, dir);
+  const int32_t role_a = dir == DFP_BWD_DATA ? DFP_ROLE_DY : DFP_ROLE_X;
+  const int32_t role_b = dir == DFP_BWD_WT ? DFP_ROLE_DY : DFP_ROLE_W;
+  dfp_status rc;
+  if ((rc = launch_p16_scan(a, role_numel(g, role_a), b, role_numel(g, role_b), so, gate, st)) != DFP_OK) return rc;
+  if ((rc = conv_mfma(dir, g, path, a, sa, b, sb, out, so ? p16_mfma_scale(gate) : nullptr, ws, nullptr, st, i32)) !=
+      DFP_OK)
+    return rc;
+  return launch_conv_valu_gated(dir, g, a, sa, b, sb, out, so, gate, st, i32);
+}
+
 static dfp_status conv_common(int32_t dir, const dfp_desc* d, const int16_t* a, const dfp_scale* sa,
                               const int16_t* b, const dfp_scale* sb, float* out, dfp_scale* so, void* ws,
                               size_t ws_bytes, int32_t* partials, void* stream) {
@@ -275,15 +321,10 @@ static dfp_status conv_common(int32_t dir, const dfp_desc* d, const int16_t* a, 
   if ((rc = ws_check(g, dir, d->path, d->bits, ws, ws_bytes)) != DFP_OK) return rc;
   if (so && !aligned(so, 16)) return DFP_ERR_ALIGN;
   hipStream_t st = (hipStream_t)stream;
-  if (use_mfma(g, d->path, d->bits, dir)) {
-    if (dir == DFP_BWD_WT) return launch_bwdw_mfma(g, a, sa, b, sb, out, partials, ws, st);
-    if (dir == DFP_BWD_DATA && !partials && conv_bwd_data_sub_bytes(g) > 0)
-      return launch_conv_bwd_data_sub(g, a, sa, b, sb, out, so, ws, st, d->path == DFP_PATH_MFMA);
-    if (dir == DFP_BWD_DATA && !partials && conv_bwd_data_phase_bytes(g) > 0)
-      return launch_conv_bwd_data_phases(g, a, sa, b, sb, out, so, ws, st, d->path == DFP_PATH_MFMA);
-    // the filter prep kernel clears so before the main kernel raises it
-    return launch_conv_mfma(dir, g, a, sa, b, sb, out, so, partials, ws, st, false, d->path == DFP_PATH_MFMA);
-  }
+  if (use_mfma(g, d->path, d->bits, dir))
+    return conv_mfma(dir, g, d->path, a, sa, b, sb, out, so, ws, partials, st, false);
+  if (d->bits == 16 && !partials && p16_on_mfma(g, dir, d->path, ws, ws_bytes))
+    return conv_p16(dir, g, d->path, a, sa, b, sb, out, so, ws, st, false);
   if (so && (rc = launch_scale_reset(so, st)) != DFP_OK) return rc;
   return launch_conv_valu(dir, g, a, sa, b, sb, out, so, partials, st);
 }
@@ -302,8 +343,10 @@ static dfp_status conv_i32_common(int32_t dir, const dfp_desc* d, const int16_t*
   if (!aligned(so, 16)) return DFP_ERR_ALIGN;
   hipStream_t st = (hipStream_t)stream;
   float* outf = reinterpret_cast<float*>(out);
-  if (use_mfma(g, d->path, d->bits, dir))  // the filter prep kernel clears so
-    return launch_conv_mfma(dir, g, a, sa, b, sb, outf, so, nullptr, ws, st, true);
+  if (use_mfma(g, d->path, d->bits, dir))
+    return conv_mfma(dir, g, d->path, a, sa, b, sb, outf, so, ws, nullptr, st, true);
+  if (d->bits == 16 && p16_on_mfma(g, dir, d->path, ws, ws_bytes))
+    return conv_p16(dir, g, d->path, a, sa, b, sb, outf, so, ws, st, true);
   if ((rc = launch_scale_reset(so, st)) != DFP_OK) return rc;
   return launch_conv_valu(dir, g, a, sa, b, sb, outf, so, nullptr, st, true);
 }
@@ -493,7 +536,8 @@ dfp_status dfp_conv_bwd_weights_noalloc(const dfp_desc* d, const int16_t* x, con
   Geom g;
   dfp_status rc = conv_checks(d, &g, x, sx, dy, sdy, dw);
   if (rc != DFP_OK) return rc;
-  const size_t need = workspace_bytes(g, DFP_BWD_WT, d->path, d->bits);
+  // (P = 16 runs the VALU kernel here, which needs no scratch)
+  const size_t need = d->bits == 15 ? workspace_bytes(g, DFP_BWD_WT, d->path, d->bits) : 0;
   if (need > (size_t)DFP_NOALLOC_SCRATCH_BYTES) return DFP_ERR_SCRATCH_LIMIT;
   hipStream_t st = (hipStream_t)stream;
   if (!use_mfma(g, d->path, d->bits, DFP_BWD_WT)) return launch_conv_valu(DFP_BWD_WT, g, x, sx, dy, sdy, dw, nullptr,

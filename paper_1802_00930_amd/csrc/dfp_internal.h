@@ -121,6 +121,19 @@ dfp_status launch_conv_valu(int32_t dir, const Geom& g, const int16_t* a, const 
                             const int16_t* b, const dfp_scale* sb, float* out, dfp_scale* so,
                             int32_t* partials, hipStream_t st, bool i32 = false);
 
+// P = 16 through the MFMA path (conv_valu.hip): the scan notes in gate_ws
+// (kP16GateBytes, 16-byte aligned) whether an operand element lies beyond the
+// byte digits and clears so; the MFMA kernels raise p16_mfma_scale(gate_ws)
+// instead of so; the gated VALU launch then recomputes the output if need be
+// and otherwise copies that scale to so.
+constexpr int64_t kP16GateBytes = 1280;
+dfp_status launch_p16_scan(const int16_t* a, int64_t na, const int16_t* b, int64_t nb, dfp_scale* so, void* gate_ws,
+                           hipStream_t st);
+dfp_scale* p16_mfma_scale(void* gate_ws);
+dfp_status launch_conv_valu_gated(int32_t dir, const Geom& g, const int16_t* a, const dfp_scale* sa, const int16_t* b,
+                                  const dfp_scale* sb, float* out, dfp_scale* so, void* gate_ws, hipStream_t st,
+                                  bool i32);
+
 // gemm.hip: D[m][n] = opA opB with the forward convolution's chunked contract.
 struct GemmPlan {
   int32_t KB, G16, Mp;                          // 32-blocks and 16-groups of the padded reduction, padded rows
