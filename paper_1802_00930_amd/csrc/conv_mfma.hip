@@ -1688,9 +1688,20 @@ constexpr int kWaves16 = 16;
 constexpr int kThreads16 = kWaves16 * 64;
 constexpr int32_t kW16MaxKB = 36;
 
-template <bool PARTIALS, bool I32 = false, bool PHASED = false>
+// CL: the chunk length, 64, 32, 16 or 8.  Below 64 a block of 32 indices holds
+// 32 / CL chunks, each multiplied by itself: a lane's 16 indices of a block
+// lie in one half, so at 16 the filter operand of a chunk is read with the
+// lanes of the other half at a zero piece of LDS (no VALU work), and at 8 its
+// other two dwords are zero as well.  The chunk conversion (four VALU
+// operations per output) then costs 2, 4 or 8 times the MFMAs of L = 64 and
+// bounds the kernel: ResNet-50 conv2_x forward at L = 32 / 16 / 8 31 / 47 / 83
+// us, 44 / 77 / 126 us on the shared-ring and masked kernels (at L = 16 the
+// conversions alone take 27 us of every SIMD's VALU).
+template <bool PARTIALS, bool I32 = false, bool PHASED = false, int CL = 64>
 __global__ __launch_bounds__(kThreads16, 1) void k_conv_mfma_w16(ConvMfmaArgs a) {
-  __shared__ __align__(16) uint8_t sA[kW16MaxKB * kStageA];
+  static_assert(CL == 64 || ((CL == 32 || CL == 16 || CL == 8) && !I32), "chunk lengths");
+  constexpr int kZeroA = kW16MaxKB * kStageA;  // the zero piece
+  __shared__ __align__(16) uint8_t sA[kZeroA + (CL < 32 ? 16 : 0)];
   __shared__ __align__(8) int32_t s_boff[kW16MaxKB];
   __shared__ uint32_t red[kWaves16];
   __shared__ int32_t s_next;  // the first unit of the range no wave has taken yet
@@ -1745,6 +1756,7 @@ __global__ __launch_bounds__(kThreads16, 1) void k_conv_mfma_w16(ConvMfmaArgs a)
   const int32_t my_units = (u1 - u0 > wave) ? (u1 - u0 - wave + kWaves16 - 1) / kWaves16 : 0;
   auto unit_of = [&](int32_t i) { return u0 + wave + kWaves16 * i; };
   if (threadIdx.x == 0) s_next = u0 + kWaves16;
+  if (CL < 32 && threadIdx.x < 4) reinterpret_cast<uint32_t*>(sA + kZeroA)[threadIdx.x] = 0u;
   // byte offset of this lane's operand for the pixel of unit u (block offsets come from s_boff)
   auto pixel_off = [&](int32_t u) -> int32_t {
     int32_t gp = (u >> hsh) * 32 + col;
@@ -1827,20 +1839,63 @@ __global__ __launch_bounds__(kThreads16, 1) void k_conv_mfma_w16(ConvMfmaArgs a)
         }
       }
       const uint8_t* ab = sA + msub * 2048;
+      // chunks of less than two blocks: LDS offsets of this lane's filter
+      // operand for the chunks of each half (the zero piece, not advanced, on
+      // the lanes of the other half), and the block's chunks
+      uint32_t fa[2][2];
+      if constexpr (CL < 32) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          fa[h][0] = half == h ? (uint32_t)(msub * 2048) + ra_hi : (uint32_t)kZeroA;
+          fa[h][1] = half == h ? (uint32_t)(msub * 2048) + ra_lo : (uint32_t)kZeroA;
+        }
+      }
+      auto short_chunks = [&](int32_t blk, const v4i& bh, const v4i& bl) __attribute__((always_inline)) {
+        auto chunk = [&](const v4i& ah, const v4i& al, int i) __attribute__((always_inline)) {
+          mfma_tile(acc, ah, al, bh, bl, true);
+          flush_tile<PARTIALS>(acc, sum, (int64_t)(kb0 + blk) * (32 / CL) + i, a.partials, a.O, obase, PQ, mrow0, a.M,
+                               gvalid);
+        };
+        if constexpr (CL == 32) {
+          const uint8_t* abk = sA + msub * 2048 + blk * kStageA;
+          chunk(*reinterpret_cast<const v4i*>(abk + ra_hi), *reinterpret_cast<const v4i*>(abk + ra_lo), 0);
+        } else {
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const v4i ah = *reinterpret_cast<const v4i*>(sA + fa[h][0]);
+            const v4i al = *reinterpret_cast<const v4i*>(sA + fa[h][1]);
+            fa[h][0] += half == h ? kStageA : 0;
+            fa[h][1] += half == h ? kStageA : 0;
+            if constexpr (CL == 16) {
+              chunk(ah, al, h);
+            } else {
+              chunk((v4i){ah.x, ah.y, 0, 0}, (v4i){al.x, al.y, 0, 0}, 2 * h);
+              chunk((v4i){0, 0, ah.z, ah.w}, (v4i){0, 0, al.z, al.w}, 2 * h + 1);
+            }
+          }
+        }
+      };
       for (int32_t c = 0; c < J; ++c, ab += 2 * kStageA) {
         const bool last = c + 1 == J;
         const int2 bo = *reinterpret_cast<const int2*>(s_boff + (last ? 0 : 2 * c + 2));
         const int32_t pix = last ? next_pix : cur_pix;
-        const v4i ah0 = *reinterpret_cast<const v4i*>(ab + ra_hi);
-        const v4i al0 = *reinterpret_cast<const v4i*>(ab + ra_lo);
-        if (I32 && c != 0) mfma_tile(acc, ah0, al0, b0h, b0l, false);
-        else mfma_tile(acc, ah0, al0, b0h, b0l, true);
-        load_b(b0h, b0l, pix, bo.x);
-        const v4i ah1 = *reinterpret_cast<const v4i*>(ab + kStageA + ra_hi);
-        const v4i al1 = *reinterpret_cast<const v4i*>(ab + kStageA + ra_lo);
-        mfma_tile(acc, ah1, al1, b1h, b1l, false);
-        load_b(b1h, b1l, pix, bo.y);
-        if (!I32) flush_tile<PARTIALS>(acc, sum, kb0 / 2 + c, a.partials, a.O, obase, PQ, mrow0, a.M, gvalid);
+        if constexpr (CL == 64) {
+          const v4i ah0 = *reinterpret_cast<const v4i*>(ab + ra_hi);
+          const v4i al0 = *reinterpret_cast<const v4i*>(ab + ra_lo);
+          if (I32 && c != 0) mfma_tile(acc, ah0, al0, b0h, b0l, false);
+          else mfma_tile(acc, ah0, al0, b0h, b0l, true);
+          load_b(b0h, b0l, pix, bo.x);
+          const v4i ah1 = *reinterpret_cast<const v4i*>(ab + kStageA + ra_hi);
+          const v4i al1 = *reinterpret_cast<const v4i*>(ab + kStageA + ra_lo);
+          mfma_tile(acc, ah1, al1, b1h, b1l, false);
+          load_b(b1h, b1l, pix, bo.y);
+          if (!I32) flush_tile<PARTIALS>(acc, sum, kb0 / 2 + c, a.partials, a.O, obase, PQ, mrow0, a.M, gvalid);
+        } else {
+          short_chunks(2 * c, b0h, b0l);
+          load_b(b0h, b0l, pix, bo.x);
+          short_chunks(2 * c + 1, b1h, b1l);
+          load_b(b1h, b1l, pix, bo.y);
+        }
       }
       if (I32) keep_tile_i32(acc, sum);
       if (PHASED && gvalid && !last_phase) {  // unscaled sums for the next phase
@@ -1931,9 +1986,15 @@ constexpr int32_t kS16Rows = 32;                   // filter rows per workgroup
 constexpr int32_t kS16Block = kS16Rows * 64;        // LDS bytes of one filter block
 constexpr int32_t kS16MaxKB = kW16MaxKB * kStageA / kS16Block;  // 72
 
-template <bool PHASED>
+// CL: the chunk length, 64, 32, 16 or 8; below 64 the filter operand of each
+// of the 64 / CL chunks is read with the other index groups' lanes at zero
+// bytes of LDS, as in the 32 x 32 kernel (ResNet-50 res4 3 x 3, N = 32, L =
+// 16: 95 us there, two phases of 1568 units, 67 us here; 106 us on the masked
+// kernel).
+template <bool PHASED, int CL = 64>
 __global__ __launch_bounds__(kThreads16, 1) void k_conv_mfma_s16(ConvMfmaArgs a) {
-  __shared__ __align__(16) uint8_t sA[kS16MaxKB * kS16Block];
+  constexpr int kZeroA = kS16MaxKB * kS16Block;  // zero pieces of both subtiles, 1024 bytes apart
+  __shared__ __align__(16) uint8_t sA[kZeroA + (CL < 64 ? 1024 + 16 : 0)];
   __shared__ __align__(8) int32_t s_boff[kS16MaxKB];
   __shared__ uint32_t red[kWaves16];
   const int lane = threadIdx.x & 63;
@@ -1968,6 +2029,8 @@ __global__ __launch_bounds__(kThreads16, 1) void k_conv_mfma_s16(ConvMfmaArgs a)
     return a.rsign * (r * cpb * 4 * plane_bytes + sx * 16) + cb * 4 * plane_bytes;
   };
   if ((int32_t)threadIdx.x < KB) s_boff[threadIdx.x] = boff_of(kb0 + (int32_t)threadIdx.x);
+  if (CL < 64 && threadIdx.x < 8)
+    reinterpret_cast<uint32_t*>(sA + kZeroA + (threadIdx.x >> 2) * 1024)[threadIdx.x & 3] = 0u;
 
   // ---- this workgroup's unit range (XCD x = workgroup id mod 8 gets adjacent ranges)
   // units: 16-pixel tiles; both 16-row subtiles of the slice, or only the
@@ -2056,32 +2119,79 @@ __global__ __launch_bounds__(kThreads16, 1) void k_conv_mfma_s16(ConvMfmaArgs a)
           }
       }
       auto chunk = [&](int32_t c, v4i& bh, v4i& bl) __attribute__((always_inline)) {
-        const uint8_t* ab = sA + c * 2 * kS16Block;
-        const v4i z = {0, 0, 0, 0};
-        v4i ah[NSUB], al[NSUB];
+        // the operands' products and, at the chunk's end, its FP32 conversion
+        auto products = [&](const v4i (&ah)[NSUB], const v4i (&al)[NSUB]) __attribute__((always_inline)) {
+          const v4i z = {0, 0, 0, 0};
 #pragma unroll
-        for (int sb = 0; sb < NSUB; ++sb) {
-          ah[sb] = *reinterpret_cast<const v4i*>(ab + sb * 1024 + ra_hi);
-          al[sb] = *reinterpret_cast<const v4i*>(ab + sb * 1024 + ra_lo);
-        }
-#pragma unroll
-        for (int sb = 0; sb < NSUB; ++sb) {
-          hh[sb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ah[sb], bh, z, 0, 0, 0);
-          ll[sb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al[sb], bl, z, 0, 0, 0);
-          xx[sb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ah[sb], bl, z, 0, 0, 0);
-        }
-#pragma unroll
-        for (int sb = 0; sb < NSUB; ++sb) xx[sb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al[sb], bh, xx[sb], 0, 0, 0);
-        // chunk c + 2 of this unit, or chunk c + 2 - J of the next one
-        const int32_t nc = c + 2 < J ? c + 2 : c + 2 - J;
-        load_b(bh, bl, c + 2 < J ? cur_pix : next_pix, boff_chunk(nc));
-#pragma unroll
-        for (int sb = 0; sb < NSUB; ++sb)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const uint32_t p = recombine((uint32_t)hh[sb][v], (uint32_t)xx[sb][v], (uint32_t)ll[sb][v]);
-            sum[sb][v] += (float)(int32_t)p;
+          for (int sb = 0; sb < NSUB; ++sb) {
+            hh[sb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ah[sb], bh, z, 0, 0, 0);
+            ll[sb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al[sb], bl, z, 0, 0, 0);
+            xx[sb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ah[sb], bl, z, 0, 0, 0);
           }
+#pragma unroll
+          for (int sb = 0; sb < NSUB; ++sb) xx[sb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al[sb], bh, xx[sb], 0, 0, 0);
+        };
+        auto flush = [&]() __attribute__((always_inline)) {
+#pragma unroll
+          for (int sb = 0; sb < NSUB; ++sb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              const uint32_t p = recombine((uint32_t)hh[sb][v], (uint32_t)xx[sb][v], (uint32_t)ll[sb][v]);
+              sum[sb][v] += (float)(int32_t)p;
+            }
+        };
+        // chunk c + 2 of this unit, or chunk c + 2 - J of the next one
+        auto refill = [&]() __attribute__((always_inline)) {
+          const int32_t nc = c + 2 < J ? c + 2 : c + 2 - J;
+          load_b(bh, bl, c + 2 < J ? cur_pix : next_pix, boff_chunk(nc));
+        };
+        const uint32_t ab = (uint32_t)(c * 2 * kS16Block);
+        if constexpr (CL == 64) {
+          v4i ah[NSUB], al[NSUB];
+#pragma unroll
+          for (int sb = 0; sb < NSUB; ++sb) {
+            ah[sb] = *reinterpret_cast<const v4i*>(sA + ab + sb * 1024 + ra_hi);
+            al[sb] = *reinterpret_cast<const v4i*>(sA + ab + sb * 1024 + ra_lo);
+          }
+          products(ah, al);
+          refill();
+          flush();
+        } else {
+          constexpr int kGroups = CL == 32 ? 2 : 4;  // of the 64 indices, read with one set of lanes each
+#pragma unroll
+          for (int q = 0; q < kGroups; ++q) {
+            const bool mine = (CL == 32 ? kg >> 1 : kg) == q;
+            const uint32_t oh = mine ? ab + ra_hi : (uint32_t)kZeroA, ol = mine ? ab + ra_lo : (uint32_t)kZeroA;
+            v4i ah[NSUB], al[NSUB];
+#pragma unroll
+            for (int sb = 0; sb < NSUB; ++sb) {
+              ah[sb] = *reinterpret_cast<const v4i*>(sA + oh + sb * 1024);
+              al[sb] = *reinterpret_cast<const v4i*>(sA + ol + sb * 1024);
+            }
+            if constexpr (CL > 8) {
+              products(ah, al);
+              if (q == kGroups - 1) refill();
+              flush();
+            } else {  // the group's first and last 8 indices
+              v4i ph[NSUB], pl[NSUB];
+#pragma unroll
+              for (int sb = 0; sb < NSUB; ++sb) {
+                ph[sb] = (v4i){ah[sb].x, ah[sb].y, 0, 0};
+                pl[sb] = (v4i){al[sb].x, al[sb].y, 0, 0};
+              }
+              products(ph, pl);
+              flush();
+#pragma unroll
+              for (int sb = 0; sb < NSUB; ++sb) {
+                ph[sb] = (v4i){0, 0, ah[sb].z, ah[sb].w};
+                pl[sb] = (v4i){0, 0, al[sb].z, al[sb].w};
+              }
+              products(ph, pl);
+              if (q == kGroups - 1) refill();
+              flush();
+            }
+          }
+        }
       };
       for (int32_t c = 0; c < J; c += 2) {
         chunk(c, b0h, b0l);
@@ -2495,7 +2605,7 @@ inline int64_t align256(int64_t v) { return (v + 255) & ~(int64_t)255; }
 
 }  // namespace
 
-// The 16 x 16-tile kernel serves FP32 outputs at L = 64 without partials
+// The 16 x 16-tile kernel serves FP32 outputs at L = 64, 32, 16 or 8 without partials
 // when the 32 x 32 tiles are fewer than the chip's wave slots (16 per CU), or
 // the output has at most 16 rows (a 16-row subtile then wastes half as many
 // rows as a 32-row half), and every phase (whole chunks, at most kS16MaxKB
@@ -2517,9 +2627,10 @@ static int device_cus() {
 }
 
 bool conv_w16_eligible(int32_t Cin, int32_t T, int32_t L, bool i32) {
-  // FP32 outputs at L = 64 take any number of blocks in phases of at most
-  // kW16MaxKB; single-chunk INT32 outputs one phase
-  return (Cin % 32) == 0 && (T % 64) == 0 && (i32 ? T / 32 <= kW16MaxKB : L == 64);
+  // FP32 outputs take any number of blocks in phases of at most kW16MaxKB;
+  // single-chunk INT32 outputs one phase
+  return (Cin % 32) == 0 && (T % 64) == 0 &&
+         (i32 ? T / 32 <= kW16MaxKB : L == 64 || L == 32 || L == 16 || L == 8);
 }
 
 bool conv_mfma_supported(const Geom& g, int32_t dir) {
@@ -2571,7 +2682,8 @@ dfp_status launch_conv_mfma(int32_t dir, const Geom& g, const int16_t* a, const 
   const int32_t tap_row_bytes = rsign * p.Wp * p.CG * 32, tap_col_bytes = rsign * p.CG * 32;
   bool plane = conv_w16_eligible(p.Cin, p.T, g.L, i32) && (int64_t)g.n * p.Po * p.Qo * p.M < (1ll << 31) &&
                p.ws_b_bytes < (1ll << 31);
-  if (plane && p.KB > kW16MaxKB && !prefer_w16) {
+  if (plane && p.KB > kW16MaxKB && !prefer_w16 && g.L >= 32) {
+    // (shorter chunks would run the masked kernel, which is always slower)
     // phases pay the kernel's fixed cost once each: taken only when there are
     // at least as many 16 x 16 (32 x 32) output tiles per workgroup as it has
     // waves, in each phase
@@ -2748,7 +2860,7 @@ dfp_status launch_mfma_main(ConvMfmaArgs& args, int64_t ws_b_bytes, int kid, int
     return DFP_OK;
   }
   const bool persist_ok = chan16 && (args.T % 64) == 0 && args.KB >= 4 && args.KB <= kARes3Max && small_index;
-  // four waves per SIMD: 32-channel blocks (each block inside one filter tap), full chunks of two blocks
+  // four waves per SIMD: 32-channel blocks (each block inside one filter tap), pairs of blocks
   const bool w16_ok = args.plane != 0 && small_index;
   args.div_pq = make_fastdiv((uint32_t)(args.Po * args.Qo));
   args.div_q = make_fastdiv((uint32_t)args.Qo);
@@ -2785,7 +2897,7 @@ dfp_status launch_mfma_main(ConvMfmaArgs& args, int64_t ws_b_bytes, int kid, int
     DFP_LAUNCH(kid, (k_conv_mfma<MK, PT, CH>), grid, dim3(kThreads), 0, st, args);          \
     return DFP_OK;                                                                          \
   }
-  if (w16_ok && args.L == 64) {
+  if (w16_ok) {
     // phases of whole chunks, at most kW16MaxKB blocks each, as equal as possible;
     // each launch continues the chunk sums the previous one left in the output
     const int32_t chunks = args.KB / 2;
@@ -2805,8 +2917,16 @@ dfp_status launch_mfma_main(ConvMfmaArgs& args, int64_t ws_b_bytes, int kid, int
         args.kb0 = 2 * c0;
         args.kbn = 2 * (c1 - c0);
         args.phase_flags = (ph == 0 ? 1 : 0) | (ph == nph16 - 1 ? 2 : 0);
-        if (nph16 == 1) DFP_LAUNCH(kid, (k_conv_mfma_s16<false>), grid_s, dim3(kThreads16), 0, st, args);
-        else DFP_LAUNCH(kid, (k_conv_mfma_s16<true>), grid_s, dim3(kThreads16), 0, st, args);
+#define DFP_S16(CL)                                                                                        \
+  do {                                                                                                     \
+    if (nph16 == 1) DFP_LAUNCH(kid, (k_conv_mfma_s16<false, CL>), grid_s, dim3(kThreads16), 0, st, args);  \
+    else DFP_LAUNCH(kid, (k_conv_mfma_s16<true, CL>), grid_s, dim3(kThreads16), 0, st, args);              \
+  } while (0)
+        if (args.L == 64) DFP_S16(64);
+        else if (args.L == 32) DFP_S16(32);
+        else if (args.L == 16) DFP_S16(16);
+        else DFP_S16(8);
+#undef DFP_S16
       }
       return DFP_OK;
     }
@@ -2816,11 +2936,22 @@ dfp_status launch_mfma_main(ConvMfmaArgs& args, int64_t ws_b_bytes, int kid, int
       args.kb0 = 2 * c0;
       args.kbn = 2 * (c1 - c0);
       args.phase_flags = (ph == 0 ? 1 : 0) | (ph == nph - 1 ? 2 : 0);
-      if (nph == 1 && partials) DFP_LAUNCH(kid, (k_conv_mfma_w16<true>), grid16, dim3(kThreads16), 0, st, args);
-      else if (nph == 1) DFP_LAUNCH(kid, (k_conv_mfma_w16<false>), grid16, dim3(kThreads16), 0, st, args);
-      else if (partials)
-        DFP_LAUNCH(kid, (k_conv_mfma_w16<true, false, true>), grid16, dim3(kThreads16), 0, st, args);
-      else DFP_LAUNCH(kid, (k_conv_mfma_w16<false, false, true>), grid16, dim3(kThreads16), 0, st, args);
+#define DFP_W16(CL)                                                                                          \
+  do {                                                                                                       \
+    if (nph == 1 && partials)                                                                                \
+      DFP_LAUNCH(kid, (k_conv_mfma_w16<true, false, false, CL>), grid16, dim3(kThreads16), 0, st, args);     \
+    else if (nph == 1)                                                                                       \
+      DFP_LAUNCH(kid, (k_conv_mfma_w16<false, false, false, CL>), grid16, dim3(kThreads16), 0, st, args);    \
+    else if (partials)                                                                                       \
+      DFP_LAUNCH(kid, (k_conv_mfma_w16<true, false, true, CL>), grid16, dim3(kThreads16), 0, st, args);      \
+    else                                                                                                     \
+      DFP_LAUNCH(kid, (k_conv_mfma_w16<false, false, true, CL>), grid16, dim3(kThreads16), 0, st, args);     \
+  } while (0)
+      if (args.L == 64) DFP_W16(64);
+      else if (args.L == 32) DFP_W16(32);
+      else if (args.L == 16) DFP_W16(16);
+      else DFP_W16(8);
+#undef DFP_W16
     }
     return DFP_OK;
   }
