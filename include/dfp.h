@@ -194,8 +194,9 @@ dfp_status dfp_conv_bwd_weights(const dfp_desc* d, const int16_t* x, const dfp_s
  * sums) lives in a static device array of DFP_NOALLOC_SCRATCH_BYTES bytes
  * inside the library: every GPU the call runs on holds one such array from
  * the library's first use on it until the process ends.  A layer whose
- * workspace, dfp_workspace_bytes(d, DFP_BWD_WT), exceeds that size returns
- * DFP_ERR_SCRATCH_LIMIT before any HIP call.  stream (NULL = the default
+ * workspace, dfp_workspace_bytes(d, DFP_BWD_WT), exceeds that size runs kernels
+ * that need less where there are some and else returns DFP_ERR_SCRATCH_LIMIT
+ * before any HIP call.  stream (NULL = the default
  * stream) must belong to the current device, else DFP_ERR_PARAM.  Nothing in
  * the scratch needs to start at zero; the array keeps the last call's
  * contents.  Calls in flight at the same time on one GPU share the array and

@@ -537,11 +537,12 @@ dfp_status dfp_conv_bwd_weights_noalloc(const dfp_desc* d, const int16_t* x, con
   dfp_status rc = conv_checks(d, &g, x, sx, dy, sdy, dw);
   if (rc != DFP_OK) return rc;
   // (P = 16 runs the VALU kernel here, which needs no scratch)
-  const size_t need = d->bits == 15 ? workspace_bytes(g, DFP_BWD_WT, d->path, d->bits) : 0;
-  if (need > (size_t)DFP_NOALLOC_SCRATCH_BYTES) return DFP_ERR_SCRATCH_LIMIT;
+  const bool mfma = use_mfma(g, d->path, d->bits, DFP_BWD_WT);
+  // a layer whose ring-kernel scratch is too large runs the kernels without it
+  const bool ring = mfma && plan_bwdw_mfma(g).bytes <= (int64_t)DFP_NOALLOC_SCRATCH_BYTES;
+  if (mfma && plan_bwdw_mfma(g, ring).bytes > (int64_t)DFP_NOALLOC_SCRATCH_BYTES) return DFP_ERR_SCRATCH_LIMIT;
   hipStream_t st = (hipStream_t)stream;
-  if (!use_mfma(g, d->path, d->bits, DFP_BWD_WT)) return launch_conv_valu(DFP_BWD_WT, g, x, sx, dy, sdy, dw, nullptr,
-                                                                            nullptr, st);
+  if (!mfma) return launch_conv_valu(DFP_BWD_WT, g, x, sx, dy, sdy, dw, nullptr, nullptr, st);
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return DFP_ERR_HIP;
   if (st) {
@@ -551,7 +552,7 @@ dfp_status dfp_conv_bwd_weights_noalloc(const dfp_desc* d, const int16_t* x, con
   }
   void* ws = scratch_on_device(dev);
   if (!ws) return DFP_ERR_HIP;
-  return launch_bwdw_mfma(g, x, sx, dy, sdy, dw, nullptr, ws, st);
+  return launch_bwdw_mfma(g, x, sx, dy, sdy, dw, nullptr, ws, st, ring);
 }
 
 dfp_status dfp_profile_start(int32_t capacity) {

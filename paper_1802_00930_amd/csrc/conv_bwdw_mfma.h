@@ -35,9 +35,11 @@ struct BwdwArgs {
   uint32_t flat_tab;            // flat-band kernel: byte offset of the selector table after the planes
 };
 
-BwdwPlan plan_bwdw_mfma(const Geom& g);
+// ring: whether the ring kernel, whose workspace may be larger, may be used.
+BwdwPlan plan_bwdw_mfma(const Geom& g, bool ring = true);
 bool bwdw_mfma_supported(const Geom& g);
 dfp_status launch_bwdw_mfma(const Geom& g, const int16_t* x, const dfp_scale* sx, const int16_t* dy,
-                            const dfp_scale* sdy, float* dw, int32_t* partials, void* ws, hipStream_t st);
+                            const dfp_scale* sdy, float* dw, int32_t* partials, void* ws, hipStream_t st,
+                            bool ring = true);
 
 }  // namespace dfp

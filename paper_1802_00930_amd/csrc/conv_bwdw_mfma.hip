@@ -1754,6 +1754,459 @@ __global__ __launch_bounds__(kThreadsW8, PARTIALS ? 2 : 4) void k_bwdw_flat(Bwdw
   }
 }
 
+// ---------------------------------------------------------------------------
+// Ring kernel: the flat-band operands for any filter and stride whose padding
+// keeps the input within the output grid ("same" layers: ceil(H / sh) <= P and
+// ceil(W / sw) <= Q), chunks of 64, 32, 16 or 8 and any reduction length.
+// With r - ph = r' sh + a (0 <= a < sh; columns likewise), the input pixel of
+// column (c, r, s) and index t = (n, p, q) is element (p + r', q + s') of the
+// subsampled plane (c, a, b), x[n][c][. sh + a][. sw + b], which in t order
+// sits at t + r' Q + s'.  Windows and selectors are those of the flat-band
+// kernel, one selector row per (r', s').
+//
+// What bounds it: at the default segment length of 4096 indices a layer has
+// only one or two 32 x 32 tiles per SIMD (conv2_x at N = 32: 36 tiles x 24.5
+// segments for 1024 SIMDs), each a serial chain of 64 chunks whose latencies
+// nothing hides.  Hence tiles of 16 columns x 16 NSUB rows
+// (v_mfma_i32_16x16x64_i8, one instruction per product and 64 indices), of
+// which a 64 x 64 (or, for at most 32 rows, 32 x 64) workgroup tile gives 4,
+// 8 or 16 to as many waves; a ring of LDS buffers of 128 indices filled two
+// bands ahead; and two accumulator sets, so that a chunk's conversion is
+// issued between the MFMAs of the next.  One window per lane serves all NSUB
+// row subtiles.  For chunks below 64 the dy operand of a chunk is read with
+// the other index groups' lanes at zero bytes of LDS.
+// Measured (kernel, event times, default segments): conv2x 3x3 at N = 32 and
+// L = 64 / 32 / 16 / 8 39 / 49 / 74 / 121 us (before it 43 / 136 / 325 / 492);
+// ResNet-50 stem, N = 64, 101 us (176).  A workgroup barrier and its burst of
+// LDS reads per band cost about a quarter of the L = 64 time, the chunk
+// conversions most of the rest.
+constexpr int kRingBufs = 3;
+constexpr int kRingMaxPer = 10;  // copy instructions per band and wave
+struct RingArgs {
+  int32_t plane, nplanes;            // bytes per digit plane; planes of the whole input (C sh sw)
+  uint32_t tab;                      // byte offset of the selector table after the planes
+  int32_t npl, ppp, ch_stride;       // planes per column tile, 16-byte pieces per digit plane and band, LDS bytes per plane pair
+  int32_t hl, nsel, r0, s0, nsx;     // halo before t, selector rows, smallest r' and s', number of s'
+  int32_t RS, S, sh, sw, ph, pw, Q, npar;
+  int32_t ainstr, xinstr, tot;       // copy instructions per band: dy digits, planes, all
+  int32_t buf_bytes;
+};
+
+// r' and the phase a of filter row r: r - ph = r' sh + a.
+struct TapPos {
+  int32_t shift, phase;
+};
+__host__ __device__ __forceinline__ TapPos tap_pos(int32_t r, int32_t pad, int32_t stride) {
+  const int32_t z = r - pad + pad * stride;  // >= 0
+  return {z / stride - pad, z % stride};
+}
+
+struct RingPrep {
+  const int16_t* x;
+  uint8_t* xf;
+  int32_t C, H, W, P, Q, PQ, T, plane, hl, ngroups, sh, sw, npar, nsel, r0, s0, nsx;
+  uint32_t tab;
+  // plane bytes per thread read as one load: 8, 4, or (single elements) 1; 2:
+  // four of both column phases of a stride-2 row
+  int32_t vec;
+  FastDiv div_pq, div_q;
+};
+// Workgroups [0, nbx): the planes; [nbx, nbx + nbt): the selectors; the rest: dy digits.
+__global__ __launch_bounds__(256) void k_prep_ring(RingPrep f, DyPrep q, int32_t nbx, int32_t nbt) {
+  const int32_t b = blockIdx.x;
+  if (b >= nbx + nbt) {
+    prep_dy_item(q, (b - nbx - nbt) * 256 + threadIdx.x);
+    return;
+  }
+  if (b >= nbx) {  // one thread per selector dword (group, row, piece, dword)
+    const int32_t i = (b - nbx) * 256 + threadIdx.x;
+    if (i >= f.ngroups * f.nsel * 16) return;
+    const int32_t gi = i / (f.nsel * 16), rem = i - gi * (f.nsel * 16);
+    const int32_t sr = rem >> 4, dr = f.r0 + sr / f.nsx, ds = f.s0 + sr % f.nsx;
+    const uint32_t a = (uint32_t)(f.hl + dr * f.Q + ds) & 3u;  // the window's misalignment
+    uint32_t sel = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int32_t t = gi * 64 + (rem & 15) * 4 + k;
+      bool valid = false;
+      if (t < f.T) {
+        const int32_t n = (int32_t)fdiv((uint32_t)t, f.div_pq), pq = t - n * f.PQ;
+        const int32_t p = (int32_t)fdiv((uint32_t)pq, f.div_q), qq = pq - p * f.Q;
+        valid = (uint32_t)(p + dr) < (uint32_t)f.P && (uint32_t)(qq + ds) < (uint32_t)f.Q;
+      }
+      sel |= (valid ? a + (uint32_t)k : 12u) << (8 * k);
+    }
+    reinterpret_cast<uint32_t*>(f.xf + f.tab)[i] = sel;
+    return;
+  }
+  const int32_t V = f.vec == 8 ? 8 : 4;  // plane bytes per thread
+  const int32_t per = f.plane / V;
+  const int64_t i = (int64_t)b * 256 + threadIdx.x;
+  if (f.vec == 2) {  // (c, row phase, four indices of one output row): eight input columns
+    if (i >= (int64_t)f.C * f.sh * per) return;
+    const int32_t cp = (int32_t)(i / per), u = (int32_t)(i - (int64_t)cp * per) * 4, t = u - f.hl;
+    const int32_t c = cp / f.sh, pa = cp - c * f.sh;
+    uint4 v = make_uint4(0u, 0u, 0u, 0u);
+    if (t >= 0 && t < f.T) {
+      const int32_t n = (int32_t)fdiv((uint32_t)t, f.div_pq), pq = t - n * f.PQ;
+      const int32_t p = (int32_t)fdiv((uint32_t)pq, f.div_q), qq = pq - p * f.Q, ih = p * f.sh + pa;
+      if (ih < f.H) v = *reinterpret_cast<const uint4*>(f.x + (((int64_t)n * f.C + c) * f.H + ih) * f.W + 2 * qq);
+    }
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int pb = 0; pb < 2; ++pb) {
+      uint32_t lo = 0, hi = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int32_t a = (int32_t)(int16_t)(w[k] >> (16 * pb));
+        lo |= lo_digit(a) << (8 * k);
+        hi |= hi_digit(a) << (8 * k);
+      }
+      uint8_t* row = f.xf + (int64_t)(c * f.npar + pa * 2 + pb) * 2 * f.plane + u;
+      *reinterpret_cast<uint32_t*>(row) = lo;
+      *reinterpret_cast<uint32_t*>(row + f.plane) = hi;
+    }
+    return;
+  }
+  if (i >= (int64_t)f.C * f.npar * per) return;
+  const int32_t pl = (int32_t)(i / per), u = (int32_t)(i - (int64_t)pl * per) * V;
+  const int32_t t = u - f.hl;
+  uint8_t* row = f.xf + (int64_t)pl * 2 * f.plane + u;
+  if (f.vec != 1) {  // V indices from a multiple of V lie in one image and are one load
+    uint32_t w[4] = {0u, 0u, 0u, 0u}, lo[2] = {0u, 0u}, hi[2] = {0u, 0u};
+    if (t >= 0 && t < f.T) {
+      const int32_t n = (int32_t)fdiv((uint32_t)t, f.div_pq), pq = t - n * f.PQ;
+      const int16_t* src = f.x + ((int64_t)n * f.C + pl) * f.PQ + pq;
+      if (f.vec == 8) {
+        const uint4 v = *reinterpret_cast<const uint4*>(src);
+        w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+      } else {
+        const uint2 v = *reinterpret_cast<const uint2*>(src);
+        w[0] = v.x; w[1] = v.y;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int32_t a = (int32_t)(int16_t)(w[k >> 1] >> (16 * (k & 1)));
+      lo[k >> 2] |= lo_digit(a) << (8 * (k & 3));
+      hi[k >> 2] |= hi_digit(a) << (8 * (k & 3));
+    }
+    if (f.vec == 8) {
+      *reinterpret_cast<uint2*>(row) = make_uint2(lo[0], lo[1]);
+      *reinterpret_cast<uint2*>(row + f.plane) = make_uint2(hi[0], hi[1]);
+    } else {
+      *reinterpret_cast<uint32_t*>(row) = lo[0];
+      *reinterpret_cast<uint32_t*>(row + f.plane) = hi[0];
+    }
+    return;
+  }
+  const int32_t c = pl / f.npar, par = pl - c * f.npar;
+  const int32_t pa = par / f.sw, pb = par - pa * f.sw;
+  uint32_t lo = 0, hi = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (t + k >= 0 && t + k < f.T) {
+      const int32_t n = (int32_t)fdiv((uint32_t)(t + k), f.div_pq), pq = t + k - n * f.PQ;
+      const int32_t p = (int32_t)fdiv((uint32_t)pq, f.div_q), qq = pq - p * f.Q;
+      const int32_t ih = p * f.sh + pa, iw = qq * f.sw + pb;
+      const int32_t v = ih < f.H && iw < f.W ? (int32_t)f.x[(((int64_t)n * f.C + c) * f.H + ih) * f.W + iw] : 0;
+      lo |= lo_digit(v) << (8 * k);
+      hi |= hi_digit(v) << (8 * k);
+    }
+  }
+  *reinterpret_cast<uint32_t*>(row) = lo;
+  *reinterpret_cast<uint32_t*>(row + f.plane) = hi;
+}
+
+// Waits until at most n of this lane's copies are in flight (n >= 1 uniform;
+// rounded down to one of six counts).
+__device__ __forceinline__ void wait_copies(int32_t n) {
+  if (n >= 4) {
+    if (n >= 8) wait_vmcnt<8>();
+    else if (n >= 6) wait_vmcnt<6>();
+    else wait_vmcnt<4>();
+  } else {
+    if (n >= 3) wait_vmcnt<3>();
+    else if (n >= 2) wait_vmcnt<2>();
+    else wait_vmcnt<1>();
+  }
+}
+
+// CL: chunk length.  NSUB: 16-row subtiles per wave.  RG: row groups of waves
+// (the workgroup: 4 RG waves, 16 NSUB RG rows x 64 columns).
+template <int CL, int NSUB, int RG>
+__global__ __launch_bounds__(256 * RG, NSUB == 4 ? 2 : NSUB == 2 ? 2 : 4) void k_bwdw_ring(BwdwArgs a, RingArgs f) {
+  static_assert(CL == 64 || CL == 32 || CL == 16 || CL == 8, "chunk lengths");
+  constexpr int kRows = 16 * NSUB * RG;
+  constexpr int kBlockBytes = kRows * 64;               // LDS bytes of one dy block
+  constexpr int kWaves = 4 * RG;
+  constexpr int kFixed = CL < 64 ? NSUB * 1024 : 0;     // zero pieces 1024 bytes apart
+  const BwdwTile tl = bwdw_tile(a);
+  const int32_t e = __builtin_amdgcn_readfirstlane(a.ea->exp + a.eb->exp);
+  extern __shared__ __align__(16) uint8_t ring_lds[];   // [zero pieces][ring]
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int rg = wave >> 2, ct = wave & 3;              // row group, 16-column tile
+  const int kg = lane >> 4;                             // index group of 16
+  const int lc = lane & 15;
+  const int32_t CRS = a.C * f.RS;
+  const int32_t col0 = tl.tx * 64;
+  const int32_t col = col0 + ct * 16 + lc;
+  const int32_t colc = col < CRS ? col : col0;
+  const int32_t c = colc / f.RS, rs = colc - c * f.RS, r = rs / f.S, s = rs - r * f.S;
+  const TapPos tr = tap_pos(r, f.ph, f.sh), ts = tap_pos(s, f.pw, f.sw);
+  const int32_t pl_lo = (col0 / f.RS) * f.npar;
+  const int32_t pl = c * f.npar + tr.phase * f.sw + ts.phase - pl_lo;
+  const int32_t m0 = tl.ty * kRows;
+  const int32_t g = tl.seg;
+  const int32_t seg_len = a.G * a.L;
+  const int32_t t_seg0 = g * seg_len;
+  const int32_t t_seg1 = (int32_t)min((int64_t)t_seg0 + seg_len, a.T);
+  const int32_t NH = (t_seg1 - t_seg0 + 63) / 64;  // groups of 64 indices (dy digits past T are zero)
+  const int32_t nbands = (NH + 1) / 2;
+
+  const v4i rs_a = rsrc_words(a.ad, a.ad_bytes);
+  const v4i rs_b = rsrc_words(a.xb, a.xb_bytes);
+  const uint32_t a_block = (uint32_t)a.Mp * 64;
+  // Source offset of this lane for each copy instruction of its wave (wave w:
+  // instructions w, w + kWaves, ...), the band start excepted: instruction
+  // q < ainstr fills 64 of the 4 kRows 16-byte pieces of a dy block (row,
+  // piece swizzled as swz), the next xinstr the planes (piece: plane, digit,
+  // 16 bytes), the rest the two selector groups; lanes past the last piece
+  // reload one into padding.
+  // (4 NSUB RG dy instructions: NSUB per wave)
+  constexpr int kMaxB = kRingMaxPer - NSUB;  // plane and selector instructions per wave at most
+  uint32_t va[NSUB], vb[kMaxB];
+#pragma unroll
+  for (int u = 0; u < NSUB; ++u) {
+    const int32_t i = (u * kWaves + wave) * 64 + lane;
+    const int32_t kb = i / (kRows * 4), sl = i - kb * (kRows * 4), row = sl >> 2, pc = (sl & 3) ^ ((row >> 2) & 3);
+    va[u] = (uint32_t)kb * a_block + (uint32_t)((m0 + row) * 64 + pc * 16);
+  }
+  const int32_t binstr = f.tot - f.ainstr;
+#pragma unroll
+  for (int u = 0; u < kMaxB; ++u) {
+    const int32_t q = u * kWaves + wave, i = q * 64 + lane;
+    if (q < f.xinstr) {
+      const int32_t pi = i < f.npl * (f.ch_stride >> 4) ? i : 0;
+      const int32_t k = pi / (f.ch_stride >> 4), w = pi - k * (f.ch_stride >> 4);
+      const int32_t d = w >= f.ppp ? 1 : 0, pc = min(w - d * f.ppp, f.ppp - 1);
+      vb[u] = (uint32_t)(min(pl_lo + k, f.nplanes - 1) * 2 + d) * (uint32_t)f.plane + (uint32_t)pc * 16;
+    } else {
+      const int32_t pi = i - f.xinstr * 64;
+      vb[u] = f.tab + (uint32_t)(pi < 2 * f.nsel * 4 ? pi : 0) * 16;
+    }
+  }
+  const int32_t nb = wave < binstr ? (binstr - wave + kWaves - 1) / kWaves : 0;
+  const int32_t per = NSUB + nb;  // this wave's copies per band
+  if (CL < 64 && threadIdx.x < 4 * NSUB)
+    reinterpret_cast<uint32_t*>(ring_lds + (threadIdx.x >> 2) * 1024)[threadIdx.x & 3] = 0u;
+
+  const uint32_t ring0 = __builtin_amdgcn_readfirstlane(lds_addr(ring_lds) + (uint32_t)kFixed + (uint32_t)wave * 1024u);
+  auto issue_band = [&](int32_t b, int32_t buf) __attribute__((always_inline)) {
+    const int32_t t_b0 = t_seg0 + min(b, nbands - 1) * kSBT;  // bands past the segment reload its last
+    const uint32_t dst = ring0 + (uint32_t)(buf * f.buf_bytes);
+    const uint32_t so_a = (uint32_t)(t_b0 / 32) * a_block, so_x = (uint32_t)t_b0;
+    const uint32_t so_s = (uint32_t)t_b0 * (uint32_t)f.nsel;
+#pragma unroll
+    for (int u = 0; u < NSUB; ++u) dma16(rs_a, dst + u * kWaves * 1024, va[u], so_a);
+    const uint32_t dst_b = dst + (uint32_t)f.ainstr * 1024u;
+#pragma unroll
+    for (int u = 0; u < kMaxB; ++u) {
+      if (u < nb)
+        dma16(rs_b, dst_b + u * kWaves * 1024, vb[u], u * kWaves + wave < f.xinstr ? so_x : so_s);
+    }
+  };
+
+  struct Acc {
+    v4i hh[NSUB], xx[NSUB], ll[NSUB];
+  };
+  Acc acc[2];
+  float sum[NSUB][4];
+#pragma unroll
+  for (int sb = 0; sb < NSUB; ++sb) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sum[sb][v] = 0.f;
+    acc[1].hh[sb] = acc[1].xx[sb] = acc[1].ll[sb] = (v4i){0, 0, 0, 0};  // the chunk "before" the first adds +0
+  }
+  // This lane's operands in the current buffer: dy pieces (hi, lo) of its row
+  // and half of block kg / 2, plane windows (lo, hi), selectors of both groups.
+  typedef __attribute__((address_space(3))) const uint8_t* lds_cp;
+  const lds_cp lds0 = (lds_cp)ring_lds;
+  const uint32_t ofs_a = (uint32_t)(kFixed + (kg >> 1) * kBlockBytes + rg * NSUB * 1024);
+  uint32_t pah = ofs_a + (uint32_t)(swz(lc, 2 * (kg & 1)) * 16);
+  uint32_t pal = ofs_a + (uint32_t)(swz(lc, 2 * (kg & 1) + 1) * 16);
+  uint32_t pxl = (uint32_t)(kFixed + f.ainstr * 1024 + pl * f.ch_stride + kg * 16) +
+                 ((uint32_t)(f.hl + tr.shift * f.Q + ts.shift) & ~3u);
+  uint32_t pxh = pxl + (uint32_t)(f.ppp * 16);  // the hi plane after the lo plane
+  uint32_t ps0 = (uint32_t)(kFixed + (f.ainstr + f.xinstr) * 1024 +
+                            ((tr.shift - f.r0) * f.nsx + ts.shift - f.s0) * 64 + kg * 16);
+  uint32_t ps1 = ps0 + (uint32_t)(f.nsel * 64);
+
+  // dy reads per group of 64 indices: whole, by index half or by quarter
+  constexpr int kParts = CL == 64 ? 1 : CL == 32 ? 2 : 4;
+  struct Win {
+    int lo[5], hi[5];
+    v4i sel;
+  };
+  struct Rows {
+    v4i ah[NSUB], al[NSUB];
+  };
+  Win win[2];
+  Rows rows[2];
+  auto read_win = [&](auto hc) __attribute__((always_inline)) {
+    constexpr int H = decltype(hc)::value;
+    Win& q = win[H];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+      q.lo[i] = *(__attribute__((address_space(3))) const int*)(lds0 + pxl + H * 64 + i * 4);
+      q.hi[i] = *(__attribute__((address_space(3))) const int*)(lds0 + pxh + H * 64 + i * 4);
+    }
+    q.sel = *(__attribute__((address_space(3))) const v4i*)(lds0 + (H ? ps1 : ps0));
+  };
+  auto read_rows = [&](auto pc) __attribute__((always_inline)) {  // part of the band
+    constexpr int PT = decltype(pc)::value, H = PT / kParts, Q = PT % kParts;
+    Rows& d = rows[PT & 1];
+    // the other index groups' lanes read the zero pieces, which start the LDS
+    const bool mine = kParts == 1 || (kParts == 2 ? kg >> 1 : kg) == Q;
+    const uint32_t oh = mine ? pah + H * 2 * kBlockBytes : 0u, ol = mine ? pal + H * 2 * kBlockBytes : 0u;
+#pragma unroll
+    for (int sb = 0; sb < NSUB; ++sb) {
+      d.ah[sb] = *(__attribute__((address_space(3))) const v4i*)(lds0 + oh + sb * 1024);
+      d.al[sb] = *(__attribute__((address_space(3))) const v4i*)(lds0 + ol + sb * 1024);
+    }
+  };
+  auto pm = [](int hi, int lo, int sel) __attribute__((always_inline)) {
+    return (int)__builtin_amdgcn_perm((uint32_t)hi, (uint32_t)lo, (uint32_t)sel);
+  };
+  auto window = [&](const int (&w)[5], const v4i& sel) __attribute__((always_inline)) {
+    return v4i{pm(w[1], w[0], sel.x), pm(w[2], w[1], sel.y), pm(w[3], w[2], sel.z), pm(w[4], w[3], sel.w)};
+  };
+  // converts subtile sb of a finished chunk and adds it
+  auto flush = [&](const Acc& d, int sb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      sum[sb][v] += (float)(int32_t)recombine((uint32_t)d.hh[sb][v], (uint32_t)d.xx[sb][v], (uint32_t)d.ll[sb][v]);
+      asm volatile("" : "+v"(sum[sb][v]));  // here, not sunk to the end
+    }
+  };
+  // one chunk's products into acc[P], subtile by subtile, each followed by the
+  // same subtile's conversion of the previous chunk
+  auto mul = [&](auto pc, const v4i (&ah)[NSUB], const v4i (&al)[NSUB], const v4i& bh, const v4i& bl)
+      __attribute__((always_inline)) {
+    constexpr int PP = decltype(pc)::value;
+    const v4i z = {0, 0, 0, 0};
+    Acc& d = acc[PP];
+#pragma unroll
+    for (int sb = 0; sb < NSUB; ++sb) {
+      d.xx[sb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ah[sb], bl, z, 0, 0, 0);
+      d.hh[sb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ah[sb], bh, z, 0, 0, 0);
+      d.ll[sb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al[sb], bl, z, 0, 0, 0);
+      d.xx[sb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al[sb], bh, d.xx[sb], 0, 0, 0);
+      flush(acc[1 - PP], sb);
+    }
+  };
+  int32_t buf = 0;
+  v4i bh, bl;
+  // Part PT of band b: the next part's operands are requested (NEXT; across
+  // the band's end once the next band has landed in every wave and every wave
+  // has read this one, whose buffer takes the band kRingBufs further on), then
+  // this part is multiplied.  No branch depends on the band: past the segment's
+  // end the ring holds its last band again.
+  auto do_part = [&](auto pc, auto nextc, int32_t b) __attribute__((always_inline)) {
+    constexpr int PT = decltype(pc)::value, H = PT / kParts;
+    if constexpr (PT % kParts == 0) {
+      bh = window(win[H].hi, win[H].sel);
+      bl = window(win[H].lo, win[H].sel);
+    }
+    if constexpr (!decltype(nextc)::value) {
+    } else if constexpr (PT + 1 < 2 * kParts) {
+      if constexpr (PT + 1 == kParts) read_win(IC<1>{});
+      read_rows(IC<PT + 1>{});
+    } else {
+      wait_copies((kRingBufs - 2) * per);
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      issue_band(b + kRingBufs, buf);
+      buf = buf + 1 == kRingBufs ? 0 : buf + 1;
+      const uint32_t d = (uint32_t)(buf == 0 ? -(kRingBufs - 1) * f.buf_bytes : f.buf_bytes);
+      pah += d; pal += d; pxl += d; pxh += d; ps0 += d; ps1 += d;
+      read_win(IC<0>{});
+      read_rows(IC<0>{});
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const Rows& q = rows[PT & 1];
+    if constexpr (CL == 64) {
+      mul(IC<H>{}, q.ah, q.al, bh, bl);
+    } else if constexpr (CL >= 16) {
+      mul(IC<PT & 1>{}, q.ah, q.al, bh, bl);
+    } else {
+      v4i ph[NSUB], pl8[NSUB];
+#pragma unroll
+      for (int sb = 0; sb < NSUB; ++sb) {
+        ph[sb] = (v4i){q.ah[sb].x, q.ah[sb].y, 0, 0};
+        pl8[sb] = (v4i){q.al[sb].x, q.al[sb].y, 0, 0};
+      }
+      mul(IC<0>{}, ph, pl8, bh, bl);
+#pragma unroll
+      for (int sb = 0; sb < NSUB; ++sb) {
+        ph[sb] = (v4i){0, 0, q.ah[sb].z, q.ah[sb].w};
+        pl8[sb] = (v4i){0, 0, q.al[sb].z, q.al[sb].w};
+      }
+      mul(IC<1>{}, ph, pl8, bh, bl);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+#pragma unroll
+  for (int b = 0; b < kRingBufs; ++b) issue_band(b, b);
+  wait_copies((kRingBufs - 1) * per);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  read_win(IC<0>{});
+  read_rows(IC<0>{});
+  const auto yes = std::true_type{};
+  const auto no = std::false_type{};
+  for (int32_t b = 0; b < NH / 2; ++b) {
+    do_part(IC<0>{}, yes, b);
+    do_part(IC<1>{}, yes, b);
+    if constexpr (kParts >= 2) {
+      do_part(IC<2>{}, yes, b);
+      do_part(IC<3>{}, yes, b);
+    }
+    if constexpr (kParts == 4) {
+      do_part(IC<4>{}, yes, b);
+      do_part(IC<5>{}, yes, b);
+      do_part(IC<6>{}, yes, b);
+      do_part(IC<7>{}, yes, b);
+    }
+  }
+  if (NH & 1) {  // a last group by itself
+    do_part(IC<0>{}, std::integral_constant<bool, (kParts > 1)>{}, 0);
+    if constexpr (kParts == 2) do_part(IC<1>{}, no, 0);
+    if constexpr (kParts == 4) {
+      do_part(IC<1>{}, yes, 0);
+      do_part(IC<2>{}, yes, 0);
+      do_part(IC<3>{}, no, 0);
+    }
+  }
+#pragma unroll
+  for (int sb = 0; sb < NSUB; ++sb) {
+    if (CL == 64 && (NH & 1)) flush(acc[0], sb);
+    else flush(acc[1], sb);
+  }
+  wait_vmcnt<0>();  // no copy outlives the workgroup's LDS
+
+  if (col < CRS) {
+    float* dst = a.nseg == 1 ? a.out : a.useg + (int64_t)g * a.O;
+#pragma unroll
+    for (int sb = 0; sb < NSUB; ++sb) {
+      const int32_t row = m0 + (rg * NSUB + sb) * 16 + 4 * kg;
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (row + v < a.K) dst[(uint32_t)((row + v) * CRS + col)] = a.nseg == 1 ? ldexpf(sum[sb][v], e) : sum[sb][v];
+    }
+  }
+}
+
 // dW = 2^e * (((U_0 + U_1) + U_2) + ...), segment order.
 __global__ __launch_bounds__(64) void k_seg_reduce(const float* __restrict__ useg, float* __restrict__ out, int64_t O,
                                                   int32_t nseg, const dfp_scale* ea, const dfp_scale* eb) {
@@ -1914,9 +2367,150 @@ static FlatLayout flat_layout(const Geom& g) {
   return f;
 }
 
-BwdwPlan plan_bwdw_mfma(const Geom& g) {
+// Ring kernel: whether the layer qualifies, its operand layout and tiles.
+struct RingLayout {
+  RingArgs f;
+  int32_t hh, rows;        // halo after t; rows per workgroup
+  int32_t ngroups, kbt;    // selector groups; dy blocks (padded to whole bands past T)
+  int64_t xb_bytes, ad_bytes;
+  size_t lds;
+  bool ok;
+};
+static RingLayout ring_layout(const Geom& g) {
+  RingLayout y{};
+  const int64_t T = (int64_t)g.n * g.p * g.q;
+  const int64_t seg_len = (int64_t)g.G * g.L;
+  if ((g.L != 64 && g.L != 32 && g.L != 16 && g.L != 8) || (seg_len % 64 != 0 && seg_len < T)) return y;
+  if ((g.h + g.sh - 1) / g.sh > g.p || (g.w + g.sw - 1) / g.sw > g.q || g.sh > 4 || g.sw > 4) return y;
+  if (T + 4096 >= (1ll << 31) || seg_len >= (1ll << 31)) return y;
+  RingArgs& f = y.f;
+  f.RS = g.r * g.s;
+  f.S = g.s;
+  f.sh = g.sh; f.sw = g.sw; f.ph = g.ph; f.pw = g.pw; f.Q = g.q;
+  f.npar = g.sh * g.sw;
+  f.r0 = tap_pos(0, g.ph, g.sh).shift;
+  f.s0 = tap_pos(0, g.pw, g.sw).shift;
+  const int32_t r1 = tap_pos(g.r - 1, g.ph, g.sh).shift, s1 = tap_pos(g.s - 1, g.pw, g.sw).shift;
+  f.nsx = s1 - f.s0 + 1;
+  f.nsel = (r1 - f.r0 + 1) * f.nsx;
+  const int64_t dmin = (int64_t)f.r0 * g.q + f.s0, dmax = (int64_t)r1 * g.q + s1;
+  if (dmin < -2048 || dmax > 2048 || f.nsel > 32) return y;
+  f.hl = (int32_t)(std::max<int64_t>(0, -dmin) + 15) / 16 * 16;
+  y.hh = (int32_t)(std::max<int64_t>(0, dmax) + 15) / 16 * 16;
+  const int32_t band = f.hl + kSBT + y.hh + 16;
+  f.ppp = band / 16;
+  // an odd number of 16-byte pieces per plane pair, so that the planes of a
+  // wave's columns fall on different LDS banks
+  f.ch_stride = 2 * band + (2 * f.ppp % 2 == 0 ? 16 : 0);
+  f.nplanes = g.c * f.npar;
+  f.plane = (int32_t)((T + band + 15) / 16 * 16);
+  y.ngroups = (int32_t)(T / 64 + 4);
+  y.kbt = (int32_t)((T + kSBT - 1) / kSBT + 1) * (kSBT / 32);
+  const int32_t Mp = (g.k + kMT - 1) / kMT * kMT;
+  y.ad_bytes = ((int64_t)y.kbt * Mp * 64 + 255) / 256 * 256;
+  const int64_t tab = ((int64_t)f.nplanes * 2 * f.plane + 255) / 256 * 256;
+  y.xb_bytes = tab + (int64_t)y.ngroups * f.nsel * 64;
+  if (y.ad_bytes >= (1ll << 31) || y.xb_bytes >= (1ll << 31) || (int64_t)g.k * g.c * f.RS >= (1ll << 30)) return y;
+  f.tab = (uint32_t)tab;
+  y.rows = g.k <= 32 ? 32 : 64;
+  f.npl = std::min(g.c, 63 / f.RS + 2) * f.npar;
+  f.ainstr = y.rows / 4;
+  f.xinstr = (f.npl * (f.ch_stride / 16) + 63) / 64;
+  f.tot = f.ainstr + f.xinstr + (2 * f.nsel * 4 + 63) / 64;
+  if (f.tot - f.ainstr > 4 * (kRingMaxPer - 4)) return y;  // (the widest wave: four dy copies)
+  f.buf_bytes = f.tot * 1024;
+  y.lds = (size_t)kRingBufs * f.buf_bytes + (g.L < 64 ? 4096 : 0);
+  if (y.lds > 160 * 1024) return y;
+  y.ok = true;
+  return y;
+}
+
+template <int CL, int NSUB, int RG>
+static dfp_status launch_ring_kernel(const RingLayout& y, const BwdwArgs& args, dim3 grid, hipStream_t st) {
+  static const bool set = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bwdw_ring<CL, NSUB, RG>),
+                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess;
+  (void)set;
+  DFP_LAUNCH(K_BWDW_MFMA, (k_bwdw_ring<CL, NSUB, RG>), grid, dim3(256 * RG), y.lds, st, args, y.f);
+  return DFP_OK;
+}
+template <int CL>
+static dfp_status launch_ring_cl(const RingLayout& y, const BwdwArgs& args, dim3 grid, hipStream_t st) {
+  // Longer chunks convert little per product and want the fewest operand
+  // reads (64 rows per wave); shorter ones are bound by their conversions and
+  // want more waves (ResNet-50 conv2_x at N = 32, L = 16: 73 us with four
+  // waves per workgroup, 69 us with eight, 75 us with sixteen of one subtile).
+  if (y.rows == 32) return launch_ring_kernel<CL, 2, 1>(y, args, grid, st);
+  if constexpr (CL == 64) return launch_ring_kernel<CL, 4, 1>(y, args, grid, st);
+  else return launch_ring_kernel<CL, 2, 2>(y, args, grid, st);
+}
+
+static dfp_status launch_ring(const Geom& g, const BwdwPlan& p, const RingLayout& y, const int16_t* x,
+                              const dfp_scale* sx, const int16_t* dy, const dfp_scale* sdy, float* dw, void* ws,
+                              hipStream_t st) {
+  uint8_t* base = reinterpret_cast<uint8_t*>(ws);
+  uint8_t* ad = base;
+  uint8_t* xf = base + p.ad_bytes;
+  float* useg = reinterpret_cast<float*>(base + p.ad_bytes + p.xp_bytes);
+  const int32_t PQ = g.p * g.q;
+  const bool plain = y.f.npar == 1 && g.h == g.p && g.w == g.q;
+  const int32_t vec = plain && PQ % 8 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0 ? 8
+                      : plain && PQ % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 7) == 0 ? 4
+                      : g.sw == 2 && g.w == 2 * g.q && g.q % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0 ? 2
+                                                                                                                  : 1;
+  const RingPrep f{x, xf, g.c, g.h, g.w, g.p, g.q, PQ, (int32_t)p.T, y.f.plane, y.f.hl, y.ngroups, g.sh, g.sw,
+                   y.f.npar, y.f.nsel, y.f.r0, y.f.s0, y.f.nsx, y.f.tab, vec, make_fastdiv((uint32_t)PQ),
+                   make_fastdiv((uint32_t)g.q)};
+  const DyPrep dq{dy, ad, g.k, p.Mp, PQ, (int32_t)p.T, y.kbt};
+  const int64_t nbx =
+      ((int64_t)(vec == 2 ? g.c * g.sh : y.f.nplanes) * (y.f.plane / (vec == 8 ? 8 : 4)) + 255) / 256;
+  const int64_t nbt = ((int64_t)y.ngroups * y.f.nsel * 16 + 255) / 256;
+  const int64_t nby = ((int64_t)y.kbt * p.Mp * 2 + 255) / 256;
+  DFP_LAUNCH(K_XPREP, k_prep_ring, dim3((unsigned)(nbx + nbt + nby)), dim3(256), 0, st, f, dq, (int32_t)nbx,
+             (int32_t)nbt);
+  BwdwArgs args{};
+  args.ad = ad;
+  args.xb = xf;
+  args.ea = sx;
+  args.eb = sdy;
+  args.out = dw;
+  args.useg = useg;
+  args.T = p.T;
+  args.O = (int64_t)g.k * g.c * y.f.RS;
+  args.K = g.k; args.Mp = p.Mp; args.C = g.c;
+  args.L = g.L; args.G = g.G; args.nseg = p.nseg;
+  args.ad_bytes = (uint32_t)y.ad_bytes;
+  args.xb_bytes = (uint32_t)y.xb_bytes;
+  args.ntx = (int32_t)(((int64_t)g.c * y.f.RS + 63) / 64);
+  args.nty = (g.k + y.rows - 1) / y.rows;
+  const dim3 grid((unsigned)(p.nseg * args.ntx * args.nty));
+  dfp_status rc = g.L == 64   ? launch_ring_cl<64>(y, args, grid, st)
+                  : g.L == 32 ? launch_ring_cl<32>(y, args, grid, st)
+                  : g.L == 16 ? launch_ring_cl<16>(y, args, grid, st)
+                              : launch_ring_cl<8>(y, args, grid, st);
+  if (rc != DFP_OK) return rc;
+  if (p.nseg > 1)
+    DFP_LAUNCH(K_BWDW_REDUCE, k_seg_reduce, dim3((unsigned)((args.O + 63) / 64)), dim3(64), 0, st, useg, dw, args.O,
+               p.nseg, sx, sdy);
+  return DFP_OK;
+}
+
+// The layers the ring kernel takes (calls without partials), measured at N =
+// 32 and the default segments: every chunk length below 64 (conv2_x 3x3 at L =
+// 32 / 16 / 8: 49 / 74 / 121 us, 136 / 325 / 492 on the band and general kernels)
+// except 1x1 layers at 32, which have a kernel of their own; at 64 the layers
+// neither the flat-band kernel (41 us on conv2_x, 39 here, but 51 against 59
+// on res5 and 55 against 74 on VGG-16's 224-wide rows) nor the band kernels
+// take: reductions that are not a multiple of 64, other filters and strides
+// (ResNet-50 stem 101 us, 176 on the general kernel; 45 images of 26 x 26, 80
+// to 120 channels, 34 us and 153).
+static bool ring_wanted(const Geom& g) {
+  if (unit_1x1(g) ? g.L % 32 == 0 : g.L == 64 && flat_geom(g)) return false;
+  return ring_layout(g).ok;
+}
+
+BwdwPlan plan_bwdw_mfma(const Geom& g, bool ring) {
   if (strided_1x1(g)) {
-    BwdwPlan p = plan_bwdw_mfma(subsampled(g));
+    BwdwPlan p = plan_bwdw_mfma(subsampled(g), ring);
     p.sub_bytes = align256((int64_t)g.n * g.c * g.p * g.q * 2);
     p.bytes += p.sub_bytes;
     return p;
@@ -1953,6 +2547,11 @@ BwdwPlan plan_bwdw_mfma(const Geom& g) {
   p.xp_bytes = align256((int64_t)g.c * g.n * p.Hpad * (2 * p.Wpad + 16));
   if (unit_1x1(g)) p.xp_bytes = std::max<int64_t>(p.xp_bytes, align256(p.KBT * ((g.c + 63) / 64 * 64) * 64));
   if (flat_geom(g)) p.xp_bytes = std::max<int64_t>(p.xp_bytes, align256(flat_layout(g).bytes));
+  if (ring && ring_wanted(g)) {
+    const RingLayout y = ring_layout(g);
+    p.ad_bytes = std::max<int64_t>(p.ad_bytes, y.ad_bytes);
+    p.xp_bytes = std::max<int64_t>(p.xp_bytes, align256(y.xb_bytes));
+  }
   p.u_bytes = p.nseg > 1 ? align256((int64_t)p.nseg * g.k * g.c * RS * 4) : 0;
   p.bytes = p.ad_bytes + p.xp_bytes + p.u_bytes;
   return p;
@@ -1993,9 +2592,9 @@ bool bwdw_mfma_supported(const Geom& g) {
 }
 
 dfp_status launch_bwdw_mfma(const Geom& g, const int16_t* x, const dfp_scale* sx, const int16_t* dy,
-                            const dfp_scale* sdy, float* dw, int32_t* partials, void* ws, hipStream_t st) {
+                            const dfp_scale* sdy, float* dw, int32_t* partials, void* ws, hipStream_t st, bool ring) {
   if (strided_1x1(g)) {
-    const BwdwPlan p = plan_bwdw_mfma(g);
+    const BwdwPlan p = plan_bwdw_mfma(g, ring);
     int16_t* xs = reinterpret_cast<int16_t*>(reinterpret_cast<uint8_t*>(ws) + (p.bytes - p.sub_bytes));
     const int64_t planes = (int64_t)g.n * g.c;
     const int32_t gx = (g.p * g.q + 255) / 256;
@@ -2003,9 +2602,9 @@ dfp_status launch_bwdw_mfma(const Geom& g, const int16_t* x, const dfp_scale* sx
     DFP_LAUNCH(K_XPREP, k_subsample, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, st, x, xs, planes, g.h, g.w,
                g.p, g.q, g.sh, g.sw);
     // the subsampled plan's workspace ends where xs begins
-    return launch_bwdw_mfma(subsampled(g), xs, sx, dy, sdy, dw, partials, ws, st);
+    return launch_bwdw_mfma(subsampled(g), xs, sx, dy, sdy, dw, partials, ws, st, ring);
   }
-  const BwdwPlan p = plan_bwdw_mfma(g);
+  const BwdwPlan p = plan_bwdw_mfma(g, ring);
   uint8_t* base = reinterpret_cast<uint8_t*>(ws);
   uint8_t* ad = base;
   uint16_t* xp = reinterpret_cast<uint16_t*>(base + p.ad_bytes);
@@ -2105,11 +2704,13 @@ dfp_status launch_bwdw_mfma(const Geom& g, const int16_t* x, const dfp_scale* sx
     return DFP_OK;
   }
   const bool l64 = g.L == 64 && (p.T % 64) == 0;  // every segment a whole number of two-block chunks
+  const bool to_ring = ring && !partials && ring_wanted(g);
   // runs of 4 and big buffers: the eight-wave kernel only (L = 64, no partials)
   const bool band_ok = bl.big ? (bl.run == 8 && l64 && !partials && safe.w8_big)
                        : bl.run == 8 ? (l64 ? (partials ? safe.skew_t : (safe.w8 || safe.skew_f))
                                             : (partials ? safe.band_t : safe.band_f))
                                      : (l64 && !partials && safe.w8_r4);
+  if (to_ring && (g.L < 64 || !band_ok || bl.buf_bytes == 0)) return launch_ring(g, p, ring_layout(g), x, sx, dy, sdy, dw, ws, st);
   if (band_ok && bl.buf_bytes > 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0 && p.ad_bytes < (1ll << 31) &&
       p.xp_bytes < (1ll << 31)) {
     uint8_t* xb = reinterpret_cast<uint8_t*>(xp);  // same workspace region as the pair layout
