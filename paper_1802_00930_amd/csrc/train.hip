@@ -14,9 +14,16 @@
 //
 // Passes (all HBM-bound):
 //   forward   k_bn_stats (y) -> k_bn_finalize -> [res: k_bn_amax + max reduce]
-//             -> k_bn_convert (y [, res]) writing zq [and z]
-//   backward  k_bn_stats (y, dz [, res]) -> k_bn_finalize -> k_bn_amax (writes
-//             dy / dres if asked) -> max reduce -> k_bn_convert
+//             -> k_bn_convert (y [, res]) writing zq [and z]; with res and z
+//             the max pass writes z and the tensor quantiser reads it
+//   backward  k_bn_stats (y, dz [, res]; with res it leaves the ReLU mask, a
+//             byte per four elements, so that res is read once) ->
+//             k_bn_finalize -> k_bn_amax (writes dy / dres if asked) -> max
+//             reduce -> k_bn_convert (or, with dy, the tensor quantiser)
+// 64 x 256 x 56 x 56 with a residual, z and dres (26 B per element at least):
+// forward stats 20, max pass + z 88, quantiser 59 us; backward stats 105, max
+// pass 74, convert 65 us (742 -> 429 us in all; copies run at 5.1 TB/s, the
+// passes at 3.9 to 5.7).
 //   SGD       k_sgd (update + max) -> max reduce -> the tensor quantiser
 // Without a residual the forward output is a monotone function of the input
 // integer within a channel (ReLU of an affine map evaluated with monotone
@@ -26,6 +33,7 @@
 
 #include <algorithm>
 #include <climits>
+#include <type_traits>
 
 #include "dfp_internal.h"
 #include "dfp_round.h"
@@ -35,7 +43,7 @@ namespace dfp {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kMaxParts = 1024;
+constexpr int kMaxParts = 2048;
 
 struct Chan {
   float mean, inv, gamma, beta;
@@ -49,23 +57,9 @@ __device__ __forceinline__ Chan load_chan(const float* mean, const float* inv, c
 __device__ __forceinline__ float bn_xhat(int32_t yi, int32_t ey, const Chan& p) {
   return __fmul_rn(__fsub_rn(ldexpf((float)yi, ey), p.mean), p.inv);
 }
-// Pre-activation gamma * xhat + beta (fused), plus the residual if any.
-__device__ __forceinline__ float bn_pre(float xh, const Chan& p, const float* res, int32_t idx) {
-  const float zp = __fmaf_rn(xh, p.gamma, p.beta);
-  return res ? __fadd_rn(zp, res[idx]) : zp;
-}
+// gamma * xhat + beta (fused); the residual, if any, is added to it.
+__device__ __forceinline__ float bn_affine(float xh, const Chan& p) { return __fmaf_rn(xh, p.gamma, p.beta); }
 __device__ __forceinline__ float relu(float v) { return v > 0.0f ? v : 0.0f; }
-
-// Gradient at y of one element: dy = fma(k1, g, fma(k2, xhat, k3)) with
-// g = pre > 0 ? dz 2^Edz : 0; also returns g (the gradient at res).
-__device__ __forceinline__ float bn_dy(int32_t yi, int32_t dzi, int32_t ey, int32_t edz, const Chan& p,
-                                       const float4& k, const float* res, int32_t idx, float* g_out) {
-  const float xh = bn_xhat(yi, ey, p);
-  const float pre = bn_pre(xh, p, res, idx);
-  const float g = pre > 0.0f ? ldexpf((float)dzi, edz) : 0.0f;
-  *g_out = g;
-  return __fmaf_rn(k.x, g, __fmaf_rn(k.y, xh, k.z));
-}
 
 __device__ __forceinline__ int32_t lo16(uint32_t w) { return (int32_t)(int16_t)(w & 0xffffu); }
 __device__ __forceinline__ int32_t hi16(uint32_t w) { return (int32_t)w >> 16; }
@@ -76,21 +70,20 @@ __device__ __forceinline__ int32_t hi16(uint32_t w) { return (int32_t)w >> 16; }
 // Pd = sum g_i * y_i with g_i = dz_i where the recomputed pre-activation is
 // positive, else 0.  Partials: part[(s*C + c)*3 + {0, 1, 2}], slot 2 holding
 // (max << 32) | (uint32)min.  VEC: 8 elements per unit (hw % 8 == 0).
-template <bool BWD, bool VEC>
+template <bool BWD, int V, bool RES>
 __global__ __launch_bounds__(kBlock) void k_bn_stats(const int16_t* __restrict__ y, const int16_t* __restrict__ dz,
                                                      const float* __restrict__ res, const float* __restrict__ mean,
                                                      const float* __restrict__ inv, const float* __restrict__ gamma,
                                                      const float* __restrict__ beta, const dfp_scale* __restrict__ sy,
-                                                     const dfp_scale* __restrict__ sdz, int32_t N, int32_t C,
-                                                     int32_t HW, int32_t S, FastDiv upr_div,
-                                                     int64_t* __restrict__ part, dfp_scale* __restrict__ sz) {
+                                                     int32_t N, int32_t C, int32_t HW, int32_t S, FastDiv upr_div,
+                                                     int64_t* __restrict__ part, uint8_t* __restrict__ mask,
+                                                     dfp_scale* __restrict__ sz) {
   const int32_t s = blockIdx.x, c = blockIdx.y;
   if (sz && s == 0 && c == 0 && threadIdx.x == 0) {  // the finalize kernel max-reduces into it
     sz->amax_bits = 0u;
     sz->flags = 0u;
   }
   const int32_t n0 = (int32_t)((int64_t)N * s / S), n1 = (int32_t)((int64_t)N * (s + 1) / S);
-  constexpr int V = VEC ? 8 : 1;
   const int32_t upr = HW / V;
   const int32_t units = (n1 - n0) * upr;
   int64_t a = 0, b = 0;
@@ -101,40 +94,73 @@ __global__ __launch_bounds__(kBlock) void k_bn_stats(const int16_t* __restrict__
     p = load_chan(mean, inv, gamma, beta, c);
     ey = sy->exp;
   }
-  (void)sdz;
-  for (int32_t j = threadIdx.x; j < units; j += kBlock) {
-    const int32_t r = (int32_t)fdiv((uint32_t)j, upr_div);
-    const int32_t off = ((n0 + r) * C + c) * HW + (j - r * upr) * V;
-    int32_t yv[V], dv[V];
-    if (VEC) {
-      const uint4 w = *reinterpret_cast<const uint4*>(y + off);
-      const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) { yv[2 * q] = lo16(ws[q]); yv[2 * q + 1] = hi16(ws[q]); }
-      if (BWD) {
-        const uint4 d = *reinterpret_cast<const uint4*>(dz + off);
-        const uint32_t ds[4] = {d.x, d.y, d.z, d.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) { dv[2 * q] = lo16(ds[q]); dv[2 * q + 1] = hi16(ds[q]); }
+  // one unit's loads (V elements); the next unit's are in flight while one is summed
+  struct Unit {
+    int32_t off;
+    uint32_t y[(V + 1) / 2], d[(V + 1) / 2];
+    float r[V];
+  };
+  auto load = [&](int32_t j) {
+    Unit u;
+    const int32_t row = (int32_t)fdiv((uint32_t)j, upr_div);
+    u.off = ((n0 + row) * C + c) * HW + (j - row * upr) * V;
+    auto ints = [&](const int16_t* src, uint32_t(&w)[(V + 1) / 2]) {
+      if constexpr (V == 8) {
+        const uint4 q = *reinterpret_cast<const uint4*>(src + u.off);
+        w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
+      } else if constexpr (V == 4) {
+        const uint2 q = *reinterpret_cast<const uint2*>(src + u.off);
+        w[0] = q.x; w[1] = q.y;
+      } else {
+        w[0] = (uint16_t)src[u.off];
       }
-    } else {
-      yv[0] = y[off];
-      if (BWD) dv[0] = dz[off];
+    };
+    ints(y, u.y);
+    if (BWD) ints(dz, u.d);
+    if (BWD && RES) {
+      if constexpr (V >= 4) {
+#pragma unroll
+        for (int q = 0; q < V / 4; ++q) {
+          const float4 f = *reinterpret_cast<const float4*>(res + u.off + 4 * q);
+          u.r[4 * q] = f.x; u.r[4 * q + 1] = f.y; u.r[4 * q + 2] = f.z; u.r[4 * q + 3] = f.w;
+        }
+      } else {
+        u.r[0] = res[u.off];
+      }
     }
+    return u;
+  };
+  auto add = [&](const Unit& u) {
+    uint32_t bits = 0u;
 #pragma unroll
     for (int q = 0; q < V; ++q) {
+      const int32_t yv = (q & 1) ? hi16(u.y[q >> 1]) : lo16(u.y[q >> 1]);
       if (BWD) {
-        const float pre = bn_pre(bn_xhat(yv[q], ey, p), p, res, off + q);
-        const int32_t g = pre > 0.0f ? dv[q] : 0;
+        const float zp = bn_affine(bn_xhat(yv, ey, p), p);
+        const float pre = RES ? __fadd_rn(zp, u.r[q]) : zp;
+        const int32_t dv = (q & 1) ? hi16(u.d[q >> 1]) : lo16(u.d[q >> 1]);
+        const int32_t g = pre > 0.0f ? dv : 0;
+        if (RES) bits |= (pre > 0.0f ? 1u : 0u) << q;
         a += g;
-        b += g * yv[q];  // |g y| <= 2^30
+        b += g * yv;  // |g y| <= 2^30
       } else {
-        a += yv[q];
-        b += yv[q] * yv[q];
-        mn = min(mn, yv[q]);
-        mx = max(mx, yv[q]);
+        a += yv;
+        b += yv * yv;
+        mn = min(mn, yv);
+        mx = max(mx, yv);
       }
     }
+    if (BWD && RES && V == 4) mask[u.off >> 2] = (uint8_t)bits;
+  };
+  int32_t j = threadIdx.x;
+  if (j < units) {
+    Unit u = load(j);
+    for (; j + kBlock < units; j += kBlock) {
+      const Unit nx = load(j + kBlock);
+      add(u);
+      u = nx;
+    }
+    add(u);
   }
   __shared__ int64_t ra[kBlock], rb[kBlock];
   __shared__ int32_t rmn[kBlock], rmx[kBlock];
@@ -175,8 +201,8 @@ __global__ __launch_bounds__(kBlock) void k_bn_finalize(const int64_t* __restric
                                                         const float* __restrict__ beta, float* __restrict__ mean,
                                                         float* __restrict__ inv, int64_t* __restrict__ sums,
                                                         float* __restrict__ dgamma, float* __restrict__ dbeta,
-                                                        float4* __restrict__ kco, dfp_scale* __restrict__ sz,
-                                                        bool write_max) {
+                                                        float4* __restrict__ kco, float4* __restrict__ chan,
+                                                        dfp_scale* __restrict__ sz, bool write_max) {
   const int lane = threadIdx.x & 63;
   const int32_t c = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
   if (c >= C) return;
@@ -214,10 +240,11 @@ __global__ __launch_bounds__(kBlock) void k_bn_finalize(const int64_t* __restric
     const float iv = __fdiv_rn(1.0f, sq);
     mean[c] = mf;
     inv[c] = iv;
+    chan[c] = make_float4(mf, iv, gamma[c], beta[c]);
     if (write_max) {
       const Chan p{mf, iv, gamma[c], beta[c]};
-      const float zlo = relu(bn_pre(bn_xhat(mn, ey, p), p, nullptr, 0));
-      const float zhi = relu(bn_pre(bn_xhat(mx, ey, p), p, nullptr, 0));
+      const float zlo = relu(bn_affine(bn_xhat(mn, ey, p), p));
+      const float zhi = relu(bn_affine(bn_xhat(mx, ey, p), p));
       const uint32_t m = max(__float_as_uint(zlo), __float_as_uint(zhi)) & 0x7fffffffu;
       if (m) atomicMax(&sz->amax_bits, m);
     }
@@ -230,6 +257,7 @@ __global__ __launch_bounds__(kBlock) void k_bn_finalize(const int64_t* __restric
     dbeta[c] = dbf;
     dgamma[c] = dgf;
     const double al = __dmul_rn((double)gamma[c], iv);  // exact: two FP32 factors
+    chan[c] = make_float4(mean[c], inv[c], gamma[c], beta[c]);
     kco[c] = make_float4((float)al, (float)__ddiv_rn(__dmul_rn(-al, (double)dgf), dcnt),
                          (float)__ddiv_rn(__dmul_rn(-al, (double)dbf), dcnt), 0.0f);
   }
@@ -241,17 +269,15 @@ __global__ __launch_bounds__(kBlock) void k_bn_finalize(const int64_t* __restric
 struct Elems {
   const int16_t* y;
   const int16_t* dz;
-  const float* res;
-  const float* mean;
-  const float* inv;
-  const float* gamma;
-  const float* beta;
+  const float* res;     // null where the mask replaces it
+  const uint8_t* mask;  // backward with res and hw % 4 == 0: bit q of byte g, element 4 g + q passes the ReLU
+  const float4* chan;   // mean, inv_std, gamma, beta
   const float4* kco;
   const dfp_scale* sy;
   const dfp_scale* sdz;
   int32_t total, C;
   FastDiv hw_div, c_div;
-  bool hw4;  // hw % 4 == 0: a group lies in one channel
+  bool hw4;  // hw % 4 == 0
 };
 
 __device__ __forceinline__ int32_t chan_of(const Elems& e, int32_t idx) {
@@ -259,77 +285,129 @@ __device__ __forceinline__ int32_t chan_of(const Elems& e, int32_t idx) {
   return (int32_t)(row - fdiv(row, e.c_div) * (uint32_t)e.C);
 }
 
-// Values of the group starting at base (valid lanes < cnt): the forward output
-// z or the backward gradient dy (and g, the gradient at res).
-template <bool BWD>
-__device__ __forceinline__ void group_values(const Elems& e, int32_t base, int32_t cnt, int32_t ey, int32_t edz,
-                                             float v[4], float g[4]) {
-  int32_t yi[4] = {0, 0, 0, 0}, di[4] = {0, 0, 0, 0};
-  if (cnt == 4) {
-    const uint2 w = *reinterpret_cast<const uint2*>(e.y + base);
-    yi[0] = lo16(w.x); yi[1] = hi16(w.x); yi[2] = lo16(w.y); yi[3] = hi16(w.y);
-    if (BWD) {
-      const uint2 d = *reinterpret_cast<const uint2*>(e.dz + base);
-      di[0] = lo16(d.x); di[1] = hi16(d.x); di[2] = lo16(d.y); di[3] = hi16(d.y);
-    }
+// A group's operands, loaded ahead of their use (the last group may be short).
+//   HW4: hw % 4 == 0, so a group lies in one channel.  SRC: where the ReLU's
+//   sign comes from: kPlain the affine value, kRes that plus the residual,
+//   kMask (backward, HW4, with a residual) the mask of the statistics pass.
+enum Src { kPlain = 0, kRes = 1, kMask = 2 };
+struct Group {
+  uint2 y, d;
+  float4 r;
+  uint32_t mask;
+  float4 p, k;  // channel values (HW4)
+};
+__device__ __forceinline__ int32_t group_int(const uint2& w, int q) {
+  const uint32_t v = q < 2 ? w.x : w.y;
+  return (q & 1) ? hi16(v) : lo16(v);
+}
+__device__ __forceinline__ uint2 short_group(const int16_t* src, int32_t left) {
+  const uint32_t a = (uint16_t)src[0], b = left > 1 ? (uint16_t)src[1] : 0u, c = left > 2 ? (uint16_t)src[2] : 0u;
+  return make_uint2(a | (b << 16), c);
+}
+template <bool BWD, bool HW4, int SRC>
+__device__ __forceinline__ Group load_group(const Elems& e, int32_t gi) {
+  Group g;
+  const int32_t base = gi << 2;
+  const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
+  g.d = make_uint2(0u, 0u);
+  g.r = g.p = g.k = z4;
+  if (base + 4 <= e.total) {
+    g.y = *reinterpret_cast<const uint2*>(e.y + base);
+    if (BWD) g.d = *reinterpret_cast<const uint2*>(e.dz + base);
+    if (SRC == kRes) g.r = *reinterpret_cast<const float4*>(e.res + base);
   } else {
-    for (int q = 0; q < cnt; ++q) {
-      yi[q] = e.y[base + q];
-      if (BWD) di[q] = e.dz[base + q];
-    }
+    const int32_t left = e.total - base;
+    g.y = short_group(e.y + base, left);
+    if (BWD) g.d = short_group(e.dz + base, left);
+    if (SRC == kRes) g.r = make_float4(e.res[base], left > 1 ? e.res[base + 1] : 0.f, left > 2 ? e.res[base + 2] : 0.f, 0.f);
   }
-  Chan p{};
-  float4 k{};
-  int32_t c0 = -1;
-  if (e.hw4) {
-    c0 = chan_of(e, base);
-    p = load_chan(e.mean, e.inv, e.gamma, e.beta, c0);
-    if (BWD) k = e.kco[c0];
+  g.mask = SRC == kMask ? e.mask[gi] : 0u;
+  if (HW4) {
+    const int32_t c = chan_of(e, base);
+    g.p = e.chan[c];
+    if (BWD) g.k = e.kco[c];
   }
+  return g;
+}
+
+// Values of group gi (elements past the tensor's end: 0): the forward output
+// z, or the backward gradient dy = fma(k1, g, fma(k2, xhat, k3)) with g =
+// pre > 0 ? dz 2^Edz : 0, which is also the gradient at res.
+template <bool BWD, bool HW4, int SRC>
+__device__ __forceinline__ void group_values(const Elems& e, Group in, int32_t gi, int32_t ey, int32_t edz,
+                                             float v[4], float g[4]) {
+  const int32_t base = gi << 2;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     v[q] = 0.0f;
     g[q] = 0.0f;
-    if (q >= cnt) continue;
-    if (!e.hw4) {
+    if (base + q >= e.total) continue;
+    float4 pc = in.p, k = in.k;
+    if (!HW4) {
       const int32_t c = chan_of(e, base + q);
-      p = load_chan(e.mean, e.inv, e.gamma, e.beta, c);
+      pc = e.chan[c];
       if (BWD) k = e.kco[c];
     }
-    if (BWD) v[q] = bn_dy(yi[q], di[q], ey, edz, p, k, e.res, base + q, &g[q]);
-    else v[q] = relu(bn_pre(bn_xhat(yi[q], ey, p), p, e.res, base + q));
+    const Chan p{pc.x, pc.y, pc.z, pc.w};
+    const int32_t yi = group_int(in.y, q);
+    const float xh = bn_xhat(yi, ey, p);
+    bool pass = false;
+    float pre = 0.0f;
+    if (SRC == kMask) {
+      pass = (in.mask >> q) & 1u;
+    } else {
+      pre = bn_affine(xh, p);
+      if (SRC == kRes) pre = __fadd_rn(pre, q == 0 ? in.r.x : q == 1 ? in.r.y : q == 2 ? in.r.z : in.r.w);
+      pass = pre > 0.0f;
+    }
+    if (BWD) {
+      const int32_t di = group_int(in.d, q);
+      g[q] = pass ? ldexpf((float)di, edz) : 0.0f;
+      v[q] = __fmaf_rn(k.x, g[q], __fmaf_rn(k.y, xh, k.z));
+    } else {
+      v[q] = pass ? pre : 0.0f;
+    }
+  }
+}
+
+// Stores the group's valid values.
+__device__ __forceinline__ void store_group(float* dst, int32_t base, int32_t total, const float v[4]) {
+  if (base + 4 <= total) {
+    *reinterpret_cast<float4*>(dst + base) = make_float4(v[0], v[1], v[2], v[3]);
+  } else {
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      if (base + q < total) dst[base + q] = v[q];
   }
 }
 
 // Max pass: part[workgroup] = max |v| bits over its groups (part == nullptr:
-// a single workgroup writes the scale directly and clears its flags).
-// Backward: also stores dy and dres when asked.
-template <bool BWD>
-__global__ __launch_bounds__(kBlock) void k_bn_amax(Elems e, float* __restrict__ dy, float* __restrict__ dres,
+// a single workgroup writes the scale directly and clears its flags).  Also
+// stores the values (forward z, backward dy) and the gradient at res where
+// asked.  Two groups' loads are in flight per thread.
+template <bool BWD, bool HW4, int SRC>
+__global__ __launch_bounds__(kBlock) void k_bn_amax(Elems e, float* __restrict__ out, float* __restrict__ dres,
                                                     uint32_t* __restrict__ part, dfp_scale* __restrict__ s) {
   const int32_t ey = e.sy->exp;
   const int32_t edz = BWD ? e.sdz->exp : 0;
   const int32_t groups = (e.total + 3) >> 2;
+  const int32_t stride = gridDim.x * kBlock;
   uint32_t m = 0u;
-  for (int32_t gi = blockIdx.x * kBlock + threadIdx.x; gi < groups; gi += gridDim.x * kBlock) {
-    const int32_t base = gi << 2;
-    const int32_t cnt = min(4, e.total - base);
+  auto use = [&](Group in, int32_t gi) {
     float v[4], g[4];
-    group_values<BWD>(e, base, cnt, ey, edz, v, g);
+    group_values<BWD, HW4, SRC>(e, in, gi, ey, edz, v, g);
 #pragma unroll
     for (int q = 0; q < 4; ++q) m = max(m, __float_as_uint(v[q]) & 0x7fffffffu);
-    if (BWD) {
-      if (cnt == 4) {
-        if (dy) *reinterpret_cast<float4*>(dy + base) = make_float4(v[0], v[1], v[2], v[3]);
-        if (dres) *reinterpret_cast<float4*>(dres + base) = make_float4(g[0], g[1], g[2], g[3]);
-      } else {
-        for (int q = 0; q < cnt; ++q) {
-          if (dy) dy[base + q] = v[q];
-          if (dres) dres[base + q] = g[q];
-        }
-      }
-    }
+    if (out) store_group(out, gi << 2, e.total, v);
+    if (BWD && dres) store_group(dres, gi << 2, e.total, g);
+  };
+  int32_t gi = blockIdx.x * kBlock + threadIdx.x;
+  for (; gi < groups - stride; gi += 2 * stride) {
+    const Group a = load_group<BWD, HW4, SRC>(e, gi), b = load_group<BWD, HW4, SRC>(e, gi + stride);
+    use(a, gi);
+    use(b, gi + stride);
   }
+  if (gi < groups) use(load_group<BWD, HW4, SRC>(e, gi), gi);
   __shared__ uint32_t red[kBlock / 64];
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
@@ -350,7 +428,7 @@ __global__ __launch_bounds__(kBlock) void k_bn_amax(Elems e, float* __restrict__
 // Rounding pass: recomputes each element's value, rounds it with the shared
 // exponent of the tensor max (Eq. 2-3, the descriptor's mode), writes the
 // INT16 result and, forward, the FP32 value when z != nullptr.
-template <bool BWD, int MODE, bool SAT>
+template <bool BWD, bool HW4, int SRC, int MODE, bool SAT>
 __global__ __launch_bounds__(kBlock) void k_bn_convert(Elems e, float* __restrict__ z, int16_t* __restrict__ dst,
                                                        dfp_scale* __restrict__ s, int32_t bits, uint32_t key0,
                                                        uint32_t key1, uint32_t role) {
@@ -362,12 +440,12 @@ __global__ __launch_bounds__(kBlock) void k_bn_convert(Elems e, float* __restric
   const int32_t ey = e.sy->exp;
   const int32_t edz = BWD ? e.sdz->exp : 0;
   const int32_t groups = (e.total + 3) >> 2;
+  const int32_t stride = gridDim.x * kBlock;
   bool saturated = false;
-  for (int32_t gi = blockIdx.x * kBlock + threadIdx.x; gi < groups; gi += gridDim.x * kBlock) {
+  auto use = [&](Group in, int32_t gi) {
     const int32_t base = gi << 2;
-    const int32_t cnt = min(4, e.total - base);
     float v[4], g[4];
-    group_values<BWD>(e, base, cnt, ey, edz, v, g);
+    group_values<BWD, HW4, SRC>(e, in, gi, ey, edz, v, g);
     uint32_t u[4] = {0u, 0u, 0u, 0u};
     if (MODE == DFP_ROUND_STOCHASTIC) {
       const uint4 r = philox4x32_10(make_uint4((uint32_t)gi, 0u, role, 0u), key0, key1);
@@ -385,19 +463,25 @@ __global__ __launch_bounds__(kBlock) void k_bn_convert(Elems e, float* __restric
       }
       iv[q] = t;
     }
-    if (cnt == 4) {
+    if (base + 4 <= e.total) {
       uint2 packed;
       packed.x = ((uint32_t)iv[0] & 0xffffu) | ((uint32_t)iv[1] << 16);
       packed.y = ((uint32_t)iv[2] & 0xffffu) | ((uint32_t)iv[3] << 16);
       *reinterpret_cast<uint2*>(dst + base) = packed;
-      if (!BWD && z) *reinterpret_cast<float4*>(z + base) = make_float4(v[0], v[1], v[2], v[3]);
     } else {
-      for (int q = 0; q < cnt; ++q) {
-        dst[base + q] = (int16_t)iv[q];
-        if (!BWD && z) z[base + q] = v[q];
-      }
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        if (base + q < e.total) dst[base + q] = (int16_t)iv[q];
     }
+    if (!BWD && z) store_group(z, base, e.total, v);
+  };
+  int32_t gi = blockIdx.x * kBlock + threadIdx.x;
+  for (; gi < groups - stride; gi += 2 * stride) {
+    const Group a = load_group<BWD, HW4, SRC>(e, gi), b = load_group<BWD, HW4, SRC>(e, gi + stride);
+    use(a, gi);
+    use(b, gi + stride);
   }
+  if (gi < groups) use(load_group<BWD, HW4, SRC>(e, gi), gi);
   if (SAT && saturated) atomicOr(&s->flags, DFP_FLAG_SATURATED);
 }
 
@@ -461,13 +545,22 @@ int32_t bn_splits(const dfp_bn_desc& d) {
   return std::max(1, std::min(want, d.n));
 }
 
+inline int64_t align256(int64_t v) { return (v + 255) & ~(int64_t)255; }
+
+// Workspace: the statistics' partial sums, the per-channel values and the
+// backward ReLU mask (a byte per group of four elements).
 struct BnWs {
   int64_t* part;
-  float4* kco;
+  float4 *kco, *chan;
+  uint8_t* mask;
+  int64_t bytes;
 };
 BnWs bn_ws(const dfp_bn_desc& d, void* ws) {
-  const int64_t part_bytes = ((int64_t)bn_splits(d) * d.c * 24 + 255) / 256 * 256;
-  return {reinterpret_cast<int64_t*>(ws), reinterpret_cast<float4*>(reinterpret_cast<uint8_t*>(ws) + part_bytes)};
+  const int64_t part = align256((int64_t)bn_splits(d) * d.c * 24), ch = align256((int64_t)d.c * 16);
+  const int64_t mask = d.hw % 4 == 0 ? align256((int64_t)d.n * d.c * d.hw / 4) : 0;
+  uint8_t* w = reinterpret_cast<uint8_t*>(ws);
+  return {reinterpret_cast<int64_t*>(w), reinterpret_cast<float4*>(w + part), reinterpret_cast<float4*>(w + part + ch),
+          mask ? w + part + 2 * ch : nullptr, part + 2 * ch + mask};
 }
 
 // Workgroups of a max pass over `groups` groups of four whose per-workgroup
@@ -479,37 +572,35 @@ int32_t max_parts(int64_t groups, int64_t n) {
   return (int32_t)std::max<int64_t>(parts, 1);
 }
 
-dfp_status launch_stats(bool bwd, const dfp_bn_desc& d, const int16_t* y, const int16_t* dz, const float* res,
+template <bool BWD, bool RES>
+dfp_status launch_stats(const dfp_bn_desc& d, const int16_t* y, const int16_t* dz, const float* res,
                         const float* mean, const float* inv, const float* gamma, const float* beta,
-                        const dfp_scale* sy, const dfp_scale* sdz, int64_t* part, dfp_scale* sz, hipStream_t st) {
+                        const dfp_scale* sy, const BnWs& w, dfp_scale* sz, hipStream_t st) {
   const int32_t S = bn_splits(d);
-  const bool vec = (d.hw % 8) == 0 && ((uintptr_t)y & 15) == 0 && (!bwd || ((uintptr_t)dz & 15) == 0);
-  const FastDiv upr = make_fastdiv((uint32_t)(vec ? d.hw / 8 : d.hw));
+  // elements per load (every tensor is 16-byte aligned); with a residual four,
+  // so that a wave's loads of it are contiguous
+  const int32_t V = !RES && d.hw % 8 == 0 ? 8 : d.hw % 4 == 0 ? 4 : 1;
+  const FastDiv upr = make_fastdiv((uint32_t)(d.hw / V));
   const dim3 grid((unsigned)S, (unsigned)d.c);
-  if (bwd) {
-    if (vec)
-      DFP_LAUNCH(K_BN_STATS, (k_bn_stats<true, true>), grid, dim3(kBlock), 0, st, y, dz, res, mean, inv, gamma, beta,
-                 sy, sdz, d.n, d.c, d.hw, S, upr, part, sz);
-    else
-      DFP_LAUNCH(K_BN_STATS, (k_bn_stats<true, false>), grid, dim3(kBlock), 0, st, y, dz, res, mean, inv, gamma,
-                 beta, sy, sdz, d.n, d.c, d.hw, S, upr, part, sz);
-  } else {
-    if (vec)
-      DFP_LAUNCH(K_BN_STATS, (k_bn_stats<false, true>), grid, dim3(kBlock), 0, st, y, dz, res, mean, inv, gamma,
-                 beta, sy, sdz, d.n, d.c, d.hw, S, upr, part, sz);
-    else
-      DFP_LAUNCH(K_BN_STATS, (k_bn_stats<false, false>), grid, dim3(kBlock), 0, st, y, dz, res, mean, inv, gamma,
-                 beta, sy, sdz, d.n, d.c, d.hw, S, upr, part, sz);
-  }
+  if (V == 8)
+    DFP_LAUNCH(K_BN_STATS, (k_bn_stats<BWD, RES ? 4 : 8, RES>), grid, dim3(kBlock), 0, st, y, dz, res, mean, inv, gamma, beta,
+               sy, d.n, d.c, d.hw, S, upr, w.part, w.mask, sz);
+  else if (V == 4)
+    DFP_LAUNCH(K_BN_STATS, (k_bn_stats<BWD, 4, RES>), grid, dim3(kBlock), 0, st, y, dz, res, mean, inv, gamma, beta,
+               sy, d.n, d.c, d.hw, S, upr, w.part, w.mask, sz);
+  else
+    DFP_LAUNCH(K_BN_STATS, (k_bn_stats<BWD, 1, RES>), grid, dim3(kBlock), 0, st, y, dz, res, mean, inv, gamma, beta,
+               sy, d.n, d.c, d.hw, S, upr, w.part, w.mask, sz);
   return DFP_OK;
 }
 
-Elems make_elems(const dfp_bn_desc& d, const int16_t* y, const int16_t* dz, const float* res, const float* mean,
-                 const float* inv, const float* gamma, const float* beta, const float4* kco, const dfp_scale* sy,
-                 const dfp_scale* sdz) {
+Elems make_elems(const dfp_bn_desc& d, const int16_t* y, const int16_t* dz, const float* res, const BnWs& w,
+                 const dfp_scale* sy, const dfp_scale* sdz) {
   Elems e{};
-  e.y = y; e.dz = dz; e.res = res; e.mean = mean; e.inv = inv; e.gamma = gamma; e.beta = beta; e.kco = kco;
+  e.y = y; e.dz = dz; e.chan = w.chan; e.kco = w.kco;
   e.sy = sy; e.sdz = sdz;
+  e.mask = dz && res ? w.mask : nullptr;
+  e.res = e.mask ? nullptr : res;
   e.total = d.n * d.c * d.hw;
   e.C = d.c;
   e.hw_div = make_fastdiv((uint32_t)d.hw);
@@ -518,16 +609,30 @@ Elems make_elems(const dfp_bn_desc& d, const int16_t* y, const int16_t* dz, cons
   return e;
 }
 
+// Calls f(HW4, SRC) with the element kernels' template arguments.
+template <bool BWD, typename F>
+dfp_status with_src(const Elems& e, F f) {
+  using std::false_type;
+  using std::true_type;
+  if (!e.hw4)
+    return e.res ? f(false_type{}, std::integral_constant<int, kRes>{}) : f(false_type{}, std::integral_constant<int, kPlain>{});
+  if constexpr (BWD)
+    return e.mask ? f(true_type{}, std::integral_constant<int, kMask>{}) : f(true_type{}, std::integral_constant<int, kPlain>{});
+  else
+    return e.res ? f(true_type{}, std::integral_constant<int, kRes>{}) : f(true_type{}, std::integral_constant<int, kPlain>{});
+}
+
 // Max pass (k_bn_amax + the max reduce) into s.
 template <bool BWD>
-dfp_status launch_max(const Elems& e, float* dy, float* dres, int16_t* scratch, dfp_scale* s, hipStream_t st) {
+dfp_status launch_max(const Elems& e, float* out, float* dres, int16_t* scratch, dfp_scale* s, hipStream_t st) {
   const int32_t parts = max_parts((e.total + 3) / 4, e.total);
-  if (parts <= 1) {
-    DFP_LAUNCH(K_BN_AMAX, k_bn_amax<BWD>, dim3(1), dim3(kBlock), 0, st, e, dy, dres, (uint32_t*)nullptr, s);
+  uint32_t* part = parts > 1 ? reinterpret_cast<uint32_t*>(scratch) : nullptr;
+  dfp_status rc = with_src<BWD>(e, [&](auto hw4, auto src) -> dfp_status {
+    DFP_LAUNCH(K_BN_AMAX, (k_bn_amax<BWD, decltype(hw4)::value, decltype(src)::value>), dim3((unsigned)parts),
+               dim3(kBlock), 0, st, e, out, dres, part, s);
     return DFP_OK;
-  }
-  uint32_t* part = reinterpret_cast<uint32_t*>(scratch);
-  DFP_LAUNCH(K_BN_AMAX, k_bn_amax<BWD>, dim3((unsigned)parts), dim3(kBlock), 0, st, e, dy, dres, part, s);
+  });
+  if (rc != DFP_OK || !part) return rc;
   return launch_amax_final(part, parts, s, st);
 }
 
@@ -537,13 +642,17 @@ dfp_status launch_convert_mode(const Elems& e, float* z, int16_t* dst, dfp_scale
   int64_t blocks = ((int64_t)(e.total + 3) / 4 + kBlock - 1) / kBlock;
   blocks = std::max<int64_t>(1, std::min<int64_t>(blocks, 8192));
   const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
-  if (bits == 16)
-    DFP_LAUNCH(K_BN_CONVERT, (k_bn_convert<BWD, MODE, true>), dim3((unsigned)blocks), dim3(kBlock), 0, st, e, z, dst,
-               s, bits, k0, k1, role);
-  else
-    DFP_LAUNCH(K_BN_CONVERT, (k_bn_convert<BWD, MODE, false>), dim3((unsigned)blocks), dim3(kBlock), 0, st, e, z,
-               dst, s, bits, k0, k1, role);
-  return DFP_OK;
+  return with_src<BWD>(e, [&](auto hw4, auto src) -> dfp_status {
+    constexpr bool H = decltype(hw4)::value;
+    constexpr int S = decltype(src)::value;
+    if (bits == 16)
+      DFP_LAUNCH(K_BN_CONVERT, (k_bn_convert<BWD, H, S, MODE, true>), dim3((unsigned)blocks), dim3(kBlock), 0, st, e,
+                 z, dst, s, bits, k0, k1, role);
+    else
+      DFP_LAUNCH(K_BN_CONVERT, (k_bn_convert<BWD, H, S, MODE, false>), dim3((unsigned)blocks), dim3(kBlock), 0, st, e,
+                 z, dst, s, bits, k0, k1, role);
+    return DFP_OK;
+  });
 }
 
 template <bool BWD>
@@ -560,26 +669,26 @@ dfp_status launch_convert(const Elems& e, float* z, int16_t* dst, dfp_scale* s, 
 
 }  // namespace
 
-size_t bn_workspace_bytes(const dfp_bn_desc& d) {
-  const int64_t part_bytes = ((int64_t)bn_splits(d) * d.c * 24 + 255) / 256 * 256;
-  const int64_t k_bytes = ((int64_t)d.c * 16 + 255) / 256 * 256;
-  return (size_t)(part_bytes + k_bytes);
-}
+size_t bn_workspace_bytes(const dfp_bn_desc& d) { return (size_t)bn_ws(d, nullptr).bytes; }
 
 dfp_status launch_bn_relu_fwd(const dfp_bn_desc& d, const int16_t* y, const dfp_scale* sy, const float* gamma,
                               const float* beta, const float* res, float* z, int16_t* zq, dfp_scale* sz, float* mean,
                               float* inv_std, int64_t* sums, void* ws, hipStream_t st) {
   const BnWs w = bn_ws(d, ws);
   dfp_status rc;
-  if ((rc = launch_stats(false, d, y, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, sy, nullptr, w.part,
-                         res ? nullptr : sz, st)) != DFP_OK)
+  if ((rc = launch_stats<false, false>(d, y, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, sy, w,
+                                       res ? nullptr : sz, st)) != DFP_OK)
     return rc;
   const int64_t cnt = (int64_t)d.n * d.hw;
   DFP_LAUNCH(K_BN_FINAL, k_bn_finalize<false>, dim3((unsigned)((d.c + 3) / 4)), dim3(kBlock), 0, st, w.part, bn_splits(d), d.c, cnt, sy,
              (const dfp_scale*)nullptr, d.eps, gamma, beta, mean, inv_std, sums, (float*)nullptr, (float*)nullptr,
-             (float4*)nullptr, sz, res == nullptr);
-  const Elems e = make_elems(d, y, nullptr, res, mean, inv_std, gamma, beta, nullptr, sy, nullptr);
-  if (res && (rc = launch_max<false>(e, nullptr, nullptr, zq, sz, st)) != DFP_OK) return rc;
+             (float4*)nullptr, w.chan, sz, res == nullptr);
+  const Elems e = make_elems(d, y, nullptr, res, w, sy, nullptr);
+  if (res) {
+    if ((rc = launch_max<false>(e, z, nullptr, zq, sz, st)) != DFP_OK) return rc;
+    // z written: 4 bytes of it per element to read against 6 of y and res
+    if (z) return launch_quant_convert(z, zq, e.total, sz, d.bits, d.rounding, d.seed, DFP_ROLE_X, st);
+  }
   return launch_convert<false>(e, z, zq, sz, d.bits, d.rounding, d.seed, DFP_ROLE_X, st);
 }
 
@@ -589,14 +698,16 @@ dfp_status launch_bn_relu_bwd(const dfp_bn_desc& d, const int16_t* dz, const dfp
                               float* dgamma, float* dbeta, float* dres, int64_t* sums, void* ws, hipStream_t st) {
   const BnWs w = bn_ws(d, ws);
   dfp_status rc;
-  if ((rc = launch_stats(true, d, y, dz, res, mean, inv_std, gamma, beta, sy, sdz, w.part, nullptr, st)) != DFP_OK)
-    return rc;
+  rc = res ? launch_stats<true, true>(d, y, dz, res, mean, inv_std, gamma, beta, sy, w, nullptr, st)
+           : launch_stats<true, false>(d, y, dz, res, mean, inv_std, gamma, beta, sy, w, nullptr, st);
+  if (rc != DFP_OK) return rc;
   const int64_t cnt = (int64_t)d.n * d.hw;
   DFP_LAUNCH(K_BN_FINAL, k_bn_finalize<true>, dim3((unsigned)((d.c + 3) / 4)), dim3(kBlock), 0, st, w.part, bn_splits(d), d.c, cnt, sy, sdz,
              d.eps, gamma, beta, const_cast<float*>(mean), const_cast<float*>(inv_std), sums, dgamma, dbeta, w.kco,
-             (dfp_scale*)nullptr, false);
-  const Elems e = make_elems(d, y, dz, res, mean, inv_std, gamma, beta, w.kco, sy, sdz);
+             w.chan, (dfp_scale*)nullptr, false);
+  const Elems e = make_elems(d, y, dz, res, w, sy, sdz);
   if ((rc = launch_max<true>(e, dy, dres, dyq, sdy, st)) != DFP_OK) return rc;
+  if (dy) return launch_quant_convert(dy, dyq, e.total, sdy, d.bits, d.rounding, d.seed, DFP_ROLE_DY, st);
   return launch_convert<true>(e, nullptr, dyq, sdy, d.bits, d.rounding, d.seed, DFP_ROLE_DY, st);
 }
 
