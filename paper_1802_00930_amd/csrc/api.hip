@@ -1,6 +1,7 @@
 // C ABI of libdfp: host-side validation and dispatch.  Every argument check
 // runs before the first HIP call, so an invalid call enqueues nothing.
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <vector>
 
@@ -17,7 +18,7 @@ struct ProfRec {
   hipEvent_t start, stop;
 };
 std::mutex g_prof_mu;
-bool g_prof_on = false;
+std::atomic<bool> g_prof_on{false};  // read without the mutex by every launch
 int32_t g_prof_cap = 0;
 std::vector<ProfRec> g_prof;
 std::vector<hipEvent_t> g_event_pool;
@@ -35,6 +36,7 @@ hipEvent_t pooled_event() {
 }  // namespace
 
 int prof_begin(int32_t id, hipStream_t st) {
+  if (!g_prof_on.load(std::memory_order_relaxed)) return -1;
   std::lock_guard<std::mutex> lk(g_prof_mu);
   if (!g_prof_on || (int32_t)g_prof.size() >= g_prof_cap) return -1;
   ProfRec rec{id, pooled_event(), pooled_event()};

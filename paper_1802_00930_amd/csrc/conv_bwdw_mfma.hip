@@ -19,6 +19,7 @@
 // that band.  A lane owning column (c, r, s) then gathers its 16 operand pairs
 // as band[c][offset(t) + r*Wpad + s], which covers padding, strides and image
 // boundaries with no branches.
+#include <numeric>
 #include <type_traits>
 
 #include "conv_bwdw_mfma.h"
@@ -2523,17 +2524,25 @@ BwdwPlan plan_bwdw_mfma(const Geom& g, bool ring) {
   p.Wpad = (g.w + 2 * g.pw + 7) / 8 * 8;
   const int64_t J = (p.T + g.L - 1) / g.L;
   p.nseg = (int32_t)((J + g.G - 1) / g.G);
-  // largest band (padded rows touched by kSBT consecutive indices of a segment)
+  // largest band (padded rows touched by kSBT consecutive indices of a
+  // segment).  Where segments are whole bands, band i starts at index 128 i and
+  // its rows repeat with the period of 128 i mod PQ.
   const int64_t PQ = (int64_t)g.p * g.q;
   int64_t rows_max = 0;
   const int64_t seg_len = (int64_t)g.G * g.L;
-  for (int64_t s = 0; s < p.nseg; ++s) {
-    const int64_t t0 = s * seg_len, t1 = std::min(t0 + seg_len, p.T);
-    for (int64_t sb = t0 / 32; sb < (t1 + 31) / 32; sb += kSBT / 32) {
-      const int64_t ta = std::max(sb * 32, t0), tb = std::min((sb + kSBT / 32) * 32, t1) - 1;
-      const int64_t za = (ta / PQ) * p.Hpad + ((ta % PQ) / g.q) * g.sh;
-      const int64_t zb = (tb / PQ) * p.Hpad + ((tb % PQ) / g.q) * g.sh + g.r - 1;
-      rows_max = std::max(rows_max, zb - za + 1);
+  auto band = [&](int64_t ta, int64_t tb) {  // indices ta .. tb
+    const int64_t za = (ta / PQ) * p.Hpad + ((ta % PQ) / g.q) * g.sh;
+    const int64_t zb = (tb / PQ) * p.Hpad + ((tb % PQ) / g.q) * g.sh + g.r - 1;
+    rows_max = std::max(rows_max, zb - za + 1);
+  };
+  if (seg_len % kSBT == 0 || p.nseg == 1) {
+    const int64_t nbands = (p.T + kSBT - 1) / kSBT, period = PQ / std::gcd(PQ, (int64_t)kSBT);
+    for (int64_t i = 0; i < std::min(nbands, period); ++i) band(i * kSBT, std::min((i + 1) * kSBT, p.T) - 1);
+  } else {
+    for (int64_t s = 0; s < p.nseg; ++s) {
+      const int64_t t0 = s * seg_len, t1 = std::min(t0 + seg_len, p.T);
+      for (int64_t sb = t0 / 32; sb < (t1 + 31) / 32; sb += kSBT / 32)
+        band(std::max(sb * 32, t0), std::min((sb + kSBT / 32) * 32, t1) - 1);
     }
   }
   const int64_t RS = (int64_t)g.r * g.s;

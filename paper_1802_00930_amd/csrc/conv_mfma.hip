@@ -33,6 +33,7 @@
 // multiple of 32 run the block once per chunk it overlaps, with the bytes of
 // the other chunks masked to zero.
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 #include "dfp_internal.h"
@@ -2620,9 +2621,14 @@ static bool use_s16(int64_t NP, int32_t M, int32_t Mp, int32_t KB, bool partials
   return true;
 }
 
+// CUs of the current device (looked up once per device).
 static int device_cus() {
+  static std::atomic<int> known[64];
   int dev = 0, cus = 256;
-  if (hipGetDevice(&dev) == hipSuccess) hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return cus;
+  if (const int k = known[dev].load(std::memory_order_relaxed)) return k;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
+    known[dev].store(cus, std::memory_order_relaxed);
   return cus;
 }
 
@@ -2841,8 +2847,7 @@ dfp_status launch_mfma_main(ConvMfmaArgs& args, int64_t ws_b_bytes, int kid, int
   const bool partials = args.partials != nullptr;
   // persistent grid: one workgroup per CU for each 64-row tile of the output channels
   auto persist_grid = [&]() {
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    const int cus = device_cus();
     const int64_t wave_tiles = (args.NP + 31) / 32;
     const int64_t mtiles = args.Mp / kMT;
     int64_t gx = std::max<int64_t>(1, cus / mtiles);
@@ -2865,8 +2870,7 @@ dfp_status launch_mfma_main(ConvMfmaArgs& args, int64_t ws_b_bytes, int kid, int
   args.div_pq = make_fastdiv((uint32_t)(args.Po * args.Qo));
   args.div_q = make_fastdiv((uint32_t)args.Qo);
   auto w16_grid = [&]() {
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    const int cus = device_cus();
     const int64_t units = 2 * ((args.NP + 31) / 32);
     const int64_t mtiles = args.Mp / kMT;
     int64_t gx = std::max<int64_t>(1, cus / mtiles);

@@ -116,19 +116,18 @@ def make_desc(n, c, h, w, k, r, s, stride=1, pad=0, chunk_len=64, seg_chunks=0, 
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
+    """Handle of `stream`, by default torch's current stream on the current device."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _need(t, dtype, what):
-    if t is None:
-        return
-    if not t.is_cuda or t.dtype != dtype or not t.is_contiguous():
+    if t is not None and not (t.is_cuda and t.dtype is dtype and t.is_contiguous()):
         raise TypeError("%s must be a contiguous %s CUDA tensor" % (what, dtype))
 
 
