@@ -64,6 +64,12 @@ __device__ __forceinline__ float relu(float v) { return v > 0.0f ? v : 0.0f; }
 __device__ __forceinline__ int32_t lo16(uint32_t w) { return (int32_t)(int16_t)(w & 0xffffu); }
 __device__ __forceinline__ int32_t hi16(uint32_t w) { return (int32_t)w >> 16; }
 
+// The backward ReLU mask is a byte per group of four elements (bit q: element q
+// passes) in the INT16 output buffer, at the start of the 512 bytes that the
+// 64 groups' own results fill: the wave that rounds these groups has read the
+// 64 bytes before it stores.
+__device__ __forceinline__ int64_t mask_at(int32_t group) { return (int64_t)(group >> 6) * 512 + (group & 63); }
+
 // ------------------------------------------------------------ statistics
 // Workgroup (s, c) reduces channel c over images [N s / S, N (s+1) / S).
 // Forward: S1 = sum i, S2 = sum i^2, min i, max i.  Backward: D = sum g_i,
@@ -150,7 +156,7 @@ __global__ __launch_bounds__(kBlock) void k_bn_stats(const int16_t* __restrict__
         mx = max(mx, yv);
       }
     }
-    if (BWD && RES && V == 4) mask[u.off >> 2] = (uint8_t)bits;
+    if (BWD && RES && V == 4) mask[mask_at(u.off >> 2)] = (uint8_t)bits;
   };
   int32_t j = threadIdx.x;
   if (j < units) {
@@ -192,7 +198,8 @@ __global__ __launch_bounds__(kBlock) void k_bn_stats(const int16_t* __restrict__
 // Forward: mean / inv_std from the exact sums (float64, rounded once), and
 // without a residual the output max from the channel's extreme integers,
 // max-reduced into the output scale (cleared by the statistics kernel).
-// Backward: dbeta, dgamma and the per-element coefficients k1..k3.
+// Per channel for the element passes: forward (mean, inv_std, gamma, beta),
+// backward (k1, k2, k3, mean), with dbeta and dgamma.
 template <bool BWD>
 __global__ __launch_bounds__(kBlock) void k_bn_finalize(const int64_t* __restrict__ part, int32_t S, int32_t C,
                                                         int64_t cnt, const dfp_scale* __restrict__ sy,
@@ -201,7 +208,7 @@ __global__ __launch_bounds__(kBlock) void k_bn_finalize(const int64_t* __restric
                                                         const float* __restrict__ beta, float* __restrict__ mean,
                                                         float* __restrict__ inv, int64_t* __restrict__ sums,
                                                         float* __restrict__ dgamma, float* __restrict__ dbeta,
-                                                        float4* __restrict__ kco, float4* __restrict__ chan,
+                                                        float4* __restrict__ kco,
                                                         dfp_scale* __restrict__ sz, bool write_max) {
   const int lane = threadIdx.x & 63;
   const int32_t c = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
@@ -240,7 +247,7 @@ __global__ __launch_bounds__(kBlock) void k_bn_finalize(const int64_t* __restric
     const float iv = __fdiv_rn(1.0f, sq);
     mean[c] = mf;
     inv[c] = iv;
-    chan[c] = make_float4(mf, iv, gamma[c], beta[c]);
+    kco[c] = make_float4(mf, iv, gamma[c], beta[c]);
     if (write_max) {
       const Chan p{mf, iv, gamma[c], beta[c]};
       const float zlo = relu(bn_affine(bn_xhat(mn, ey, p), p));
@@ -257,9 +264,8 @@ __global__ __launch_bounds__(kBlock) void k_bn_finalize(const int64_t* __restric
     dbeta[c] = dbf;
     dgamma[c] = dgf;
     const double al = __dmul_rn((double)gamma[c], iv);  // exact: two FP32 factors
-    chan[c] = make_float4(mean[c], inv[c], gamma[c], beta[c]);
     kco[c] = make_float4((float)al, (float)__ddiv_rn(__dmul_rn(-al, (double)dgf), dcnt),
-                         (float)__ddiv_rn(__dmul_rn(-al, (double)dbf), dcnt), 0.0f);
+                         (float)__ddiv_rn(__dmul_rn(-al, (double)dbf), dcnt), mean[c]);
   }
 }
 
@@ -270,9 +276,9 @@ struct Elems {
   const int16_t* y;
   const int16_t* dz;
   const float* res;     // null where the mask replaces it
-  const uint8_t* mask;  // backward with res and hw % 4 == 0: bit q of byte g, element 4 g + q passes the ReLU
-  const float4* chan;   // mean, inv_std, gamma, beta
-  const float4* kco;
+  const uint8_t* mask;  // backward with res and hw % 4 == 0 (mask_at)
+  const float4* kco;    // forward mean, inv_std, gamma, beta; backward k1, k2, k3, mean
+  const float *inv, *gamma, *beta;  // backward
   const dfp_scale* sy;
   const dfp_scale* sdz;
   int32_t total, C;
@@ -294,7 +300,8 @@ struct Group {
   uint2 y, d;
   float4 r;
   uint32_t mask;
-  float4 p, k;  // channel values (HW4)
+  float4 k;     // channel values (HW4): kco, and backward inv_std, gamma, beta
+  float inv, gamma, beta;
 };
 __device__ __forceinline__ int32_t group_int(const uint2& w, int q) {
   const uint32_t v = q < 2 ? w.x : w.y;
@@ -304,13 +311,25 @@ __device__ __forceinline__ uint2 short_group(const int16_t* src, int32_t left) {
   const uint32_t a = (uint16_t)src[0], b = left > 1 ? (uint16_t)src[1] : 0u, c = left > 2 ? (uint16_t)src[2] : 0u;
   return make_uint2(a | (b << 16), c);
 }
+template <bool BWD, int SRC>
+__device__ __forceinline__ void load_channel(const Elems& e, int32_t c, Group& g) {
+  g.k = e.kco[c];
+  if (BWD) {
+    g.inv = e.inv[c];
+    if (SRC != kMask) {
+      g.gamma = e.gamma[c];
+      g.beta = e.beta[c];
+    }
+  }
+}
 template <bool BWD, bool HW4, int SRC>
 __device__ __forceinline__ Group load_group(const Elems& e, int32_t gi) {
   Group g;
   const int32_t base = gi << 2;
   const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
   g.d = make_uint2(0u, 0u);
-  g.r = g.p = g.k = z4;
+  g.r = g.k = z4;
+  g.inv = g.gamma = g.beta = 0.f;
   if (base + 4 <= e.total) {
     g.y = *reinterpret_cast<const uint2*>(e.y + base);
     if (BWD) g.d = *reinterpret_cast<const uint2*>(e.dz + base);
@@ -321,12 +340,8 @@ __device__ __forceinline__ Group load_group(const Elems& e, int32_t gi) {
     if (BWD) g.d = short_group(e.dz + base, left);
     if (SRC == kRes) g.r = make_float4(e.res[base], left > 1 ? e.res[base + 1] : 0.f, left > 2 ? e.res[base + 2] : 0.f, 0.f);
   }
-  g.mask = SRC == kMask ? e.mask[gi] : 0u;
-  if (HW4) {
-    const int32_t c = chan_of(e, base);
-    g.p = e.chan[c];
-    if (BWD) g.k = e.kco[c];
-  }
+  g.mask = SRC == kMask ? e.mask[mask_at(gi)] : 0u;
+  if (HW4) load_channel<BWD, SRC>(e, chan_of(e, base), g);
   return g;
 }
 
@@ -342,13 +357,9 @@ __device__ __forceinline__ void group_values(const Elems& e, Group in, int32_t g
     v[q] = 0.0f;
     g[q] = 0.0f;
     if (base + q >= e.total) continue;
-    float4 pc = in.p, k = in.k;
-    if (!HW4) {
-      const int32_t c = chan_of(e, base + q);
-      pc = e.chan[c];
-      if (BWD) k = e.kco[c];
-    }
-    const Chan p{pc.x, pc.y, pc.z, pc.w};
+    if (!HW4) load_channel<BWD, SRC>(e, chan_of(e, base + q), in);
+    const float4 k = in.k;
+    const Chan p = BWD ? Chan{k.w, in.inv, in.gamma, in.beta} : Chan{k.x, k.y, k.z, k.w};
     const int32_t yi = group_int(in.y, q);
     const float xh = bn_xhat(yi, ey, p);
     bool pass = false;
@@ -429,7 +440,7 @@ __global__ __launch_bounds__(kBlock) void k_bn_amax(Elems e, float* __restrict__
 // exponent of the tensor max (Eq. 2-3, the descriptor's mode), writes the
 // INT16 result and, forward, the FP32 value when z != nullptr.
 template <bool BWD, bool HW4, int SRC, int MODE, bool SAT>
-__global__ __launch_bounds__(kBlock) void k_bn_convert(Elems e, float* __restrict__ z, int16_t* __restrict__ dst,
+__global__ __launch_bounds__(kBlock) void k_bn_convert(Elems e, float* __restrict__ z, int16_t* dst,
                                                        dfp_scale* __restrict__ s, int32_t bits, uint32_t key0,
                                                        uint32_t key1, uint32_t role) {
   const ScaleFromMax sc = scale_from_max(s->amax_bits, bits);
@@ -545,37 +556,32 @@ int32_t bn_splits(const dfp_bn_desc& d) {
   return std::max(1, std::min(want, d.n));
 }
 
-inline int64_t align256(int64_t v) { return (v + 255) & ~(int64_t)255; }
-
-// Workspace: the statistics' partial sums, the per-channel values and the
-// backward ReLU mask (a byte per group of four elements).
+// Workspace: the statistics' partial sums (after the finalize kernel, the max
+// pass's partial maxima) and the per-channel values.
 struct BnWs {
   int64_t* part;
-  float4 *kco, *chan;
-  uint8_t* mask;
-  int64_t bytes;
+  float4* kco;
+  int64_t part_bytes;
 };
 BnWs bn_ws(const dfp_bn_desc& d, void* ws) {
-  const int64_t part = align256((int64_t)bn_splits(d) * d.c * 24), ch = align256((int64_t)d.c * 16);
-  const int64_t mask = d.hw % 4 == 0 ? align256((int64_t)d.n * d.c * d.hw / 4) : 0;
+  const int64_t part = ((int64_t)bn_splits(d) * d.c * 24 + 255) / 256 * 256;
   uint8_t* w = reinterpret_cast<uint8_t*>(ws);
-  return {reinterpret_cast<int64_t*>(w), reinterpret_cast<float4*>(w + part), reinterpret_cast<float4*>(w + part + ch),
-          mask ? w + part + 2 * ch : nullptr, part + 2 * ch + mask};
+  return {reinterpret_cast<int64_t*>(w), reinterpret_cast<float4*>(w + part), part};
 }
 
 // Workgroups of a max pass over `groups` groups of four whose per-workgroup
-// maxima are kept in an INT16 buffer of `n` elements (4 bytes each); <= 1
-// means one workgroup writing the scale directly.
-int32_t max_parts(int64_t groups, int64_t n) {
+// maxima have room for `room`; <= 1 means one workgroup writing the scale
+// directly.
+int32_t max_parts(int64_t groups, int64_t room) {
   int64_t parts = (groups + kBlock - 1) / kBlock;
-  parts = std::min<int64_t>(std::min<int64_t>(parts, kMaxParts), n / 2);
+  parts = std::min<int64_t>(std::min<int64_t>(parts, kMaxParts), room);
   return (int32_t)std::max<int64_t>(parts, 1);
 }
 
 template <bool BWD, bool RES>
 dfp_status launch_stats(const dfp_bn_desc& d, const int16_t* y, const int16_t* dz, const float* res,
                         const float* mean, const float* inv, const float* gamma, const float* beta,
-                        const dfp_scale* sy, const BnWs& w, dfp_scale* sz, hipStream_t st) {
+                        const dfp_scale* sy, const BnWs& w, uint8_t* mask, dfp_scale* sz, hipStream_t st) {
   const int32_t S = bn_splits(d);
   // elements per load (every tensor is 16-byte aligned); with a residual four,
   // so that a wave's loads of it are contiguous
@@ -584,23 +590,20 @@ dfp_status launch_stats(const dfp_bn_desc& d, const int16_t* y, const int16_t* d
   const dim3 grid((unsigned)S, (unsigned)d.c);
   if (V == 8)
     DFP_LAUNCH(K_BN_STATS, (k_bn_stats<BWD, RES ? 4 : 8, RES>), grid, dim3(kBlock), 0, st, y, dz, res, mean, inv, gamma, beta,
-               sy, d.n, d.c, d.hw, S, upr, w.part, w.mask, sz);
+               sy, d.n, d.c, d.hw, S, upr, w.part, mask, sz);
   else if (V == 4)
     DFP_LAUNCH(K_BN_STATS, (k_bn_stats<BWD, 4, RES>), grid, dim3(kBlock), 0, st, y, dz, res, mean, inv, gamma, beta,
-               sy, d.n, d.c, d.hw, S, upr, w.part, w.mask, sz);
+               sy, d.n, d.c, d.hw, S, upr, w.part, mask, sz);
   else
     DFP_LAUNCH(K_BN_STATS, (k_bn_stats<BWD, 1, RES>), grid, dim3(kBlock), 0, st, y, dz, res, mean, inv, gamma, beta,
-               sy, d.n, d.c, d.hw, S, upr, w.part, w.mask, sz);
+               sy, d.n, d.c, d.hw, S, upr, w.part, mask, sz);
   return DFP_OK;
 }
 
-Elems make_elems(const dfp_bn_desc& d, const int16_t* y, const int16_t* dz, const float* res, const BnWs& w,
-                 const dfp_scale* sy, const dfp_scale* sdz) {
+Elems make_elems(const dfp_bn_desc& d, const int16_t* y, const float* res, const BnWs& w, const dfp_scale* sy) {
   Elems e{};
-  e.y = y; e.dz = dz; e.chan = w.chan; e.kco = w.kco;
-  e.sy = sy; e.sdz = sdz;
-  e.mask = dz && res ? w.mask : nullptr;
-  e.res = e.mask ? nullptr : res;
+  e.y = y; e.res = res; e.kco = w.kco;
+  e.sy = sy;
   e.total = d.n * d.c * d.hw;
   e.C = d.c;
   e.hw_div = make_fastdiv((uint32_t)d.hw);
@@ -624,9 +627,9 @@ dfp_status with_src(const Elems& e, F f) {
 
 // Max pass (k_bn_amax + the max reduce) into s.
 template <bool BWD>
-dfp_status launch_max(const Elems& e, float* out, float* dres, int16_t* scratch, dfp_scale* s, hipStream_t st) {
-  const int32_t parts = max_parts((e.total + 3) / 4, e.total);
-  uint32_t* part = parts > 1 ? reinterpret_cast<uint32_t*>(scratch) : nullptr;
+dfp_status launch_max(const Elems& e, float* out, float* dres, const BnWs& w, dfp_scale* s, hipStream_t st) {
+  const int32_t parts = max_parts((e.total + 3) / 4, w.part_bytes / 4);
+  uint32_t* part = parts > 1 ? reinterpret_cast<uint32_t*>(w.part) : nullptr;
   dfp_status rc = with_src<BWD>(e, [&](auto hw4, auto src) -> dfp_status {
     DFP_LAUNCH(K_BN_AMAX, (k_bn_amax<BWD, decltype(hw4)::value, decltype(src)::value>), dim3((unsigned)parts),
                dim3(kBlock), 0, st, e, out, dres, part, s);
@@ -669,23 +672,25 @@ dfp_status launch_convert(const Elems& e, float* z, int16_t* dst, dfp_scale* s, 
 
 }  // namespace
 
-size_t bn_workspace_bytes(const dfp_bn_desc& d) { return (size_t)bn_ws(d, nullptr).bytes; }
+size_t bn_workspace_bytes(const dfp_bn_desc& d) {
+  return (size_t)(bn_ws(d, nullptr).part_bytes + ((int64_t)d.c * 16 + 255) / 256 * 256);
+}
 
 dfp_status launch_bn_relu_fwd(const dfp_bn_desc& d, const int16_t* y, const dfp_scale* sy, const float* gamma,
                               const float* beta, const float* res, float* z, int16_t* zq, dfp_scale* sz, float* mean,
                               float* inv_std, int64_t* sums, void* ws, hipStream_t st) {
   const BnWs w = bn_ws(d, ws);
   dfp_status rc;
-  if ((rc = launch_stats<false, false>(d, y, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, sy, w,
+  if ((rc = launch_stats<false, false>(d, y, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, sy, w, nullptr,
                                        res ? nullptr : sz, st)) != DFP_OK)
     return rc;
   const int64_t cnt = (int64_t)d.n * d.hw;
   DFP_LAUNCH(K_BN_FINAL, k_bn_finalize<false>, dim3((unsigned)((d.c + 3) / 4)), dim3(kBlock), 0, st, w.part, bn_splits(d), d.c, cnt, sy,
              (const dfp_scale*)nullptr, d.eps, gamma, beta, mean, inv_std, sums, (float*)nullptr, (float*)nullptr,
-             (float4*)nullptr, w.chan, sz, res == nullptr);
-  const Elems e = make_elems(d, y, nullptr, res, w, sy, nullptr);
+             w.kco, sz, res == nullptr);
+  const Elems e = make_elems(d, y, res, w, sy);
   if (res) {
-    if ((rc = launch_max<false>(e, z, nullptr, zq, sz, st)) != DFP_OK) return rc;
+    if ((rc = launch_max<false>(e, z, nullptr, w, sz, st)) != DFP_OK) return rc;
     // z written: 4 bytes of it per element to read against 6 of y and res
     if (z) return launch_quant_convert(z, zq, e.total, sz, d.bits, d.rounding, d.seed, DFP_ROLE_X, st);
   }
@@ -698,15 +703,19 @@ dfp_status launch_bn_relu_bwd(const dfp_bn_desc& d, const int16_t* dz, const dfp
                               float* dgamma, float* dbeta, float* dres, int64_t* sums, void* ws, hipStream_t st) {
   const BnWs w = bn_ws(d, ws);
   dfp_status rc;
-  rc = res ? launch_stats<true, true>(d, y, dz, res, mean, inv_std, gamma, beta, sy, w, nullptr, st)
-           : launch_stats<true, false>(d, y, dz, res, mean, inv_std, gamma, beta, sy, w, nullptr, st);
+  // with a residual the statistics pass leaves the ReLU mask in dyq
+  uint8_t* mask = res && d.hw % 4 == 0 ? reinterpret_cast<uint8_t*>(dyq) : nullptr;
+  rc = res ? launch_stats<true, true>(d, y, dz, res, mean, inv_std, gamma, beta, sy, w, mask, nullptr, st)
+           : launch_stats<true, false>(d, y, dz, res, mean, inv_std, gamma, beta, sy, w, mask, nullptr, st);
   if (rc != DFP_OK) return rc;
   const int64_t cnt = (int64_t)d.n * d.hw;
   DFP_LAUNCH(K_BN_FINAL, k_bn_finalize<true>, dim3((unsigned)((d.c + 3) / 4)), dim3(kBlock), 0, st, w.part, bn_splits(d), d.c, cnt, sy, sdz,
              d.eps, gamma, beta, const_cast<float*>(mean), const_cast<float*>(inv_std), sums, dgamma, dbeta, w.kco,
-             w.chan, (dfp_scale*)nullptr, false);
-  const Elems e = make_elems(d, y, dz, res, w, sy, sdz);
-  if ((rc = launch_max<true>(e, dy, dres, dyq, sdy, st)) != DFP_OK) return rc;
+             (dfp_scale*)nullptr, false);
+  Elems e = make_elems(d, y, mask ? nullptr : res, w, sy);
+  e.dz = dz; e.sdz = sdz; e.mask = mask;
+  e.inv = inv_std; e.gamma = gamma; e.beta = beta;
+  if ((rc = launch_max<true>(e, dy, dres, w, sdy, st)) != DFP_OK) return rc;
   if (dy) return launch_quant_convert(dy, dyq, e.total, sdy, d.bits, d.rounding, d.seed, DFP_ROLE_DY, st);
   return launch_convert<true>(e, nullptr, dyq, sdy, d.bits, d.rounding, d.seed, DFP_ROLE_DY, st);
 }
@@ -714,7 +723,7 @@ dfp_status launch_bn_relu_bwd(const dfp_bn_desc& d, const int16_t* dz, const dfp
 dfp_status launch_sgd_quantize(int64_t n, float lr, float mu, float wd, int32_t bits, int32_t rounding,
                                uint64_t seed, float* w, float* v, const float* dw, int16_t* wq, dfp_scale* sw,
                                hipStream_t st) {
-  const int32_t parts = max_parts((n + 3) / 4, n);
+  const int32_t parts = max_parts((n + 3) / 4, n / 2);  // in wq
   if (parts <= 1) {
     DFP_LAUNCH(K_SGD, k_sgd, dim3(1), dim3(kBlock), 0, st, n, lr, mu, wd, w, v, dw, (uint32_t*)nullptr, sw);
   } else {
