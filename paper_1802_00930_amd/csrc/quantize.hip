@@ -392,10 +392,17 @@ __global__ __launch_bounds__(kBlock) void k_i32_convert(const int32_t* __restric
 // Each block of B consecutive elements of a [rows][cols] row gets its own
 // shared exponent (Eq. 1-2 on the block's max) and is rounded like a tensor of
 // its own (Eq. 3), the stochastic word still that of the element's flat index.
-// One wave per (row, block): a max pass, then the rounding pass.  VEC4: rows
-// and blocks start at multiples of 4 elements, so a lane takes aligned groups
-// of 4 (one Philox block, one 16-byte load).  s->flags starts at ZERO_TENSOR
-// (k_blocked_init); a wave with a non-zero or non-finite block clears it.
+// A segment of lanes per (row, block): a max pass, then the rounding pass.
+// VEC4: rows and blocks start at multiples of 4 elements, so a lane takes
+// aligned groups of 4 (one Philox block, one 16-byte load) and keeps its first
+// group for the rounding pass.  The pass is bound by how it ends: every
+// workgroup reports to the one scale at about the same time, and atomics on one
+// address queue: 1000 x 2048 in blocks of 128 took 16-18 us with 1024 workgroups of
+// 4 waves and two atomics each, 9 us with one workgroup of 16 waves per CU and one.
+// s->flags starts at ZERO_TENSOR (k_blocked_init); the workgroup whose max is
+// the first above zero clears it.
+constexpr int kBlockedThreads = 1024;
+
 __global__ void k_blocked_init(dfp_scale* s) {
   if (threadIdx.x == 0) {
     s->amax_bits = 0u;
@@ -405,31 +412,38 @@ __global__ void k_blocked_init(dfp_scale* s) {
 }
 
 template <int MODE, bool SAT, bool VEC4>
-__global__ __launch_bounds__(kBlock) void k_quant_blocked(const float* __restrict__ src, int16_t* __restrict__ dst,
-                                                          int8_t* __restrict__ exps, int64_t rows, int64_t cols,
-                                                          int64_t B, int64_t nb, dfp_scale* s, int32_t bits,
-                                                          uint32_t key0, uint32_t key1, uint32_t role,
-                                                          int32_t seg_log2) {
+__global__ __launch_bounds__(kBlockedThreads) void k_quant_blocked(
+    const float* __restrict__ src, int16_t* __restrict__ dst, int8_t* __restrict__ exps, int64_t rows, int64_t cols,
+    int64_t B, int64_t nb, dfp_scale* s, int32_t bits, uint32_t key0, uint32_t key1, uint32_t role, int32_t seg_log2,
+    FastDiv nb_div) {
   // a wave serves 64 >> seg_log2 blocks at a time, 2^seg_log2 lanes each, in a
   // grid-stride loop; the workgroup reports its max and flags once at the end
   const int lane = threadIdx.x & 63;
   const int S = 1 << seg_log2;
   const int sl = lane & (S - 1);
   const int64_t nblk = rows * nb;
-  const int64_t stride = ((int64_t)gridDim.x * (kBlock / 64)) << (6 - seg_log2);
+  const int64_t stride = ((int64_t)gridDim.x * (kBlockedThreads / 64)) << (6 - seg_log2);
   uint32_t wmax = 0u;
-  bool f_nonfinite = false, f_clamped = false, f_sat = false, f_nonzero = false;
-  for (int64_t wave_first = ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) << (6 - seg_log2);
+  bool f_nonfinite = false, f_clamped = false, f_sat = false;
+  for (int64_t wave_first = ((int64_t)blockIdx.x * (kBlockedThreads / 64) + (threadIdx.x >> 6)) << (6 - seg_log2);
        wave_first < nblk; wave_first += stride) {  // uniform per wave
     const int64_t blk = wave_first + (lane >> seg_log2);
     const bool valid = blk < nblk;
-    const int64_t r = valid ? blk / nb : 0, b = valid ? blk % nb : 0;
+    // (nb_div.l > 32: more than 2^32 blocks, by division)
+    const int64_t r = !valid ? 0 : nb_div.l <= 32 ? (int64_t)fdiv((uint32_t)blk, nb_div) : blk / nb;
+    const int64_t b = valid ? blk - r * nb : 0;
     const int64_t c0 = b * B, c1 = valid ? min(c0 + B, cols) : c0;
     const int64_t base = r * cols;
     const uint32_t* s32 = reinterpret_cast<const uint32_t*>(src) + base;
     uint32_t mb = 0u;
+    uint4 first = make_uint4(0u, 0u, 0u, 0u);  // this lane's first group
     if (VEC4) {
-      for (int64_t c = c0 + 4 * sl; c < c1; c += 4 * S) {
+      int64_t c = c0 + 4 * sl;
+      if (c < c1) {
+        first = *reinterpret_cast<const uint4*>(s32 + c);
+        mb = abs_max4(first);
+      }
+      for (c += 4 * S; c < c1; c += 4 * S) {
         const uint4 v = *reinterpret_cast<const uint4*>(s32 + c);
         mb = max(mb, max(max(v.x & 0x7fffffffu, v.y & 0x7fffffffu), max(v.z & 0x7fffffffu, v.w & 0x7fffffffu)));
       }
@@ -461,7 +475,7 @@ __global__ __launch_bounds__(kBlock) void k_quant_blocked(const float* __restric
     };
     if (VEC4) {
       for (int64_t c = c0 + 4 * sl; c < c1; c += 4 * S) {
-        const uint4 v = *reinterpret_cast<const uint4*>(s32 + c);
+        const uint4 v = c == c0 + 4 * sl ? first : *reinterpret_cast<const uint4*>(s32 + c);
         const uint64_t g = (uint64_t)(base + c) >> 2;
         uint4 rw = make_uint4(0u, 0u, 0u, 0u);
         if (MODE == DFP_ROUND_STOCHASTIC)
@@ -491,13 +505,12 @@ __global__ __launch_bounds__(kBlock) void k_quant_blocked(const float* __restric
     f_nonfinite |= valid && nonfinite;
     f_clamped |= valid && clamped;
     f_sat |= saturated;
-    f_nonzero |= valid && !zero;
   }
   // workgroup totals, then one guarded set of atomics
-  __shared__ uint32_t red_max[kBlock / 64], red_flags[kBlock / 64];
+  __shared__ uint32_t red_max[kBlockedThreads / 64], red_flags[kBlockedThreads / 64];
   for (int off = 32; off > 0; off >>= 1) wmax = max(wmax, (uint32_t)__shfl_xor((int)wmax, off, 64));
   const uint32_t wf = (__any(f_nonfinite) ? DFP_FLAG_NONFINITE : 0u) | (__any(f_clamped) ? DFP_FLAG_EXP_CLAMPED : 0u) |
-                      (__any(f_sat) ? DFP_FLAG_SATURATED : 0u) | (__any(f_nonzero) ? 0x80000000u : 0u);
+                      (__any(f_sat) ? DFP_FLAG_SATURATED : 0u);
   if (lane == 0) {
     red_max[threadIdx.x >> 6] = wmax;
     red_flags[threadIdx.x >> 6] = wf;
@@ -505,15 +518,13 @@ __global__ __launch_bounds__(kBlock) void k_quant_blocked(const float* __restric
   __syncthreads();
   if (threadIdx.x == 0) {
     uint32_t m = red_max[0], f = red_flags[0];
-    for (int i = 1; i < kBlock / 64; ++i) {
+    for (int i = 1; i < kBlockedThreads / 64; ++i) {
       m = max(m, red_max[i]);
       f |= red_flags[i];
     }
-    if (m > __atomic_load_n(&s->amax_bits, __ATOMIC_RELAXED)) atomicMax(&s->amax_bits, m);
-    const uint32_t fl = f & 0x7fffffffu;
-    if (fl && (__atomic_load_n(&s->flags, __ATOMIC_RELAXED) & fl) != fl) atomicOr(&s->flags, fl);
-    if ((f & 0x80000000u) && (__atomic_load_n(&s->flags, __ATOMIC_RELAXED) & DFP_FLAG_ZERO_TENSOR))
+    if (m > __atomic_load_n(&s->amax_bits, __ATOMIC_RELAXED) && atomicMax(&s->amax_bits, m) == 0u)
       atomicAnd(&s->flags, ~DFP_FLAG_ZERO_TENSOR);
+    if (f && (__atomic_load_n(&s->flags, __ATOMIC_RELAXED) & f) != f) atomicOr(&s->flags, f);
   }
 }
 
@@ -536,14 +547,15 @@ static dfp_status launch_blocked_mode(const float* src, int16_t* dst, int8_t* ex
   int32_t seg_log2 = 0;
   while (seg_log2 < 6 && ((int64_t)1 << seg_log2) < lanes) ++seg_log2;
   const int64_t waves = (rows * nb + (64 >> seg_log2) - 1) >> (6 - seg_log2);
-  // at most 1024 workgroups (4 per CU): each reports once, so the scale sees few atomics
-  const dim3 grid((unsigned)std::min<int64_t>(1024, (waves + kBlock / 64 - 1) / (kBlock / 64)));
+  // one workgroup of 16 waves per CU: each reports once, so the scale sees few atomics
+  const dim3 grid((unsigned)std::min<int64_t>(256, (waves + kBlockedThreads / 64 - 1) / (kBlockedThreads / 64)));
+  const FastDiv nb_div = rows * nb < ((int64_t)1 << 32) ? make_fastdiv((uint32_t)nb) : FastDiv{0u, 64u};
   if (vec4)
-    DFP_LAUNCH(K_QUANT_BLOCKED, (k_quant_blocked<MODE, SAT, true>), grid, dim3(kBlock), 0, st, src, dst, exps, rows,
-               cols, B, nb, s, bits, k0, k1, role, seg_log2);
+    DFP_LAUNCH(K_QUANT_BLOCKED, (k_quant_blocked<MODE, SAT, true>), grid, dim3(kBlockedThreads), 0, st, src, dst,
+               exps, rows, cols, B, nb, s, bits, k0, k1, role, seg_log2, nb_div);
   else
-    DFP_LAUNCH(K_QUANT_BLOCKED, (k_quant_blocked<MODE, SAT, false>), grid, dim3(kBlock), 0, st, src, dst, exps,
-               rows, cols, B, nb, s, bits, k0, k1, role, seg_log2);
+    DFP_LAUNCH(K_QUANT_BLOCKED, (k_quant_blocked<MODE, SAT, false>), grid, dim3(kBlockedThreads), 0, st, src, dst,
+               exps, rows, cols, B, nb, s, bits, k0, k1, role, seg_log2, nb_div);
   return DFP_OK;
 }
 
