@@ -485,80 +485,105 @@ __device__ __forceinline__ int swz(int row, int piece) { return row * 4 + (piece
 // contiguous bytes per row and band), splits every element into its byte
 // digits once, and writes them in the MFMA operand layout: per block and row,
 // four 16-byte pieces (hi digits of indices 0-15, 16-31, then lo), swizzled
-// across LDS banks as in the forward kernels.  Each of the four waves then
-// reads its 32 x 32 tile's operands from LDS.  The loads of band b + 1 are in
-// flight while band b is multiplied (two LDS buffers, one barrier per band).
-// A piece lies in one image (P*Q a multiple of PIECE); rows past K or C and
-// indices past T are zeros.  The loads are buffer loads: per band one offset
-// per lane and operand (one division), the row step of the thread's pieces in
-// the scalar offset, and rows past K or C or indices past T at an offset past
-// the end of the tensor, which reads zeros (both tensors below 2 GiB: checked
-// by the launcher).  Chunks, segments and output as in k_bwdw_1x1.
+// across LDS banks as in the forward kernels.  Each of the eight waves then
+// reads its 32 x 16 tile's operands from LDS.
+// What bounds it: a ResNet layer at the default segments has about one
+// workgroup per CU, so everything in a band's chain of load, split, LDS write,
+// barrier, LDS read, product and conversion waits in the open (2200 cycles a
+// band with four waves of 32 x 32, 300 of them matrix instructions).  Hence
+// two waves per SIMD, loads k1x1Depth bands ahead in registers, and the reads
+// of band b in flight while band b - 1 is multiplied (two LDS buffers, one
+// barrier per band).  Two bands
+// ahead serve as well as four (and four alone, with four waves, gave 5-8%); the
+// waves' instructions are now most of a band.  Kernel, event times: 1024 -> 256
+// on 14 x 14, N = 64, 64 -> 41 us (L = 32: 70 -> 52); 256 -> 64 on 56 x 56 and
+// 512 -> 128 on 28 x 28, N = 32, 57 -> 33 us.
+// A piece lies in one image (P*Q a multiple of PIECE).  The loads are buffer
+// loads from offsets kept per lane and operand, the row step of the thread's
+// pieces in the scalar offset; indices past T take an offset past the end of
+// the tensor, which reads zeros (both tensors below 2 GiB: checked by the
+// launcher).  Rows past K or C read zeros or another image's elements, which
+// reach only outputs that are not stored; bands past the segment are not
+// multiplied.  KS: indices per matrix instruction, 64 where L is a multiple of
+// 64, else 32; ONE: L == KS, a chunk is one step.  Chunks, segments and output
+// as in k_bwdw_1x1.
 // Raw buffer resource over [p, p + bytes) (offsets past the end read zeros).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
 }
-template <int PIECE>
-__global__ __launch_bounds__(k1x1Threads, 4) void k_bwdw_1x1s(BwdwArgs a, Raw1x1 raw) {
-  constexpr int kLoads = 64 * 64 / PIECE / k1x1Threads;  // pieces per thread and operand per band
+template <int N>
+using IC = std::integral_constant<int, N>;
+constexpr int k1x1sThreads = 512;
+constexpr int k1x1Depth = 2;  // bands of loads in flight
+template <int PIECE, int KS, bool ONE>
+__global__ __launch_bounds__(k1x1sThreads, 4) void k_bwdw_1x1s(BwdwArgs a, Raw1x1 raw) {
+  constexpr int kLoads = 64 * 64 / PIECE / k1x1sThreads;  // pieces per thread and operand per band
   constexpr int kPerRow = 64 / PIECE;                     // pieces per row and band
   __shared__ __align__(16) uint8_t sbuf[2][2][2 * 4096];  // [buffer][operand][block][64 rows x 64 B]
   const BwdwTile tl = bwdw_tile(a);
   if (tl.seg >= a.nseg) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5, lc = lane & 31;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kg = lane >> 4, lc = lane & 15;
   const int32_t rA0 = tl.ty * 64, rB0 = tl.tx * 64;  // the workgroup's dy rows (k) and x rows (c)
   const int64_t t_seg0 = (int64_t)tl.seg * a.G * a.L;
   const int64_t t_seg1 = min(t_seg0 + (int64_t)a.G * a.L, a.T);
-  const int64_t kb_begin = t_seg0 / 32, kb_end = (t_seg1 + 31) / 32;
-  const int32_t chunk_blocks = a.L / 32;
+  const int32_t kb_begin = (int32_t)(t_seg0 / 32), kb_end = (int32_t)((t_seg1 + 31) / 32);
   const int32_t PQ = raw.PQ;
   typedef uint32_t vraw __attribute__((ext_vector_type(PIECE / 2)));
-  vraw ra[kLoads], rb[kLoads];
-  // piece i = j * 256 + thread of the band starting at block kb: row i / kPerRow,
+  vraw ra[k1x1Depth][kLoads], rb[k1x1Depth][kLoads];
+  // piece i = j * 512 + thread of the band starting at block kb: row i / kPerRow,
   // indices PIECE (i % kPerRow) .. of the band; i % kPerRow is the same for
-  // every j (256 is a multiple of kPerRow), so a thread's pieces share one
-  // index range and one image, and piece j lies j * (256 / kPerRow) rows after
+  // every j (512 is a multiple of kPerRow), so a thread's pieces share one
+  // index range and one image, and piece j lies j * (512 / kPerRow) rows after
   // piece 0
   const int32_t pj = (int32_t)threadIdx.x % kPerRow, row0 = (int32_t)threadIdx.x / kPerRow;
   const __amdgpu_buffer_rsrc_t rs_dy = make_rsrc(raw.dy, (uint32_t)(a.T * a.K * 2));
   const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(raw.x, (uint32_t)(a.T * a.C * 2));
-  const int32_t KPQ = a.K * PQ, CPQ = a.C * PQ;
-  const int32_t rowA = (rA0 + row0) * PQ, rowB = (rB0 + row0) * PQ;
-  const uint32_t jstep = (uint32_t)(k1x1Threads / kPerRow) * (uint32_t)PQ * 2u;
+  const uint32_t jstep = (uint32_t)(k1x1sThreads / kPerRow) * (uint32_t)PQ * 2u;
   constexpr uint32_t kOut = 0x80000000u;  // past the end of either tensor
-  auto load_band = [&](int64_t kb) {
-    const int32_t t = (int32_t)(kb * 32) + PIECE * pj;
+  // this thread's piece 0 in the next band to load: index, pixel and byte offsets; a band
+  // on is 64 / PQ images and 64 % PQ pixels on, and one image more where that passes the end
+  int32_t t = kb_begin * 32 + PIECE * pj;
+  const int32_t n0 = (int32_t)fdiv((uint32_t)t, a.div_q);
+  int32_t pq = t - n0 * PQ;
+  uint32_t oa = ((uint32_t)n0 * (uint32_t)a.K + (uint32_t)(rA0 + row0)) * (uint32_t)PQ * 2u + (uint32_t)pq * 2u;
+  uint32_t ob = ((uint32_t)n0 * (uint32_t)a.C + (uint32_t)(rB0 + row0)) * (uint32_t)PQ * 2u + (uint32_t)pq * 2u;
+  const int32_t dn = 64 / PQ, dpq = 64 - dn * PQ;
+  const uint32_t sa = ((uint32_t)(dn * a.K) * (uint32_t)PQ + (uint32_t)dpq) * 2u;
+  const uint32_t sb = ((uint32_t)(dn * a.C) * (uint32_t)PQ + (uint32_t)dpq) * 2u;
+  const uint32_t wa = (uint32_t)(a.K - 1) * (uint32_t)PQ * 2u, wb = (uint32_t)(a.C - 1) * (uint32_t)PQ * 2u;
+  auto load_band = [&](int set) __attribute__((always_inline)) {
     const bool tin = t < (int32_t)a.T;
-    const int32_t n = (int32_t)fdiv((uint32_t)(tin ? t : 0), a.div_q), pq = t - n * PQ;
-    const uint32_t oa0 = tin ? (uint32_t)(n * KPQ + rowA + pq) * 2u : kOut;
-    const uint32_t ob0 = tin ? (uint32_t)(n * CPQ + rowB + pq) * 2u : kOut;
+    const uint32_t va = tin ? oa : kOut, vb = tin ? ob : kOut;
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) {
-      const int32_t row = j * (k1x1Threads / kPerRow) + row0;
-      const uint32_t oa = rA0 + row < a.K ? oa0 : kOut;
-      const uint32_t ob = rB0 + row < a.C ? ob0 : kOut;
       const uint32_t so = __builtin_amdgcn_readfirstlane((uint32_t)j * jstep);
       if constexpr (PIECE == 8) {
-        ra[j] = __builtin_bit_cast(vraw, __builtin_amdgcn_raw_buffer_load_b128(rs_dy, oa, so, 0));
-        rb[j] = __builtin_bit_cast(vraw, __builtin_amdgcn_raw_buffer_load_b128(rs_x, ob, so, 0));
+        ra[set][j] = __builtin_bit_cast(vraw, __builtin_amdgcn_raw_buffer_load_b128(rs_dy, va, so, 0));
+        rb[set][j] = __builtin_bit_cast(vraw, __builtin_amdgcn_raw_buffer_load_b128(rs_x, vb, so, 0));
       } else {
-        ra[j] = __builtin_bit_cast(vraw, __builtin_amdgcn_raw_buffer_load_b64(rs_dy, oa, so, 0));
-        rb[j] = __builtin_bit_cast(vraw, __builtin_amdgcn_raw_buffer_load_b64(rs_x, ob, so, 0));
+        ra[set][j] = __builtin_bit_cast(vraw, __builtin_amdgcn_raw_buffer_load_b64(rs_dy, va, so, 0));
+        rb[set][j] = __builtin_bit_cast(vraw, __builtin_amdgcn_raw_buffer_load_b64(rs_x, vb, so, 0));
       }
     }
+    t += 64;
+    pq += dpq;
+    const bool wrap = pq >= PQ;
+    pq -= wrap ? PQ : 0;
+    oa += wrap ? sa + wa : sa;
+    ob += wrap ? sb + wb : sb;
   };
   // digits of the staged pieces into buffer buf
-  auto write_band = [&](int buf) {
+  auto write_band = [&](int set, int buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) {
-      const int32_t row = j * (k1x1Threads / kPerRow) + row0;
+      const int32_t row = j * (k1x1sThreads / kPerRow) + row0;
       const int32_t e = PIECE * pj;                       // index within the band
       const int32_t blk = e >> 5, h16 = (e >> 4) & 1, sub = e & 15;
       const int32_t off_hi = blk * 4096 + swz(row, h16) * 16 + sub;
       const int32_t off_lo = blk * 4096 + swz(row, 2 + h16) * 16 + sub;
 #pragma unroll
       for (int op = 0; op < 2; ++op) {
-        const vraw w = op == 0 ? ra[j] : rb[j];
+        const vraw w = op == 0 ? ra[set][j] : rb[set][j];
         uint32_t hi[PIECE / 4], lo[PIECE / 4];
 #pragma unroll
         for (int d = 0; d < PIECE / 4; ++d) {
@@ -580,44 +605,115 @@ __global__ __launch_bounds__(k1x1Threads, 4) void k_bwdw_1x1s(BwdwArgs a, Raw1x1
     }
   };
 
-  Acc3 acc;
-  float sum[16];
+  // operands of one band: KS == 64: 16 digits of index group kg; 32: 8 of each block
+  constexpr int kSteps = 64 / KS;
+  typedef int vop __attribute__((ext_vector_type(KS / 16)));
+  struct Ops {
+    vop ah[kSteps][2], al[kSteps][2], bh[kSteps], bl[kSteps];
+  };
+  Ops ops[2] = {};
+  const int32_t ra_row = (wave >> 2) * 32 + lc, rb_row = (wave & 3) * 16 + lc;
+  const int32_t pc = KS == 64 ? kg & 1 : kg >> 1;
+  const uint32_t sub_kg = KS == 64 ? (uint32_t)(kg >> 1) * 4096u : (uint32_t)(kg & 1) * 8u;
+  const uint32_t oa_hi = sub_kg + swz(ra_row, pc) * 16, oa_lo = sub_kg + swz(ra_row, 2 + pc) * 16;
+  const uint32_t ob_hi = sub_kg + swz(rb_row, pc) * 16, ob_lo = sub_kg + swz(rb_row, 2 + pc) * 16;
+  auto read_ops = [&](Ops& o, int buf) __attribute__((always_inline)) {
 #pragma unroll
-  for (int v = 0; v < 16; ++v) sum[v] = 0.f;
-  const int32_t ra_row = (wave >> 1) * 32 + lc, rb_row = (wave & 1) * 32 + lc;
-  const uint32_t oa_hi = swz(ra_row, half) * 16, oa_lo = swz(ra_row, 2 + half) * 16;
-  const uint32_t ob_hi = swz(rb_row, half) * 16, ob_lo = swz(rb_row, 2 + half) * 16;
-  int32_t blk_in_chunk = 0;
-  load_band(kb_begin);
-  int buf = 0;
-  for (int64_t kb = kb_begin; kb < kb_end; kb += 2, buf ^= 1) {
-    write_band(buf);
-    __syncthreads();
-    if (kb + 2 < kb_end) load_band(kb + 2);
-    const int32_t nblk = (int32_t)min((int64_t)2, kb_end - kb);
-    for (int32_t b = 0; b < nblk; ++b) {
-      const uint8_t* pa = &sbuf[buf][0][b * 4096];
-      const uint8_t* pb = &sbuf[buf][1][b * 4096];
-      const v4i ahi = *reinterpret_cast<const v4i*>(pa + oa_hi), alo = *reinterpret_cast<const v4i*>(pa + oa_lo);
-      const v4i bhi = *reinterpret_cast<const v4i*>(pb + ob_hi), blo = *reinterpret_cast<const v4i*>(pb + ob_lo);
-      mfma_tile(acc, ahi, alo, bhi, blo, blk_in_chunk == 0);
-      if (++blk_in_chunk == chunk_blocks || kb + b == kb_end - 1) {
-        flush_tile<false>(acc, sum, 0, nullptr, a.O, 0, a.C, 0, a.K, false);
-        blk_in_chunk = 0;
+    for (int st = 0; st < kSteps; ++st) {
+      const uint8_t* pa = &sbuf[buf][0][st * 4096];
+      const uint8_t* pb = &sbuf[buf][1][st * 4096];
+      o.bh[st] = *reinterpret_cast<const vop*>(pb + ob_hi);
+      o.bl[st] = *reinterpret_cast<const vop*>(pb + ob_lo);
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) {  // 16 rows on: 1024 bytes, the same swizzle
+        o.ah[st][rt] = *reinterpret_cast<const vop*>(pa + oa_hi + rt * 1024);
+        o.al[st][rt] = *reinterpret_cast<const vop*>(pa + oa_lo + rt * 1024);
       }
     }
+  };
+  auto mma = [](const vop& x, const vop& y, const v4i& c) __attribute__((always_inline)) {
+    if constexpr (KS == 64) return __builtin_amdgcn_mfma_i32_16x16x64_i8(x, y, c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_i32_16x16x32_i8(__builtin_bit_cast(long, x), __builtin_bit_cast(long, y), c, 0, 0, 0);
+  };
+  v4i hh[2], xx[2], ll[2];
+  float sum[2][4];
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) {
+    hh[rt] = xx[rt] = ll[rt] = (v4i){0, 0, 0, 0};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sum[rt][v] = 0.f;
   }
-  const int32_t m0 = rA0 + (wave >> 1) * 32, c = rB0 + (wave & 1) * 32 + lc;
+  auto flush = [&](int rt) __attribute__((always_inline)) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      sum[rt][v] += (float)(int32_t)recombine((uint32_t)hh[rt][v], (uint32_t)xx[rt][v], (uint32_t)ll[rt][v]);
+  };
+  const int32_t chunk_steps = a.L / KS;
+  int32_t done = -kSteps;  // steps of the chunk (the zero operands before the first band excepted)
+  auto mul = [&](const Ops& o, int32_t nst) __attribute__((always_inline)) {  // nst: steps of the band in the segment
+#pragma unroll
+    for (int st = 0; st < kSteps; ++st) {
+      if (kSteps > 1 && st >= nst) break;
+      if (ONE || done <= 0) {
+        const v4i z = {0, 0, 0, 0};
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) hh[rt] = xx[rt] = ll[rt] = z;
+      }
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) {
+        xx[rt] = mma(o.ah[st][rt], o.bl[st], xx[rt]);
+        hh[rt] = mma(o.ah[st][rt], o.bh[st], hh[rt]);
+        ll[rt] = mma(o.al[st][rt], o.bl[st], ll[rt]);
+        xx[rt] = mma(o.al[st][rt], o.bh[st], xx[rt]);
+      }
+      if (ONE || ++done == chunk_steps) {
+        flush(0);
+        flush(1);
+        done = 0;
+      }
+    }
+  };
+
+#pragma unroll
+  for (int d = 0; d < k1x1Depth; ++d) load_band(d);
+  // Round b: band b to LDS, its operands requested, band b - 1 multiplied; the
+  // round past the last band writes what nothing multiplies.  Whole groups of
+  // k1x1Depth rounds without a branch, then the rest.
+  auto round = [&](auto dc, int32_t kb, auto more) __attribute__((always_inline)) {
+    constexpr int D = decltype(dc)::value;
+    write_band(D, D & 1);
+    // every wave's writes of band b and reads of band b - 1 are done
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    read_ops(ops[D & 1], D & 1);
+    if constexpr (decltype(more)::value) load_band(D);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(ops[(D & 1) ^ 1], kb_end - (kb - 2));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  static_assert(k1x1Depth == 2, "rounds below");
+  int32_t rounds = (kb_end - kb_begin + 1) / 2 + 1, kb = kb_begin;
+  for (; rounds >= 2; rounds -= 2, kb += 4) {
+    round(IC<0>{}, kb, std::true_type{});
+    round(IC<1>{}, kb + 2, std::true_type{});
+  }
+  if (rounds > 0) round(IC<0>{}, kb, std::false_type{});
+  if (!ONE && done > 0) {
+    flush(0);
+    flush(1);
+  }
+  const int32_t c = rB0 + rb_row;
   const int32_t e = a.ea->exp + a.eb->exp;
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int32_t m = m0 + 8 * (v >> 2) + 4 * half + (v & 3);
-    if (c < a.C && m < a.K) {
-      const int64_t o = (int64_t)m * a.C + c;
-      if (a.nseg == 1) a.out[o] = ldexpf(sum[v], e);
-      else a.useg[(int64_t)tl.seg * a.O + o] = sum[v];
+  for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int32_t m = rA0 + (wave >> 2) * 32 + rt * 16 + 4 * kg + v;
+      if (c < a.C && m < a.K) {
+        const int64_t o = (int64_t)m * a.C + c;
+        if (a.nseg == 1) a.out[o] = ldexpf(sum[rt][v], e);
+        else a.useg[(int64_t)tl.seg * a.O + o] = sum[rt][v];
+      }
     }
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1161,8 +1257,6 @@ constexpr int kBandBufBytes = kBandLdsBytes / 2;
 // offsets (kBandBufBigBytes + 3 * 4096 + 15 < 65536).
 constexpr int kBandBufBigBytes = 51 * 1024;
 
-template <int N>
-using IC = std::integral_constant<int, N>;
 
 // LDS reads at a lane address plus an immediate byte offset.
 template <int OFF>
@@ -2651,9 +2745,20 @@ dfp_status launch_bwdw_mfma(const Geom& g, const int16_t* x, const dfp_scale* sx
     args.nty = p.Mp / 64;
     const dim3 grid1((unsigned)(p.nseg * args.ntx * args.nty));
     args.div_q = make_fastdiv((uint32_t)PQ);  // the direct kernels: image of an index
-    if (direct && PQ % 8 == 0) DFP_LAUNCH(K_BWDW_MFMA, k_bwdw_1x1s<8>, grid1, dim3(k1x1Threads), 0, st, args, raw);
-    else if (direct) DFP_LAUNCH(K_BWDW_MFMA, k_bwdw_1x1s<4>, grid1, dim3(k1x1Threads), 0, st, args, raw);
+#define DFP_1X1S(P, KS, ONE) \
+  DFP_LAUNCH(K_BWDW_MFMA, (k_bwdw_1x1s<P, KS, ONE>), grid1, dim3(k1x1sThreads), 0, st, args, raw)
+#define DFP_1X1S_L(P)                               \
+  do {                                              \
+    if (g.L == 64) DFP_1X1S(P, 64, true);           \
+    else if (g.L % 64 == 0) DFP_1X1S(P, 64, false); \
+    else if (g.L == 32) DFP_1X1S(P, 32, true);      \
+    else DFP_1X1S(P, 32, false);                    \
+  } while (0)
+    if (direct && PQ % 8 == 0) DFP_1X1S_L(8);
+    else if (direct) DFP_1X1S_L(4);
     else DFP_LAUNCH(K_BWDW_MFMA, k_bwdw_1x1, grid1, dim3(k1x1Threads), 0, st, args, bd, Cp);
+#undef DFP_1X1S_L
+#undef DFP_1X1S
     if (p.nseg > 1)
       DFP_LAUNCH(K_BWDW_REDUCE, k_seg_reduce, dim3((unsigned)((args.O + 63) / 64)), dim3(64), 0, st, useg, dw,
                  args.O, p.nseg, sx, sdy);
