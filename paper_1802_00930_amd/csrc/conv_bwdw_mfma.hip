@@ -90,6 +90,12 @@ __device__ __forceinline__ void prep_dy_item(const DyPrep& q, int32_t idx) {
   dst[1] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
 }
 __global__ __launch_bounds__(256) void k_prep_dy(DyPrep q) { prep_dy_item(q, blockIdx.x * 256 + threadIdx.x); }
+// Both operands of a 1x1 layer: workgroups [0, nba) dy, the rest x.
+__global__ __launch_bounds__(256) void k_prep_dy2(DyPrep q, DyPrep qx, int32_t nba) {
+  const int32_t b = blockIdx.x;
+  if (b < nba) prep_dy_item(q, b * 256 + threadIdx.x);
+  else prep_dy_item(qx, (b - nba) * 256 + threadIdx.x);
+}
 
 // XP[c][n*Hpad + u][v] = (lo | hi << 8) of x[n][c][u - ph][v - pw], zero outside.
 // Grid (rows of channel c, c): one thread per 8 consecutive pairs of a row
@@ -2727,8 +2733,8 @@ dfp_status launch_bwdw_mfma(const Geom& g, const int16_t* x, const dfp_scale* sx
                         p.T * std::max(g.c, g.k) * 2 < (1ll << 31);
     if (!direct) {
       const DyPrep dqx{x, bd, g.c, Cp, PQ, (int32_t)p.T, (int32_t)p.KBT};
-      DFP_LAUNCH(K_WPREP, k_prep_dy, dim3((unsigned)dy_blocks), dim3(256), 0, st, dq);
-      DFP_LAUNCH(K_XPREP, k_prep_dy, dim3((unsigned)((p.KBT * Cp * 2 + 255) / 256)), dim3(256), 0, st, dqx);
+      const int64_t nbx = (p.KBT * Cp * 2 + 255) / 256;
+      DFP_LAUNCH(K_XPREP, k_prep_dy2, dim3((unsigned)(dy_blocks + nbx)), dim3(256), 0, st, dq, dqx, (int32_t)dy_blocks);
     }
     const Raw1x1 raw{dy, x, PQ};
     BwdwArgs args{};

@@ -77,8 +77,13 @@ __device__ __forceinline__ uint32_t lo_digit(int32_t a) { return (uint32_t)a & 0
 
 // ---------------------------------------------------------------- A prep
 // A[m][t] for t = (r*S + s)*Cin + ci.  fwd: m = k, ci = c, value w[m][ci][r][s].
-// bwd-data: m = c, ci = k, value w[ci][m][r][s].  One thread per 4 digits of
-// one (kb, m, half) piece: the hi and lo words it packs land 16 bytes apart.
+// bwd-data: m = c, ci = k, value w[ci][m][r][s].  Cin a multiple of 16: one
+// thread per 32-byte piece (kb, m, half), whose 16 channels belong to one
+// filter tap; consecutive threads take the taps of one (m, channel group), then
+// the next group (fwd) or row (bwd-data), so a wave's loads share cache lines
+// (four digits per thread in the order of the pieces read every line once per
+// tap: 512 x 512 x 3 x 3 7.1 us; with the input's 7 x 7 planes in the same
+// launch 13.8 us that way, 7.2 this way).  Otherwise one thread per 4 digits of a piece.
 // The same launch clears the output scale and writes the per-block B offset
 // table of the main kernels.
 struct PrepAArgs {
@@ -89,9 +94,45 @@ struct PrepAArgs {
   int2* boff;
   int32_t tap_row_bytes, tap_col_bytes;
 };
+__host__ __device__ __forceinline__ int32_t prep_a_items(const PrepAArgs& a) {
+  return a.KB * a.Mp * (a.Cin % 16 == 0 ? 2 : 8);
+}
 
-// Work item idx of the filter-digit preparation: ((kb, m, half), quarter), plus
-// the block offset table (idx < KB) and the output-scale reset (idx 0).
+// One 32-byte piece (16 channels of one tap), idx < 2 KB Mp.
+__device__ __forceinline__ void prep_a_piece(const PrepAArgs& a, int32_t idx) {
+  const int32_t CG = a.Cin >> 4, RS = a.R * a.S, full = a.Mp * CG * RS;
+  int32_t m, piece;  // piece: 16-index half-block of the row
+  uint32_t hi[4] = {0u, 0u, 0u, 0u}, lo[4] = {0u, 0u, 0u, 0u};
+  if (idx >= full) {  // T an odd number of half-blocks: the last one is zero
+    m = idx - full;
+    piece = 2 * a.KB - 1;
+  } else {
+    const int32_t rest = idx / RS, tap = idx - rest * RS;
+    const int32_t q = rest / (a.transposed ? a.Mp : CG), rm = rest - q * (a.transposed ? a.Mp : CG);
+    m = a.transposed ? rm : q;
+    const int32_t cg = a.transposed ? q : rm;
+    piece = tap * CG + cg;
+    if (m < a.M) {
+      // forward: w[m][ci][tap]; backward-data: w[ci][m][tap] (Cw = C)
+      const int16_t* src = a.w + (a.transposed ? (cg * 16 * a.Cw + m) * RS + tap : (m * a.Cw + cg * 16) * RS + tap);
+      const int32_t step = a.transposed ? a.Cw * RS : RS;
+      int32_t v[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[k] = (int32_t)src[k * step];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        hi[k >> 2] |= hi_digit(v[k]) << (8 * (k & 3));
+        lo[k >> 2] |= lo_digit(v[k]) << (8 * (k & 3));
+      }
+    }
+  }
+  uint4* dst = reinterpret_cast<uint4*>(a.ws + (((int64_t)(piece >> 1) * a.Mp + m) * 2 + (piece & 1)) * 32);
+  dst[0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+  dst[1] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+}
+
+// Work item idx of the filter-digit preparation, plus the block offset table
+// (idx < KB) and the output-scale reset (idx 0).
 __device__ __forceinline__ void prep_a_item(const PrepAArgs& a, int32_t idx) {
   if (a.so && idx == 0) {  // the output scale starts empty; the conv epilogue raises its max
     a.so->amax_bits = 0u;
@@ -109,8 +150,11 @@ __device__ __forceinline__ void prep_a_item(const PrepAArgs& a, int32_t idx) {
     }
     a.boff[idx] = make_int2(o[0], o[1]);
   }
-  const int32_t total = a.KB * a.Mp * 8;
-  if (idx >= total) return;
+  if (idx >= prep_a_items(a)) return;
+  if (a.Cin % 16 == 0) {
+    prep_a_piece(a, idx);
+    return;
+  }
   const int32_t quarter = idx & 3;
   const int32_t piece = idx >> 2;  // (kb * Mp + m) * 2 + half
   const int32_t half = piece & 1;
@@ -155,9 +199,13 @@ template <bool VEC>
 __global__ __launch_bounds__(256) void k_prep_b(const int16_t* __restrict__ src, uint8_t* __restrict__ xs,
                                                int32_t N, int32_t Cs, int32_t Hs, int32_t Wsrc, int32_t Hp,
                                                int32_t Wp, int32_t CG, int32_t top, int32_t left, int32_t dil_h,
-                                               int32_t dil_w) {
+                                               int32_t dil_w, PrepAArgs pa) {
   extern __shared__ __align__(16) int16_t tile[];  // cgc * 16 * Wsrc elements (launcher sizes it)
   const int32_t row = blockIdx.x;  // n * Hp + u
+  if (row >= N * Hp) {  // workgroups past the rows prepare the filter digits
+    prep_a_item(pa, (row - N * Hp) * 256 + threadIdx.x);
+    return;
+  }
   const int32_t n = row / Hp, u = row - n * Hp;
   const int32_t zu = u - top;
   const bool row_in = zu >= 0 && (zu % dil_h) == 0 && zu / dil_h < Hs;
@@ -218,101 +266,16 @@ __global__ __launch_bounds__(256) void k_prep_b(const int16_t* __restrict__ src,
 // Plane layout Xs[n][u][cb][digit][half][v][16 B] (CG even): the hi digits of
 // channel group cg = 2 cb + half at column v sit at ((cb * 4 + half) * Wp + v)
 // * 16 within row u, the lo digits 2 * Wp * 16 bytes further; sources and
-// zero rows / columns as for k_prep_b.  Workgroup (row block, cg, n) stages
-// the group's 16 channels for up to kPlaneRows output rows in LDS as channel
-// pairs, [row][pair][w] of 32-bit (even | odd << 16) words: for one channel the
-// source rows of a block are adjacent (unit dilation), so the global reads are
-// long runs along w, the LDS writes and reads are consecutive words across
-// lanes (no bank conflicts), and the digits of each output row are written as
-// two contiguous runs of Wp * 16 bytes.
-constexpr int kPlaneRows = 8;
-// The register-only preparation (k_prep_plane_direct) measured faster than
-// the LDS-staged one on ResNet-50 conv2_x (8.0 against 8.7 us).
-constexpr bool kPlaneDirect = true;
-constexpr int kPlaneElems = 16384;  // int16 elements staged (32 KiB)
-
-template <bool VEC>
-__global__ __launch_bounds__(256) void k_prep_plane(const int16_t* __restrict__ src, uint8_t* __restrict__ xs,
-                                                   int32_t Cs, int32_t Hs, int32_t Wsrc, int32_t Hp, int32_t Wp,
-                                                   int32_t CG, int32_t top, int32_t left, int32_t dil_h,
-                                                   int32_t dil_w, int32_t rb, PrepAArgs pa, int32_t with_a) {
-  extern __shared__ __align__(16) uint32_t tile2[];  // [rb][8][Wsrc] channel pairs
-  if (with_a && blockIdx.z == gridDim.z - 1) {  // one extra slice of workgroups prepares the filter digits
-    const int32_t nthr = gridDim.x * gridDim.y * 256;
-    const int32_t total = max(pa.KB * pa.Mp * 8, pa.KB);
-    for (int32_t idx = (blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; idx < total; idx += nthr)
-      prep_a_item(pa, idx);
-    return;
-  }
-  const int32_t u0 = blockIdx.x * rb, cg = blockIdx.y, n = blockIdx.z;
-  const int32_t nr = min(rb, Hp - u0);
-  const int64_t plane = (int64_t)Hs * Wsrc;
-  const int16_t* sbase = src + ((int64_t)n * Cs + cg * 16) * plane;
-  // source row of output row u0 + r, or -1 for a zero row
-  auto src_row = [&](int32_t r) {
-    const int32_t zu = u0 + r - top;
-    return (zu >= 0 && (zu % dil_h) == 0 && zu / dil_h < Hs) ? zu / dil_h : -1;
-  };
-  if (VEC) {  // 8 consecutive columns of one (row, channel pair) per thread
-    const int32_t W8 = Wsrc >> 3;
-    for (int32_t j = threadIdx.x; j < nr * 8 * W8; j += 256) {
-      const int32_t w8 = j % W8, rest = j / W8, pr = rest & 7, r = rest >> 3;
-      const int32_t h = src_row(r);
-      const int32_t c0 = cg * 16 + 2 * pr;
-      uint4 e = make_uint4(0u, 0u, 0u, 0u), o = make_uint4(0u, 0u, 0u, 0u);
-      if (h >= 0 && c0 < Cs) e = *reinterpret_cast<const uint4*>(sbase + 2 * pr * plane + (int64_t)h * Wsrc + w8 * 8);
-      if (h >= 0 && c0 + 1 < Cs)
-        o = *reinterpret_cast<const uint4*>(sbase + (2 * pr + 1) * plane + (int64_t)h * Wsrc + w8 * 8);
-      uint4* t = reinterpret_cast<uint4*>(tile2 + ((int64_t)r * 8 + pr) * Wsrc + w8 * 8);
-      t[0] = make_uint4(__builtin_amdgcn_perm(o.x, e.x, 0x05040100u), __builtin_amdgcn_perm(o.x, e.x, 0x07060302u),
-                        __builtin_amdgcn_perm(o.y, e.y, 0x05040100u), __builtin_amdgcn_perm(o.y, e.y, 0x07060302u));
-      t[1] = make_uint4(__builtin_amdgcn_perm(o.z, e.z, 0x05040100u), __builtin_amdgcn_perm(o.z, e.z, 0x07060302u),
-                        __builtin_amdgcn_perm(o.w, e.w, 0x05040100u), __builtin_amdgcn_perm(o.w, e.w, 0x07060302u));
-    }
-  } else {
-    for (int32_t j = threadIdx.x; j < nr * 8 * Wsrc; j += 256) {
-      const int32_t w = j % Wsrc, rest = j / Wsrc, pr = rest & 7, r = rest >> 3;
-      const int32_t h = src_row(r);
-      const int32_t c0 = cg * 16 + 2 * pr;
-      const uint32_t ev = (h >= 0 && c0 < Cs) ? (uint16_t)sbase[2 * pr * plane + (int64_t)h * Wsrc + w] : 0u;
-      const uint32_t ov = (h >= 0 && c0 + 1 < Cs) ? (uint16_t)sbase[(2 * pr + 1) * plane + (int64_t)h * Wsrc + w] : 0u;
-      tile2[((int64_t)r * 8 + pr) * Wsrc + w] = ev | (ov << 16);
-    }
-  }
-  __syncthreads();
-  const int64_t row_bytes = (int64_t)CG * 32 * Wp;
-  const int32_t off_hi = ((cg >> 1) * 4 + (cg & 1)) * Wp;  // in 16-byte units within the row
-  for (int32_t j = threadIdx.x; j < nr * Wp; j += 256) {
-    const int32_t v = j % Wp, r = j / Wp;
-    const int32_t zv = v - left;
-    const bool in = src_row(r) >= 0 && zv >= 0 && (zv % dil_w) == 0 && zv / dil_w < Wsrc;
-    uint32_t hi[4] = {0u, 0u, 0u, 0u}, lo[4] = {0u, 0u, 0u, 0u};
-    if (in) {
-      const uint32_t* tp = tile2 + (int64_t)r * 8 * Wsrc + zv / dil_w;
-#pragma unroll
-      for (int pr = 0; pr < 8; ++pr) {
-        const uint32_t wv = tp[pr * Wsrc];
-#pragma unroll
-        for (int h2 = 0; h2 < 2; ++h2) {
-          const int i = 2 * pr + h2;
-          const int32_t a = (int32_t)(int16_t)(wv >> (16 * h2));
-          hi[i >> 2] |= hi_digit(a) << (8 * (i & 3));
-          lo[i >> 2] |= lo_digit(a) << (8 * (i & 3));
-        }
-      }
-    }
-    uint4* d = reinterpret_cast<uint4*>(xs + ((int64_t)n * Hp + u0 + r) * row_bytes) + off_hi + v;
-    d[0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-    d[2 * Wp] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-  }
-}
-
+// zero rows / columns as for k_prep_b.
+//
 // Plane layout written straight from registers: workgroup (u, n) covers
 // output row u of image n, a thread the 16 channels of group cg at column v
 // (lanes of a wave take consecutive columns, so each of the 16 channel loads
 // of a wave reads one contiguous run of the source row, and each of its two
-// 16-byte stores one contiguous run of the plane).  An extra row of
-// workgroups (with_a) prepares the filter digits.  Workgroup ids are mapped
+// 16-byte stores one contiguous run of the plane).  Rows of workgroups past
+// the images prepare the filter digits: a
+// launch of its own costs about 4 us behind other work (512 -> 512 on 7 x 7:
+// 7.1 + 5.5 us in two launches, 7.2 in one).  Workgroup ids are mapped
 // to rows so that each XCD (id mod 8) takes one contiguous range of rows of
 // whole images: a 128-byte line of the source holds parts of two rows, and
 // with neighbouring rows on different XCDs every such line was fetched into
@@ -320,15 +283,13 @@ __global__ __launch_bounds__(256) void k_prep_plane(const int16_t* __restrict__ 
 __global__ __launch_bounds__(256) void k_prep_plane_direct(const int16_t* __restrict__ src, uint8_t* __restrict__ xs,
                                                           int32_t Cs, int32_t Hs, int32_t Wsrc, int32_t Hp, int32_t Wp,
                                                           int32_t CG, int32_t top, int32_t left, int32_t dil_h,
-                                                          int32_t dil_w, PrepAArgs pa, int32_t with_a) {
+                                                          int32_t dil_w, PrepAArgs pa, int32_t N) {
   const int32_t nwg = gridDim.x * gridDim.y, id = blockIdx.y * gridDim.x + blockIdx.x;
   const int32_t xcd = id & 7, per = nwg >> 3, rem = nwg & 7;
   const int32_t l = xcd * per + min(xcd, rem) + (id >> 3);
   const int32_t n = l / (int32_t)gridDim.x, u = l - n * (int32_t)gridDim.x;
-  if (with_a && n == (int32_t)gridDim.y - 1) {
-    const int32_t nthr = gridDim.x * 256;
-    const int32_t total = max(pa.KB * pa.Mp * 8, pa.KB);
-    for (int32_t idx = u * 256 + threadIdx.x; idx < total; idx += nthr) prep_a_item(pa, idx);
+  if (n >= N) {
+    prep_a_item(pa, ((n - N) * (int32_t)gridDim.x + u) * 256 + (int32_t)threadIdx.x);
     return;
   }
   const int32_t zu = u - top;
@@ -366,15 +327,13 @@ __global__ __launch_bounds__(256) void k_prep_plane_direct(const int16_t* __rest
 __global__ __launch_bounds__(256) void k_prep_plane_pair(const int16_t* __restrict__ src, uint8_t* __restrict__ xs,
                                                         int32_t Cs, int32_t Hs, int32_t Wsrc, int32_t Hp, int32_t Wp,
                                                         int32_t CG, int32_t top, int32_t left, PrepAArgs pa,
-                                                        int32_t with_a) {
+                                                        int32_t N) {
   const int32_t nwg = gridDim.x * gridDim.y, id = blockIdx.y * gridDim.x + blockIdx.x;
   const int32_t xcd = id & 7, per_x = nwg >> 3, rem = nwg & 7;
   const int32_t l = xcd * per_x + min(xcd, rem) + (id >> 3);
   const int32_t n = l / (int32_t)gridDim.x, u = l - n * (int32_t)gridDim.x;
-  if (with_a && n == (int32_t)gridDim.y - 1) {
-    const int32_t nthr = gridDim.x * 256;
-    const int32_t total = max(pa.KB * pa.Mp * 8, pa.KB);
-    for (int32_t idx = u * 256 + threadIdx.x; idx < total; idx += nthr) prep_a_item(pa, idx);
+  if (n >= N) {
+    prep_a_item(pa, ((n - N) * (int32_t)gridDim.x + u) * 256 + (int32_t)threadIdx.x);
     return;
   }
   const int32_t h = u - top;
@@ -2576,7 +2535,11 @@ __global__ __launch_bounds__(k1x1fThreads, 4) void k_conv1x1_s(ConvMfmaArgs a, c
 // (they only ever meet zero filter digits or a mask).
 __global__ __launch_bounds__(256) void k_prep_cl(const int16_t* __restrict__ x, uint8_t* __restrict__ xc, int32_t N,
                                                 int32_t C, int32_t H, int32_t W, int32_t Hp, int32_t Wp, int32_t ph,
-                                                int32_t pw, int32_t row_b) {
+                                                int32_t pw, int32_t row_b, int32_t nbx, PrepAArgs pa) {
+  if ((int32_t)blockIdx.x >= nbx) {  // workgroups past the input's prepare the filter digits
+    prep_a_item(pa, ((int32_t)blockIdx.x - nbx) * 256 + threadIdx.x);
+    return;
+  }
   const int32_t W4 = (Wp + 3) / 4;
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= (int64_t)N * Hp * W4) return;
@@ -2717,8 +2680,7 @@ dfp_status launch_conv_mfma(int32_t dir, const Geom& g, const int16_t* a, const 
   if (!i32 && g.r == 1 && g.s == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0 && (g.L % 32) == 0 &&
       PQ1 % 4 == 0 && (reinterpret_cast<uintptr_t>(a) & 7) == 0 && p.KB <= 8 && (int64_t)g.n * PQ1 >= 32768 &&
       (int64_t)g.n * std::max(p.Cin, p.M) * PQ1 < (1ll << 31)) {
-    const int64_t a_items = (int64_t)p.KB * p.Mp * 8;
-    DFP_LAUNCH(K_WPREP, k_prep_a, dim3((unsigned)((a_items + 255) / 256)), dim3(256), 0, st, pa);
+    DFP_LAUNCH(K_WPREP, k_prep_a, dim3((unsigned)((prep_a_items(pa) + 255) / 256)), dim3(256), 0, st, pa);
     ConvMfmaArgs args{};
     args.wsa = wsa;
     args.ea = sa;
@@ -2736,22 +2698,17 @@ dfp_status launch_conv_mfma(int32_t dir, const Geom& g, const int16_t* a, const 
     else DFP_LAUNCH(kid, (k_conv1x1_s<false>), grid, dim3(k1x1fThreads), 0, st, args, a, PQ1, dpq);
     return DFP_OK;
   }
-  const int64_t a_total = (int64_t)p.KB * p.Mp * 8;
-  // the plane-layout preparation takes the filter digits in an extra slice of
-  // its grid when that slice needs at most 8 items per thread
-  const int32_t rb_plane = std::max(1, std::min(kPlaneRows, kPlaneElems / (16 * (fwd ? g.w : g.q))));
-  const int64_t slice_threads =
-      kPlaneDirect ? (int64_t)p.Hp * 256 : (int64_t)((p.Hp + rb_plane - 1) / rb_plane) * p.CG * 256;
-  const bool merge_a = plane && a_total <= 8 * slice_threads;
-  if (!merge_a) DFP_LAUNCH(K_WPREP, k_prep_a, dim3((unsigned)((a_total + 255) / 256)), dim3(256), 0, st, pa);
+  // the input's preparation takes the filter digits along in its launch
+  const int64_t a_wgs = (prep_a_items(pa) + 255) / 256;
   // few input channels (forward, L = 64, FP32 outputs): channel-last digit rows
   const int32_t cl_row_b = (p.Wp * p.Cin + 31) / 16 * 16;
   const int64_t cl_bytes = ((int64_t)g.n * p.Hp + 2) * 2 * cl_row_b;
   if (fwd && !i32 && g.L == 64 && p.Cin < 16 && g.s * p.Cin >= 16 && p.KB <= kW16MaxKB &&
       cl_bytes <= p.ws_b_bytes && cl_bytes < (1ll << 31) && (int64_t)g.n * p.Po * p.Qo * p.M < (1ll << 30)) {
     const int64_t items = (int64_t)g.n * p.Hp * ((p.Wp + 3) / 4);
-    DFP_LAUNCH(K_XPREP, k_prep_cl, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, a, xs, g.n, p.Cin, g.h,
-               g.w, p.Hp, p.Wp, g.ph, g.pw, cl_row_b);
+    const int64_t nbx = (items + 255) / 256;
+    DFP_LAUNCH(K_XPREP, k_prep_cl, dim3((unsigned)(nbx + a_wgs)), dim3(256), 0, st, a, xs, g.n, p.Cin, g.h, g.w, p.Hp,
+               p.Wp, g.ph, g.pw, cl_row_b, (int32_t)nbx, pa);
     ConvMfmaArgs args{};
     args.xs = xs;
     args.wsa = wsa;
@@ -2784,30 +2741,22 @@ dfp_status launch_conv_mfma(int32_t dir, const Geom& g, const int16_t* a, const 
     const int32_t cgc = std::max(1, std::min(p.CG, kPrepBElems / (16 * Wsrc)));  // as in the kernel
     const size_t lds = (size_t)cgc * 16 * Wsrc * 2;
     if (plane) {
-      const int32_t rb = rb_plane;
-      const dim3 grid((unsigned)((p.Hp + rb - 1) / rb), (unsigned)p.CG, (unsigned)(g.n + (merge_a ? 1 : 0)));
-      const size_t plds = (size_t)rb * Wsrc * 16 * 2;
-      const int32_t wa = merge_a ? 1 : 0;
-      const dim3 gridd((unsigned)p.Hp, (unsigned)(g.n + (merge_a ? 1 : 0)));
-      if (kPlaneDirect && p.dil_h == 1 && p.dil_w == 1 && (Wsrc % 2) == 0 &&
-          (reinterpret_cast<uintptr_t>(a) & 3) == 0 && p.left >= 0 && p.left + Wsrc <= p.Wp) {
+      const int64_t a_rows = (a_wgs + p.Hp - 1) / p.Hp;
+      const dim3 gridd((unsigned)p.Hp, (unsigned)(g.n + a_rows));
+      if (p.dil_h == 1 && p.dil_w == 1 && (Wsrc % 2) == 0 && (reinterpret_cast<uintptr_t>(a) & 3) == 0 &&
+          p.left >= 0 && p.left + Wsrc <= p.Wp) {
         DFP_LAUNCH(K_XPREP, k_prep_plane_pair, gridd, dim3(256), 0, st, a, xs, Cs, Hs, Wsrc, p.Hp, p.Wp, p.CG,
-                   p.top, p.left, pa, wa);
-      } else if (kPlaneDirect) {
+                   p.top, p.left, pa, g.n);
+      } else {
         DFP_LAUNCH(K_XPREP, k_prep_plane_direct, gridd, dim3(256), 0, st, a, xs, Cs, Hs, Wsrc, p.Hp, p.Wp, p.CG,
-                   p.top, p.left, p.dil_h, p.dil_w, pa, wa);
-      } else if (vec)
-        DFP_LAUNCH(K_XPREP, k_prep_plane<true>, grid, dim3(256), plds, st, a, xs, Cs, Hs, Wsrc, p.Hp, p.Wp, p.CG,
-                   p.top, p.left, p.dil_h, p.dil_w, rb, pa, wa);
-      else
-        DFP_LAUNCH(K_XPREP, k_prep_plane<false>, grid, dim3(256), plds, st, a, xs, Cs, Hs, Wsrc, p.Hp, p.Wp, p.CG,
-                   p.top, p.left, p.dil_h, p.dil_w, rb, pa, wa);
+                   p.top, p.left, p.dil_h, p.dil_w, pa, g.n);
+      }
     } else if (vec) {
-      DFP_LAUNCH(K_XPREP, k_prep_b<true>, dim3((unsigned)(g.n * p.Hp)), dim3(256), lds, st, a, xs, g.n, Cs, Hs, Wsrc,
-                 p.Hp, p.Wp, p.CG, p.top, p.left, p.dil_h, p.dil_w);
+      DFP_LAUNCH(K_XPREP, k_prep_b<true>, dim3((unsigned)(g.n * p.Hp + a_wgs)), dim3(256), lds, st, a, xs, g.n, Cs,
+                 Hs, Wsrc, p.Hp, p.Wp, p.CG, p.top, p.left, p.dil_h, p.dil_w, pa);
     } else {
-      DFP_LAUNCH(K_XPREP, k_prep_b<false>, dim3((unsigned)(g.n * p.Hp)), dim3(256), lds, st, a, xs, g.n, Cs, Hs, Wsrc,
-                 p.Hp, p.Wp, p.CG, p.top, p.left, p.dil_h, p.dil_w);
+      DFP_LAUNCH(K_XPREP, k_prep_b<false>, dim3((unsigned)(g.n * p.Hp + a_wgs)), dim3(256), lds, st, a, xs, g.n, Cs,
+                 Hs, Wsrc, p.Hp, p.Wp, p.CG, p.top, p.left, p.dil_h, p.dil_w, pa);
     }
   }
   ConvMfmaArgs args{};
