@@ -181,7 +181,8 @@ dfp_status dfp_conv_bwd_data(const dfp_desc* d, const int16_t* dy, const dfp_sca
  * products, Sec. 4.3): dw[k,c,r,s] = sum over (n,p,q) of dy[n,k,p,q] *
  * x[n,c,p*stride_h-pad_h+r, q*stride_w-pad_w+s].  x: INT16 [N,C,H,W];
  * dy: INT16 [N,K,P,Q]; dw: FP32 [K,C,R,S] (not quantised, Fig. 2 caption).
- * workspace: at least dfp_workspace_bytes(d, DFP_BWD_WT) bytes. */
+ * workspace: at least dfp_workspace_bytes(d, DFP_BWD_WT) bytes (optional where
+ * that function says so). */
 dfp_status dfp_conv_bwd_weights(const dfp_desc* d, const int16_t* x, const dfp_scale* sx,
                                 const int16_t* dy, const dfp_scale* sdy, float* dw, void* workspace,
                                 size_t ws_bytes, int32_t* partials, void* stream);
@@ -248,8 +249,11 @@ dfp_status dfp_downconvert_i32(const dfp_desc* d, int32_t role, const int32_t* s
                                int16_t* dst, dfp_scale* sout, int32_t amax_ready, void* stream);
 
 /* Device workspace needed by a convolution direction (bytes, 0 if none);
- * 0 also for an invalid descriptor.  At P = 16 it may be left out (NULL):
- * the call then runs on the VALU kernels. */
+ * 0 also for an invalid descriptor.  At P = 16, and for backward-weights
+ * layers whose rows are too wide for the general matrix-core kernel (the input
+ * rows that 128 output pixels touch, for the channels of 128 filter columns,
+ * take more than 64 KiB of INT16), it may be left out (NULL): the call then runs
+ * on the VALU kernels, as the latter do when recording partials. */
 size_t dfp_workspace_bytes(const dfp_desc* d, int32_t direction);
 
 /* Number of chunks J = ceil(T / L) of a direction; -1 for an invalid descriptor. */

@@ -142,7 +142,7 @@ dfp_status conv_checks(const dfp_desc* d, Geom* g, const void* a, const void* sa
 // with the VALU kernels gated behind it (launch_p16_scan).
 bool mfma_shape(const Geom& g, int32_t path, int32_t dir) {
   if (path == DFP_PATH_VALU) return false;
-  if (dir == DFP_BWD_WT) return bwdw_mfma_supported(g);
+  if (dir == DFP_BWD_WT) return bwdw_mfma_supported(g) || bwdw_mfma_wide(g);
   return conv_mfma_supported(g, dir);
 }
 bool use_mfma(const Geom& g, int32_t path, int32_t bits, int32_t dir) { return bits == 15 && mfma_shape(g, path, dir); }
@@ -172,7 +172,7 @@ bool p16_on_mfma(const Geom& g, int32_t dir, int32_t path, const void* ws, size_
 dfp_status ws_check(const Geom& g, int32_t dir, int32_t path, int32_t bits, const void* ws, size_t ws_bytes) {
   if (bits != 15) return DFP_OK;
   const size_t need = workspace_bytes(g, dir, path, bits);
-  if (need == 0) return DFP_OK;
+  if (need == 0 || (dir == DFP_BWD_WT && bwdw_mfma_wide(g))) return DFP_OK;  // (wide: optional)
   if (!ws || ws_bytes < need || !aligned(ws, 256)) return DFP_ERR_WORKSPACE;
   return DFP_OK;
 }
@@ -323,7 +323,10 @@ static dfp_status conv_common(int32_t dir, const dfp_desc* d, const int16_t* a, 
   if ((rc = ws_check(g, dir, d->path, d->bits, ws, ws_bytes)) != DFP_OK) return rc;
   if (so && !aligned(so, 16)) return DFP_ERR_ALIGN;
   hipStream_t st = (hipStream_t)stream;
-  if (use_mfma(g, d->path, d->bits, dir))
+  // wide backward-weights layers: the VALU kernel without a workspace or with partials
+  const bool valu = dir == DFP_BWD_WT && bwdw_mfma_wide(g) &&
+                    (partials || !ws || !aligned(ws, 256) || ws_bytes < workspace_bytes(g, dir, d->path, d->bits));
+  if (!valu && use_mfma(g, d->path, d->bits, dir))
     return conv_mfma(dir, g, d->path, a, sa, b, sb, out, so, ws, partials, st, false);
   if (d->bits == 16 && !partials && p16_on_mfma(g, dir, d->path, ws, ws_bytes))
     return conv_p16(dir, g, d->path, a, sa, b, sb, out, so, ws, st, false);
@@ -539,7 +542,9 @@ dfp_status dfp_conv_bwd_weights_noalloc(const dfp_desc* d, const int16_t* x, con
   dfp_status rc = conv_checks(d, &g, x, sx, dy, sdy, dw);
   if (rc != DFP_OK) return rc;
   // (P = 16 runs the VALU kernel here, which needs no scratch)
-  const bool mfma = use_mfma(g, d->path, d->bits, DFP_BWD_WT);
+  // (a wide layer whose scratch is too large runs there as well)
+  const bool mfma = use_mfma(g, d->path, d->bits, DFP_BWD_WT) &&
+                    (!bwdw_mfma_wide(g) || plan_bwdw_mfma(g).bytes <= (int64_t)DFP_NOALLOC_SCRATCH_BYTES);
   // a layer whose ring-kernel scratch is too large runs the kernels without it
   const bool ring = mfma && plan_bwdw_mfma(g).bytes <= (int64_t)DFP_NOALLOC_SCRATCH_BYTES;
   if (mfma && plan_bwdw_mfma(g, ring).bytes > (int64_t)DFP_NOALLOC_SCRATCH_BYTES) return DFP_ERR_SCRATCH_LIMIT;

@@ -37,7 +37,11 @@ struct BwdwArgs {
 
 // ring: whether the ring kernel, whose workspace may be larger, may be used.
 BwdwPlan plan_bwdw_mfma(const Geom& g, bool ring = true);
+// Layers that any call with the plan's workspace can take to the matrix cores.
 bool bwdw_mfma_supported(const Geom& g);
+// Others that calls without partials can: rows too wide for the general kernel's
+// LDS band, on kernels that stage no such band (1x1 layers, the ring kernel).
+bool bwdw_mfma_wide(const Geom& g);
 dfp_status launch_bwdw_mfma(const Geom& g, const int16_t* x, const dfp_scale* sx, const int16_t* dy,
                             const dfp_scale* sdy, float* dw, int32_t* partials, void* ws, hipStream_t st,
                             bool ring = true);

@@ -2700,6 +2700,19 @@ bool bwdw_mfma_supported(const Geom& g) {
   return p.smem_bytes <= 64 * 1024;
 }
 
+// 1x1 layers whose operands are prepared (or read) without a band of rows; the
+// digit preparation indexes elements with 32 bits.
+static bool direct_1x1(const Geom& g) {
+  return unit_1x1(g) && (g.L % 32) == 0 && (int64_t)g.n * std::max(g.c, g.k) * g.p * g.q < (1ll << 31);
+}
+
+// (N = 8, 280 -> 40 channels on 63 x 63, 1x1, L = 16: 9.1 ms on the VALU kernel,
+// 0.10 ms on the ring kernel)
+bool bwdw_mfma_wide(const Geom& g) {
+  if (strided_1x1(g)) return bwdw_mfma_wide(subsampled(g));
+  return !bwdw_mfma_supported(g) && (direct_1x1(g) || ring_wanted(g));
+}
+
 dfp_status launch_bwdw_mfma(const Geom& g, const int16_t* x, const dfp_scale* sx, const int16_t* dy,
                             const dfp_scale* sdy, float* dw, int32_t* partials, void* ws, hipStream_t st, bool ring) {
   if (strided_1x1(g)) {
@@ -2720,9 +2733,8 @@ dfp_status launch_bwdw_mfma(const Geom& g, const int16_t* x, const dfp_scale* sx
   float* useg = reinterpret_cast<float*>(base + p.ad_bytes + p.xp_bytes);
   const DyPrep dq{dy, ad, g.k, p.Mp, g.p * g.q, (int32_t)p.T, (int32_t)p.KBT};
   const int64_t dy_blocks = (p.KBT * p.Mp * 2 + 255) / 256;
-  // unit-stride 1x1 without partials: both operands as digit blocks (the
-  // digit preparation indexes elements with 32 bits)
-  if (unit_1x1(g) && !partials && (g.L % 32) == 0 && (int64_t)g.n * std::max(g.c, g.k) * g.p * g.q < (1ll << 31)) {
+  // unit-stride 1x1 without partials: both operands as digit blocks
+  if (!partials && direct_1x1(g)) {
     const int32_t Cp = (g.c + 63) / 64 * 64;
     uint8_t* bd = reinterpret_cast<uint8_t*>(xp);
     const int32_t PQ = g.p * g.q;
@@ -2830,7 +2842,8 @@ dfp_status launch_bwdw_mfma(const Geom& g, const int16_t* x, const dfp_scale* sx
                        : bl.run == 8 ? (l64 ? (partials ? safe.skew_t : (safe.w8 || safe.skew_f))
                                             : (partials ? safe.band_t : safe.band_f))
                                      : (l64 && !partials && safe.w8_r4);
-  if (to_ring && (g.L < 64 || !band_ok || bl.buf_bytes == 0)) return launch_ring(g, p, ring_layout(g), x, sx, dy, sdy, dw, ws, st);
+  if (to_ring && (g.L < 64 || !band_ok || bl.buf_bytes == 0 || p.smem_bytes > 64 * 1024))
+    return launch_ring(g, p, ring_layout(g), x, sx, dy, sdy, dw, ws, st);
   if (band_ok && bl.buf_bytes > 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0 && p.ad_bytes < (1ll << 31) &&
       p.xp_bytes < (1ll << 31)) {
     uint8_t* xb = reinterpret_cast<uint8_t*>(xp);  // same workspace region as the pair layout
