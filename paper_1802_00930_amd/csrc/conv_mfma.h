@@ -10,6 +10,7 @@ struct ConvMfmaPlan {
   int32_t M, Mp, Cin, T, KB, CG;   // output channels (padded), reduction channels, T, 32-blocks, 16-groups
   int32_t Hp, Wp, top, left, dil_h, dil_w;  // channels-last digit tensor geometry
   int32_t Po, Qo;                  // output spatial size
+  int32_t Tu;                      // unfolded operand: T rounded up to 64, or 0 where the layer does not take it
   int64_t ws_a_bytes, ws_b_bytes, ws_t_bytes, bytes;
 };
 

@@ -103,9 +103,10 @@ __device__ __forceinline__ void prep_a_piece(const PrepAArgs& a, int32_t idx) {
   const int32_t CG = a.Cin >> 4, RS = a.R * a.S, full = a.Mp * CG * RS;
   int32_t m, piece;  // piece: 16-index half-block of the row
   uint32_t hi[4] = {0u, 0u, 0u, 0u}, lo[4] = {0u, 0u, 0u, 0u};
-  if (idx >= full) {  // T an odd number of half-blocks: the last one is zero
-    m = idx - full;
-    piece = 2 * a.KB - 1;
+  if (idx >= full) {  // zero half-blocks past T
+    piece = (idx - full) / a.Mp;
+    m = idx - full - piece * a.Mp;
+    piece += CG * RS;
   } else {
     const int32_t rest = idx / RS, tap = idx - rest * RS;
     const int32_t q = rest / (a.transposed ? a.Mp : CG), rm = rest - q * (a.transposed ? a.Mp : CG);
@@ -2529,6 +2530,77 @@ __global__ __launch_bounds__(k1x1fThreads, 4) void k_conv1x1_s(ConvMfmaArgs a, c
   }
 }
 
+// Unfolded operand for layers whose channel count the plane layout does not
+// take: the plane layout of the 1x1 convolution over the Po x Qo output grid
+// whose "channels" are the reduction indices t = (r*S + s)*Cin + ci themselves,
+// zeros from T to Tu, so that the chunks stay those of t and the four-waves-
+// per-SIMD kernels apply.  A thread gathers the 16 indices of group cg at output
+// column v (consecutive lanes read along a source row), workgroup (u, n) one
+// output row; rows of workgroups past the images prepare the filter digits.
+// The operand is R S times the input, which costs far less than the general
+// kernel's gathers, call times before and now: 88 -> 96 channels 3x3 on 28 x 28,
+// N = 16, forward 136 -> 35 us; 136 -> 152 on 14 x 14 200 -> 27 and backward-data
+// 227 -> 28; 24 -> 40 on 56 x 56, N = 32, 126 -> 40 and 182 -> 51; 1000 -> 264 on
+// 10 x 10, N = 4, 1366 -> 211.  (Calls with partials and single-chunk INT32
+// outputs keep the general kernels.)
+struct UnfoldArgs {
+  const int16_t* src;
+  uint8_t* xs;
+  int32_t N, Cs, Hs, Ws, Cin, S, T, Tu, Po, Qo, sh, sw, ph, pw, bwd;
+};
+__global__ __launch_bounds__(256) void k_prep_unfold(UnfoldArgs f, PrepAArgs pa) {
+  const int32_t n = blockIdx.y, u = blockIdx.x;
+  if (n >= f.N) {
+    prep_a_item(pa, ((n - f.N) * (int32_t)gridDim.x + u) * 256 + (int32_t)threadIdx.x);
+    return;
+  }
+  const int32_t G = f.Tu >> 4;
+  const int64_t plane = (int64_t)f.Hs * f.Ws;
+  const int16_t* img = f.src + (int64_t)n * f.Cs * plane;
+  uint4* rowp = reinterpret_cast<uint4*>(f.xs + ((int64_t)n * f.Po + u) * ((int64_t)f.Tu * 2 * f.Qo));
+  for (int32_t j = threadIdx.x; j < G * f.Qo; j += 256) {
+    const int32_t cg = j / f.Qo, v = j - cg * f.Qo;
+    int32_t t = cg * 16, tap = t / f.Cin, ci = t - tap * f.Cin, r = tap / f.S, s = tap - r * f.S;
+    // source element of tap (r, s), or none
+    int32_t off = 0;
+    bool in = false;
+    auto locate = [&]() __attribute__((always_inline)) {
+      if (f.bwd) {
+        const int32_t hh = u + f.ph - r, ww = v + f.pw - s, h = hh / f.sh, w = ww / f.sw;
+        in = hh >= 0 && ww >= 0 && h * f.sh == hh && w * f.sw == ww && h < f.Hs && w < f.Ws;
+        off = h * f.Ws + w;
+      } else {
+        const int32_t h = u * f.sh - f.ph + r, w = v * f.sw - f.pw + s;
+        in = h >= 0 && w >= 0 && h < f.Hs && w < f.Ws;
+        off = h * f.Ws + w;
+      }
+    };
+    locate();
+    int32_t a[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      a[k] = in && t + k < f.T ? (int32_t)img[ci * plane + off] : 0;
+      if (++ci == f.Cin) {
+        ci = 0;
+        if (++s == f.S) {
+          s = 0;
+          ++r;
+        }
+        locate();
+      }
+    }
+    uint32_t hi[4] = {0u, 0u, 0u, 0u}, lo[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      hi[k >> 2] |= hi_digit(a[k]) << (8 * (k & 3));
+      lo[k >> 2] |= lo_digit(a[k]) << (8 * (k & 3));
+    }
+    uint4* d = rowp + ((cg >> 1) * 4 + (cg & 1)) * f.Qo + v;
+    d[0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    d[2 * f.Qo] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+  }
+}
+
 // XC[n][hp][d][row_b] for k_conv_mfma_cl: byte wp C + c of digit row d (0 hi,
 // 1 lo) holds that digit of x[n][c][hp - ph][wp - pw] (zero outside the
 // image); thread (n, hp, group of four columns).  Bytes past Wp C stay unset
@@ -2631,9 +2703,16 @@ ConvMfmaPlan plan_conv_mfma(const Geom& g, int32_t dir) {
     p.dil_w = g.sw;
     p.Po = g.h; p.Qo = g.w;
   }
-  p.ws_a_bytes = align256((int64_t)p.KB * p.Mp * 2 * 32);
-  p.ws_b_bytes = align256((int64_t)g.n * p.Hp * p.Wp * p.CG * 32);
-  p.ws_t_bytes = align256((int64_t)p.KB * 8);
+  // the unfolded operand: channel counts off the plane layout, at most 1 GiB of it
+  p.Tu = (p.T + 63) / 64 * 64;
+  if (conv_w16_eligible(p.Cin, p.T, g.L, false) || !conv_w16_eligible(p.Tu, p.Tu, g.L, false) ||
+      !(p.Cin % 16 != 0 || g.L < 32) || (int64_t)g.n * p.Po * p.Qo * p.Tu * 2 > ((int64_t)1 << 30) ||
+      (int64_t)g.n * p.Po * p.Qo * p.M >= ((int64_t)1 << 31) || (int64_t)p.Mp * p.Tu >= ((int64_t)1 << 30))
+    p.Tu = 0;
+  const int32_t KB = std::max(p.KB, p.Tu / 32);
+  p.ws_a_bytes = align256((int64_t)KB * p.Mp * 2 * 32);
+  p.ws_b_bytes = align256(std::max((int64_t)g.n * p.Hp * p.Wp * p.CG * 32, (int64_t)g.n * p.Po * p.Qo * p.Tu * 2));
+  p.ws_t_bytes = align256((int64_t)KB * 8);
   p.bytes = p.ws_a_bytes + p.ws_b_bytes + p.ws_t_bytes;
   return p;
 }
@@ -2734,6 +2813,30 @@ dfp_status launch_conv_mfma(int32_t dir, const Geom& g, const int16_t* a, const 
     if (partials) DFP_LAUNCH(K_FWD_MFMA, (k_conv_mfma_cl<true>), grid, dim3(kThreads16), 0, st, args, cla);
     else DFP_LAUNCH(K_FWD_MFMA, (k_conv_mfma_cl<false>), grid, dim3(kThreads16), 0, st, args, cla);
     return DFP_OK;
+  }
+  if (p.Tu > 0 && !i32 && !partials) {
+    PrepAArgs pu = pa;
+    pu.KB = p.Tu / 32;
+    const UnfoldArgs f{a, xs, g.n, p.Cin, fwd ? g.h : g.p, fwd ? g.w : g.q, p.Cin, g.s, p.T, p.Tu, p.Po, p.Qo,
+                       g.sh, g.sw, g.ph, g.pw, fwd ? 0 : 1};
+    const int64_t a_rows = ((prep_a_items(pu) + 255) / 256 + p.Po - 1) / p.Po;
+    DFP_LAUNCH(K_XPREP, k_prep_unfold, dim3((unsigned)p.Po, (unsigned)(g.n + a_rows)), dim3(256), 0, st, f, pu);
+    ConvMfmaArgs args{};
+    args.xs = xs;
+    args.wsa = wsa;
+    args.boff = boff;
+    args.ea = sa;
+    args.eb = sb;
+    args.out = out;
+    args.so = so;
+    args.M = p.M; args.Mp = p.Mp; args.Cin = p.Tu; args.S = 1; args.T = p.Tu; args.KB = p.Tu / 32; args.L = g.L;
+    args.CG = p.Tu / 16; args.Hp = p.Po; args.Wp = p.Qo; args.Po = p.Po; args.Qo = p.Qo;
+    args.NP = (int64_t)g.n * p.Po * p.Qo;
+    args.O = args.NP * p.M;
+    args.plane = 1;
+    args.ustride_h = args.ustride_w = 1;
+    args.rsign = 1;
+    return launch_mfma_main(args, p.ws_b_bytes, fwd ? K_FWD_MFMA : K_BWDD_MFMA, fwd ? K_FWD_I32 : K_BWDD_I32, false, st);
   }
   {
     const int32_t Cs = fwd ? g.c : g.k, Hs = fwd ? g.h : g.p, Wsrc = fwd ? g.w : g.q;
