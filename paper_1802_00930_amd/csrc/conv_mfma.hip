@@ -184,6 +184,18 @@ __device__ __forceinline__ void prep_a_item(const PrepAArgs& a, int32_t idx) {
   dst[4] = lo;
 }
 
+// The filter digits from `rows` rows of gridDim.x workgroups: one item per thread,
+// more where the grid's limit cuts the rows.
+__device__ __forceinline__ void prep_a_rows(const PrepAArgs& a, int32_t row, int32_t rows, int32_t u) {
+  const int64_t nthr = (int64_t)rows * gridDim.x * 256, total = prep_a_items(a);
+  for (int64_t i = ((int64_t)row * gridDim.x + u) * 256 + threadIdx.x; i < total; i += nthr)
+    prep_a_item(a, (int32_t)i);
+}
+static int64_t prep_a_grid_rows(const PrepAArgs& a, int32_t gx, int32_t images) {
+  const int64_t wgs = ((int64_t)prep_a_items(a) + 255) / 256;
+  return std::max<int64_t>(1, std::min<int64_t>((wgs + gx - 1) / gx, 65535 - images));
+}
+
 __global__ __launch_bounds__(256) void k_prep_a(PrepAArgs a) { prep_a_item(a, blockIdx.x * 256 + threadIdx.x); }
 
 // ---------------------------------------------------------------- B prep
@@ -290,7 +302,7 @@ __global__ __launch_bounds__(256) void k_prep_plane_direct(const int16_t* __rest
   const int32_t l = xcd * per + min(xcd, rem) + (id >> 3);
   const int32_t n = l / (int32_t)gridDim.x, u = l - n * (int32_t)gridDim.x;
   if (n >= N) {
-    prep_a_item(pa, ((n - N) * (int32_t)gridDim.x + u) * 256 + (int32_t)threadIdx.x);
+    prep_a_rows(pa, n - N, (int32_t)gridDim.y - N, u);
     return;
   }
   const int32_t zu = u - top;
@@ -334,7 +346,7 @@ __global__ __launch_bounds__(256) void k_prep_plane_pair(const int16_t* __restri
   const int32_t l = xcd * per_x + min(xcd, rem) + (id >> 3);
   const int32_t n = l / (int32_t)gridDim.x, u = l - n * (int32_t)gridDim.x;
   if (n >= N) {
-    prep_a_item(pa, ((n - N) * (int32_t)gridDim.x + u) * 256 + (int32_t)threadIdx.x);
+    prep_a_rows(pa, n - N, (int32_t)gridDim.y - N, u);
     return;
   }
   const int32_t h = u - top;
@@ -2551,7 +2563,7 @@ struct UnfoldArgs {
 __global__ __launch_bounds__(256) void k_prep_unfold(UnfoldArgs f, PrepAArgs pa) {
   const int32_t n = blockIdx.y, u = blockIdx.x;
   if (n >= f.N) {
-    prep_a_item(pa, ((n - f.N) * (int32_t)gridDim.x + u) * 256 + (int32_t)threadIdx.x);
+    prep_a_rows(pa, n - f.N, (int32_t)gridDim.y - f.N, u);
     return;
   }
   const int32_t G = f.Tu >> 4;
@@ -2711,7 +2723,7 @@ ConvMfmaPlan plan_conv_mfma(const Geom& g, int32_t dir) {
   // the masked kernel.
   p.Tu = (p.T + 63) / 64 * 64;
   if (conv_w16_eligible(p.Cin, p.T, g.L, false) || !conv_w16_eligible(p.Tu, p.Tu, g.L, false) ||
-      !(p.Cin % 16 != 0 || g.L < 32) || (int64_t)g.n * p.Po * p.Qo * p.Tu * 2 > ((int64_t)1 << 30) ||
+      !(p.Cin % 16 != 0 || g.L < 32) || g.n >= 65535 || (int64_t)g.n * p.Po * p.Qo * p.Tu * 2 > ((int64_t)1 << 30) ||
       (int64_t)g.n * p.Po * p.Qo * p.M >= ((int64_t)1 << 31) || (int64_t)p.Mp * p.Tu >= ((int64_t)1 << 30))
     p.Tu = 0;
   const int32_t KB = std::max(p.KB, p.Tu / 32);
@@ -2824,7 +2836,7 @@ dfp_status launch_conv_mfma(int32_t dir, const Geom& g, const int16_t* a, const 
     pu.KB = p.Tu / 32;
     const UnfoldArgs f{a, xs, g.n, p.Cin, fwd ? g.h : g.p, fwd ? g.w : g.q, p.Cin, g.s, p.T, p.Tu, p.Po, p.Qo,
                        g.sh, g.sw, g.ph, g.pw, fwd ? 0 : 1};
-    const int64_t a_rows = ((prep_a_items(pu) + 255) / 256 + p.Po - 1) / p.Po;
+    const int64_t a_rows = prep_a_grid_rows(pu, p.Po, g.n);
     DFP_LAUNCH(K_XPREP, k_prep_unfold, dim3((unsigned)p.Po, (unsigned)(g.n + a_rows)), dim3(256), 0, st, f, pu);
     ConvMfmaArgs args{};
     args.xs = xs;
@@ -2849,7 +2861,7 @@ dfp_status launch_conv_mfma(int32_t dir, const Geom& g, const int16_t* a, const 
     const int32_t cgc = std::max(1, std::min(p.CG, kPrepBElems / (16 * Wsrc)));  // as in the kernel
     const size_t lds = (size_t)cgc * 16 * Wsrc * 2;
     if (plane) {
-      const int64_t a_rows = (a_wgs + p.Hp - 1) / p.Hp;
+      const int64_t a_rows = prep_a_grid_rows(pa, p.Hp, g.n);
       const dim3 gridd((unsigned)p.Hp, (unsigned)(g.n + a_rows));
       if (p.dil_h == 1 && p.dil_w == 1 && (Wsrc % 2) == 0 && (reinterpret_cast<uintptr_t>(a) & 3) == 0 &&
           p.left >= 0 && p.left + Wsrc <= p.Wp) {

@@ -32,3 +32,17 @@ def test_unfold(n, c, h, w, k, r, s, st, pd, L, direction):
     torch.cuda.synchronize()
     assert ulp_diff(out.cpu().numpy(), ref) == 0
     assert dfp.read_scale(so)["amax_bits"] == int((np.abs(ref).astype(np.float32).view(np.uint32)).max())
+
+
+def test_unfold_large_filter():
+    """More filter items than one row of workgroups per grid row can take."""
+    gl = GpuLayer(1, 8191, 1, 1, 8256, 1, 1, 1, 0, L=64)
+    rng = np.random.default_rng(3)
+    x = rng.integers(-16384, 16385, gl.shape_x).astype(np.int16)
+    wt = rng.integers(-16384, 16385, gl.shape_w, dtype=np.int16)
+    sc = torch.tensor([0, -12, 0, 0], dtype=torch.int32, device=DEV)
+    note("unfold large filter")
+    out, _, _ = gl.conv(dfp.FWD, to_dev(x), sc, to_dev(wt), sc)
+    ref, _, _ = oracle.conv(oracle_geom(gl), dfp.FWD, x, wt, -24, 64)
+    torch.cuda.synchronize()
+    assert ulp_diff(out.cpu().numpy(), ref) == 0
