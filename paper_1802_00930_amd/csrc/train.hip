@@ -66,9 +66,17 @@ __device__ __forceinline__ int32_t hi16(uint32_t w) { return (int32_t)w >> 16; }
 
 // The backward ReLU mask is a byte per group of four elements (bit q: element q
 // passes) in the INT16 output buffer, at the start of the 512 bytes that the
-// 64 groups' own results fill: the wave that rounds these groups has read the
-// 64 bytes before it stores.
+// 64 groups' own results fill.  The rounding pass therefore takes these 64
+// groups with one wave at a time, all of whose lanes load before any stores
+// (mask_barrier, and loops whose bounds are the same for the whole wave).
 __device__ __forceinline__ int64_t mask_at(int32_t group) { return (int64_t)(group >> 6) * 512 + (group & 63); }
+// Between a wave's mask loads and its first store (no instruction of its own):
+// neither the compiler nor a lane moves a memory access across it.
+__device__ __forceinline__ void mask_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
 
 // ------------------------------------------------------------ statistics
 // Workgroup (s, c) reduces channel c over images [N s / S, N (s+1) / S).
@@ -486,13 +494,25 @@ __global__ __launch_bounds__(kBlock) void k_bn_convert(Elems e, float* __restric
     }
     if (!BWD && z) store_group(z, base, e.total, v);
   };
+  // Bounds on the wave's first group: a bound per lane would split a wave where
+  // the number of groups is not a multiple of 64, and its first lanes would store
+  // over mask bytes that the others load afterwards.  (first < groups - stride:
+  // every lane of the wave has a first group, since stride is a multiple of 64.)
   int32_t gi = blockIdx.x * kBlock + threadIdx.x;
-  for (; gi < groups - stride; gi += 2 * stride) {
-    const Group a = load_group<BWD, HW4, SRC>(e, gi), b = load_group<BWD, HW4, SRC>(e, gi + stride);
+  int32_t first = __builtin_amdgcn_readfirstlane(gi);
+  for (; first < groups - stride; gi += 2 * stride, first += 2 * stride) {
+    const bool two = gi + stride < groups;
+    const Group a = load_group<BWD, HW4, SRC>(e, gi);
+    Group b{};
+    if (two) b = load_group<BWD, HW4, SRC>(e, gi + stride);
+    if (SRC == kMask) mask_barrier();
     use(a, gi);
-    use(b, gi + stride);
+    if (two) use(b, gi + stride);
   }
-  if (gi < groups) use(load_group<BWD, HW4, SRC>(e, gi), gi);
+  Group a{};
+  if (gi < groups) a = load_group<BWD, HW4, SRC>(e, gi);
+  if (SRC == kMask) mask_barrier();
+  if (gi < groups) use(a, gi);
   if (SAT && saturated) atomicOr(&s->flags, DFP_FLAG_SATURATED);
 }
 
