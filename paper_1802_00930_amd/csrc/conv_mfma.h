@@ -12,6 +12,7 @@ struct ConvMfmaPlan {
   int32_t Po, Qo;                  // output spatial size
   int32_t Tu;                      // unfolded operand: T rounded up to 64, or 0 where the layer does not take it
   int64_t ws_a_bytes, ws_b_bytes, ws_t_bytes, bytes;
+  int64_t unfold_bytes;            // size of the unfolded operand, at the start of ws_b
 };
 
 struct ConvMfmaArgs {

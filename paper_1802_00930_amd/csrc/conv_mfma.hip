@@ -2724,11 +2724,13 @@ ConvMfmaPlan plan_conv_mfma(const Geom& g, int32_t dir) {
   p.Tu = (p.T + 63) / 64 * 64;
   if (conv_w16_eligible(p.Cin, p.T, g.L, false) || !conv_w16_eligible(p.Tu, p.Tu, g.L, false) ||
       !(p.Cin % 16 != 0 || g.L < 32) || g.n >= 65535 || (int64_t)g.n * p.Po * p.Qo * p.Tu * 2 > ((int64_t)1 << 30) ||
-      (int64_t)g.n * p.Po * p.Qo * p.M >= ((int64_t)1 << 31) || (int64_t)p.Mp * p.Tu >= ((int64_t)1 << 30))
+      (int64_t)g.n * p.Po * p.Qo * p.M >= ((int64_t)1 << 31) || (int64_t)p.Mp * p.Tu >= ((int64_t)1 << 30) ||
+      (int64_t)(fwd ? g.h : g.p) * (fwd ? g.w : g.q) >= ((int64_t)1 << 31))  // (an offset in a source plane: 32 bits)
     p.Tu = 0;
   const int32_t KB = std::max(p.KB, p.Tu / 32);
   p.ws_a_bytes = align256((int64_t)KB * p.Mp * 2 * 32);
-  p.ws_b_bytes = align256(std::max((int64_t)g.n * p.Hp * p.Wp * p.CG * 32, (int64_t)g.n * p.Po * p.Qo * p.Tu * 2));
+  p.unfold_bytes = (int64_t)g.n * p.Po * p.Qo * p.Tu * 2;
+  p.ws_b_bytes = align256(std::max((int64_t)g.n * p.Hp * p.Wp * p.CG * 32, p.unfold_bytes));
   p.ws_t_bytes = align256((int64_t)KB * 8);
   p.bytes = p.ws_a_bytes + p.ws_b_bytes + p.ws_t_bytes;
   return p;
@@ -2853,7 +2855,9 @@ dfp_status launch_conv_mfma(int32_t dir, const Geom& g, const int16_t* a, const 
     args.plane = 1;
     args.ustride_h = args.ustride_w = 1;
     args.rsign = 1;
-    return launch_mfma_main(args, p.ws_b_bytes, fwd ? K_FWD_MFMA : K_BWDD_MFMA, fwd ? K_FWD_I32 : K_BWDD_I32, false, st);
+    // (the operand's own size: the plain layout, for which the workspace has room too, may be 2 GiB or more)
+    return launch_mfma_main(args, p.unfold_bytes, fwd ? K_FWD_MFMA : K_BWDD_MFMA, fwd ? K_FWD_I32 : K_BWDD_I32, false,
+                            st);
   }
   {
     const int32_t Cs = fwd ? g.c : g.k, Hs = fwd ? g.h : g.p, Wsrc = fwd ? g.w : g.q;
