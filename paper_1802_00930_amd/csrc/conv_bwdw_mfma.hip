@@ -505,14 +505,17 @@ __device__ __forceinline__ int swz(int row, int piece) { return row * 4 + (piece
 // on 14 x 14, N = 64, 64 -> 41 us (L = 32: 70 -> 52); 256 -> 64 on 56 x 56 and
 // 512 -> 128 on 28 x 28, N = 32, 57 -> 33 us.
 // A piece lies in one image (P*Q a multiple of PIECE).  The loads are buffer
-// loads from offsets kept per lane and operand, the row step of the thread's
-// pieces in the scalar offset; indices past T take an offset past the end of
-// the tensor, which reads zeros (both tensors below 2 GiB: checked by the
-// launcher).  Rows past K or C read zeros or another image's elements, which
-// reach only outputs that are not stored; bands past the segment are not
-// multiplied.  KS: indices per matrix instruction, 64 where L is a multiple of
-// 64, else 32; ONE: L == KS, a chunk is one step.  Chunks, segments and output
-// as in k_bwdw_1x1.
+// loads from offsets kept per lane and operand; rows past K or C and indices
+// past T take an offset past the end of the tensor, which reads zeros (both
+// tensors below 2 GiB: checked by the launcher).  EDGE: K or C is not a multiple
+// of the tile's 64 rows.  The row step of the thread's pieces is then part of
+// the vector offset, since the range check is not documented to count the
+// scalar one; otherwise every row is inside, the step is the scalar offset, and
+// an index past T is refused whether that counts or not (1024 -> 256 on 14 x 14,
+// N = 64, layer pass 168.3 us so, 173.4 with the row tests).  Bands past the
+// segment are not multiplied.  KS: indices per matrix instruction, 64 where L is
+// a multiple of 64, else 32; ONE: L == KS, a chunk is one step.  Chunks, segments
+// and output as in k_bwdw_1x1.
 // Raw buffer resource over [p, p + bytes) (offsets past the end read zeros).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
@@ -521,7 +524,7 @@ template <int N>
 using IC = std::integral_constant<int, N>;
 constexpr int k1x1sThreads = 512;
 constexpr int k1x1Depth = 2;  // bands of loads in flight
-template <int PIECE, int KS, bool ONE>
+template <int PIECE, int KS, bool ONE, bool EDGE>
 __global__ __launch_bounds__(k1x1sThreads, 4) void k_bwdw_1x1s(BwdwArgs a, Raw1x1 raw) {
   constexpr int kLoads = 64 * 64 / PIECE / k1x1sThreads;  // pieces per thread and operand per band
   constexpr int kPerRow = 64 / PIECE;                     // pieces per row and band
@@ -557,12 +560,20 @@ __global__ __launch_bounds__(k1x1sThreads, 4) void k_bwdw_1x1s(BwdwArgs a, Raw1x
   const uint32_t sa = ((uint32_t)(dn * a.K) * (uint32_t)PQ + (uint32_t)dpq) * 2u;
   const uint32_t sb = ((uint32_t)(dn * a.C) * (uint32_t)PQ + (uint32_t)dpq) * 2u;
   const uint32_t wa = (uint32_t)(a.K - 1) * (uint32_t)PQ * 2u, wb = (uint32_t)(a.C - 1) * (uint32_t)PQ * 2u;
+  bool ina[kLoads], inb[kLoads];  // whether the row of piece j lies below K (C)
+#pragma unroll
+  for (int j = 0; j < kLoads; ++j) {
+    ina[j] = !EDGE || rA0 + j * (k1x1sThreads / kPerRow) + row0 < a.K;
+    inb[j] = !EDGE || rB0 + j * (k1x1sThreads / kPerRow) + row0 < a.C;
+  }
   auto load_band = [&](int set) __attribute__((always_inline)) {
     const bool tin = t < (int32_t)a.T;
-    const uint32_t va = tin ? oa : kOut, vb = tin ? ob : kOut;
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) {
-      const uint32_t so = __builtin_amdgcn_readfirstlane((uint32_t)j * jstep);
+      const uint32_t step = (uint32_t)j * jstep, vstep = EDGE ? step : 0u;
+      const uint32_t so = EDGE ? 0u : __builtin_amdgcn_readfirstlane(step);
+      const uint32_t va = tin && ina[j] ? oa + vstep : kOut;
+      const uint32_t vb = tin && inb[j] ? ob + vstep : kOut;
       if constexpr (PIECE == 8) {
         ra[set][j] = __builtin_bit_cast(vraw, __builtin_amdgcn_raw_buffer_load_b128(rs_dy, va, so, 0));
         rb[set][j] = __builtin_bit_cast(vraw, __builtin_amdgcn_raw_buffer_load_b128(rs_x, vb, so, 0));
@@ -2763,8 +2774,12 @@ dfp_status launch_bwdw_mfma(const Geom& g, const int16_t* x, const dfp_scale* sx
     args.nty = p.Mp / 64;
     const dim3 grid1((unsigned)(p.nseg * args.ntx * args.nty));
     args.div_q = make_fastdiv((uint32_t)PQ);  // the direct kernels: image of an index
-#define DFP_1X1S(P, KS, ONE) \
-  DFP_LAUNCH(K_BWDW_MFMA, (k_bwdw_1x1s<P, KS, ONE>), grid1, dim3(k1x1sThreads), 0, st, args, raw)
+    const bool edge = g.k % 64 != 0 || g.c % 64 != 0;
+#define DFP_1X1S(P, KS, ONE)                                                                                          \
+  do {                                                                                                                \
+    if (edge) DFP_LAUNCH(K_BWDW_MFMA, (k_bwdw_1x1s<P, KS, ONE, true>), grid1, dim3(k1x1sThreads), 0, st, args, raw);  \
+    else DFP_LAUNCH(K_BWDW_MFMA, (k_bwdw_1x1s<P, KS, ONE, false>), grid1, dim3(k1x1sThreads), 0, st, args, raw);      \
+  } while (0)
 #define DFP_1X1S_L(P)                               \
   do {                                              \
     if (g.L == 64) DFP_1X1S(P, 64, true);           \

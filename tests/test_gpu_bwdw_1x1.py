@@ -23,6 +23,8 @@ SHAPES = [
     (2, 130, 14, 14, 63, 1),
     (2, 64, 16, 18, 96, 1),    # pieces of 8
     (2, 24, 16, 16, 40, 2),
+    (5, 64, 6, 6, 64, 1),      # whole tiles, the last band cut
+    (3, 64, 8, 9, 128, 1),     # whole tiles, pieces of 8
 ]
 
 
