@@ -137,44 +137,45 @@ dfp_status conv_checks(const dfp_desc* d, Geom* g, const void* a, const void* sa
   return DFP_OK;
 }
 
+// What a convolution call runs on, worked out once per call.
 // The byte-digit split is exact for integers in [-32768, 32639], which holds
 // for every DFP15 tensor; 16-bit tensors reach 32767 and take the MFMA path
 // with the VALU kernels gated behind it (launch_p16_scan).
-bool mfma_shape(const Geom& g, int32_t path, int32_t dir) {
-  if (path == DFP_PATH_VALU) return false;
-  if (dir == DFP_BWD_WT) return bwdw_mfma_supported(g) || bwdw_mfma_wide(g);
-  return conv_mfma_supported(g, dir);
+struct Route {
+  bool mfma;         // the matrix cores can take the layer at all
+  bool optional_ws;  // but a call without (enough) workspace runs on the VALU
+  int64_t mfma_bytes;  // workspace of the MFMA path; at P = 16 the gate's words follow it
+  size_t ws_bytes;     // workspace in all (dfp_workspace_bytes)
+  BwdwPlan wt;         // backward-weights
+};
+
+Route route_of(const Geom& g, int32_t dir, int32_t path, int32_t bits) {
+  Route r{};
+  if (path == DFP_PATH_VALU) return r;
+  if (dir == DFP_BWD_WT) {
+    r.wt = plan_bwdw_mfma(g);
+    r.mfma = r.wt.fits || r.wt.wide;
+    r.optional_ws = r.wt.wide;
+    r.mfma_bytes = r.wt.bytes;
+  } else {
+    r.mfma = conv_mfma_supported(g, dir);
+    if (r.mfma) r.mfma_bytes = plan_conv_mfma(g, dir).bytes;
+    if (r.mfma && dir == DFP_BWD_DATA)  // room for either route (partials take the general one)
+      r.mfma_bytes = std::max(r.mfma_bytes, std::max(conv_bwd_data_sub_bytes(g), conv_bwd_data_phase_bytes(g)));
+  }
+  if (!r.mfma) return Route{};
+  r.optional_ws |= bits != 15;
+  r.ws_bytes = (size_t)(bits == 15 ? r.mfma_bytes : (r.mfma_bytes + 255) / 256 * 256 + kP16GateBytes);
+  return r;
 }
-bool use_mfma(const Geom& g, int32_t path, int32_t bits, int32_t dir) { return bits == 15 && mfma_shape(g, path, dir); }
 
-size_t mfma_workspace_bytes(const Geom& g, int32_t dir) {
-  if (dir == DFP_BWD_DATA)  // room for either route (partials take the general one)
-    return (size_t)std::max(std::max<int64_t>(plan_conv_mfma(g, dir).bytes, conv_bwd_data_sub_bytes(g)),
-                            conv_bwd_data_phase_bytes(g));
-  if (dir == DFP_FWD) return (size_t)plan_conv_mfma(g, dir).bytes;
-  return (size_t)plan_bwdw_mfma(g).bytes;
+bool ws_holds(const Route& r, const void* ws, size_t ws_bytes) {
+  return ws && aligned(ws, 256) && ws_bytes >= r.ws_bytes;
 }
 
-// At P = 16 the gate's words follow the MFMA path's workspace.
-size_t p16_gate_offset(const Geom& g, int32_t dir) { return (mfma_workspace_bytes(g, dir) + 255) / 256 * 256; }
-
-size_t workspace_bytes(const Geom& g, int32_t dir, int32_t path, int32_t bits) {
-  if (!mfma_shape(g, path, dir)) return 0;
-  return bits == 15 ? mfma_workspace_bytes(g, dir) : p16_gate_offset(g, dir) + kP16GateBytes;
-}
-
-// P = 16 needs no workspace (the VALU kernels then run alone), but with one of
-// workspace_bytes it takes the matrix cores.
-bool p16_on_mfma(const Geom& g, int32_t dir, int32_t path, const void* ws, size_t ws_bytes) {
-  return mfma_shape(g, path, dir) && ws && aligned(ws, 256) && ws_bytes >= workspace_bytes(g, dir, path, 16);
-}
-
-dfp_status ws_check(const Geom& g, int32_t dir, int32_t path, int32_t bits, const void* ws, size_t ws_bytes) {
-  if (bits != 15) return DFP_OK;
-  const size_t need = workspace_bytes(g, dir, path, bits);
-  if (need == 0 || (dir == DFP_BWD_WT && bwdw_mfma_wide(g))) return DFP_OK;  // (wide: optional)
-  if (!ws || ws_bytes < need || !aligned(ws, 256)) return DFP_ERR_WORKSPACE;
-  return DFP_OK;
+dfp_status ws_check(const Route& r, const void* ws, size_t ws_bytes) {
+  if (r.ws_bytes == 0 || r.optional_ws || ws_holds(r, ws, ws_bytes)) return DFP_OK;
+  return DFP_ERR_WORKSPACE;
 }
 
 // GEMM descriptor and flat-tensor checks.
@@ -254,7 +255,7 @@ int64_t dfp_num_chunks(const dfp_desc* d, int32_t direction) {
 size_t dfp_workspace_bytes(const dfp_desc* d, int32_t direction) {
   Geom g;
   if (!d || !params_ok(d) || direction < 0 || direction > 2 || !geom_from_desc(d, &g)) return 0;
-  return workspace_bytes(g, direction, d->path, d->bits);
+  return route_of(g, direction, d->path, d->bits).ws_bytes;
 }
 
 dfp_status dfp_quantize(const dfp_desc* d, int32_t role, const float* src, int16_t* dst, dfp_scale* s,
@@ -285,12 +286,12 @@ dfp_status dfp_downconvert(const dfp_desc* d, int32_t role, const float* src, in
 }
 
 // One convolution on the matrix cores.
-static dfp_status conv_mfma(int32_t dir, const Geom& g, int32_t path, const int16_t* a, const dfp_scale* sa,
-                            const int16_t* b, const dfp_scale* sb, float* out, dfp_scale* so, void* ws,
-                            int32_t* partials, hipStream_t st, bool i32) {
+static dfp_status conv_mfma(int32_t dir, const Geom& g, const Route& r, int32_t path, const int16_t* a,
+                            const dfp_scale* sa, const int16_t* b, const dfp_scale* sb, float* out, dfp_scale* so,
+                            void* ws, int32_t* partials, hipStream_t st, bool i32) {
   const bool w16 = path == DFP_PATH_MFMA;
   if (i32) return launch_conv_mfma(dir, g, a, sa, b, sb, out, so, nullptr, ws, st, true);
-  if (dir == DFP_BWD_WT) return launch_bwdw_mfma(g, a, sa, b, sb, out, partials, ws, st);
+  if (dir == DFP_BWD_WT) return launch_bwdw_mfma(g, r.wt, a, sa, b, sb, out, partials, ws, st);
   if (dir == DFP_BWD_DATA && !partials && conv_bwd_data_sub_bytes(g) > 0)
     return launch_conv_bwd_data_sub(g, a, sa, b, sb, out, so, ws, st, w16);
   if (dir == DFP_BWD_DATA && !partials && conv_bwd_data_phase_bytes(g) > 0)
@@ -300,18 +301,32 @@ static dfp_status conv_mfma(int32_t dir, const Geom& g, int32_t path, const int1
 }
 
 // P = 16: scan, the MFMA path into a scale of its own, the gated VALU launch.
-static dfp_status conv_p16(int32_t dir, const Geom& g, int32_t path, const int16_t* a, const dfp_scale* sa,
-                           const int16_t* b, const dfp_scale* sb, float* out, dfp_scale* so, void* ws,
-                           hipStream_t st, bool i32) {
-  void* gate = reinterpret_cast<uint8_t*>(ws) + p16_gate_offset(g, dir);
+static dfp_status conv_p16(int32_t dir, const Geom& g, const Route& r, int32_t path, const int16_t* a,
+                           const dfp_scale* sa, const int16_t* b, const dfp_scale* sb, float* out, dfp_scale* so,
+                           void* ws, hipStream_t st, bool i32) {
+  void* gate = reinterpret_cast<uint8_t*>(ws) + (r.ws_bytes - kP16GateBytes);
   const int32_t role_a = dir == DFP_BWD_DATA ? DFP_ROLE_DY : DFP_ROLE_X;
   const int32_t role_b = dir == DFP_BWD_WT ? DFP_ROLE_DY : DFP_ROLE_W;
   dfp_status rc;
   if ((rc = launch_p16_scan(a, role_numel(g, role_a), b, role_numel(g, role_b), so, gate, st)) != DFP_OK) return rc;
-  if ((rc = conv_mfma(dir, g, path, a, sa, b, sb, out, so ? p16_mfma_scale(gate) : nullptr, ws, nullptr, st, i32)) !=
-      DFP_OK)
+  if ((rc = conv_mfma(dir, g, r, path, a, sa, b, sb, out, so ? p16_mfma_scale(gate) : nullptr, ws, nullptr, st,
+                      i32)) != DFP_OK)
     return rc;
   return launch_conv_valu_gated(dir, g, a, sa, b, sb, out, so, gate, st, i32);
+}
+
+// A checked call: the matrix cores, at P = 16 behind the scan, or the VALU kernels.
+static dfp_status conv_run(int32_t dir, const dfp_desc* d, const Geom& g, const Route& r, const int16_t* a,
+                           const dfp_scale* sa, const int16_t* b, const dfp_scale* sb, float* out, dfp_scale* so,
+                           void* ws, size_t ws_bytes, int32_t* partials, hipStream_t st, bool i32) {
+  // (calls whose workspace is optional record partials on the VALU)
+  if (r.mfma && (!r.optional_ws || (ws_holds(r, ws, ws_bytes) && !partials))) {
+    if (d->bits == 16) return conv_p16(dir, g, r, d->path, a, sa, b, sb, out, so, ws, st, i32);
+    return conv_mfma(dir, g, r, d->path, a, sa, b, sb, out, so, ws, partials, st, i32);
+  }
+  dfp_status rc;
+  if (so && (rc = launch_scale_reset(so, st)) != DFP_OK) return rc;
+  return launch_conv_valu(dir, g, a, sa, b, sb, out, so, partials, st, i32);
 }
 
 static dfp_status conv_common(int32_t dir, const dfp_desc* d, const int16_t* a, const dfp_scale* sa,
@@ -320,18 +335,10 @@ static dfp_status conv_common(int32_t dir, const dfp_desc* d, const int16_t* a, 
   Geom g;
   dfp_status rc = conv_checks(d, &g, a, sa, b, sb, out);
   if (rc != DFP_OK) return rc;
-  if ((rc = ws_check(g, dir, d->path, d->bits, ws, ws_bytes)) != DFP_OK) return rc;
+  const Route r = route_of(g, dir, d->path, d->bits);
+  if ((rc = ws_check(r, ws, ws_bytes)) != DFP_OK) return rc;
   if (so && !aligned(so, 16)) return DFP_ERR_ALIGN;
-  hipStream_t st = (hipStream_t)stream;
-  // wide backward-weights layers: the VALU kernel without a workspace or with partials
-  const bool valu = dir == DFP_BWD_WT && bwdw_mfma_wide(g) &&
-                    (partials || !ws || !aligned(ws, 256) || ws_bytes < workspace_bytes(g, dir, d->path, d->bits));
-  if (!valu && use_mfma(g, d->path, d->bits, dir))
-    return conv_mfma(dir, g, d->path, a, sa, b, sb, out, so, ws, partials, st, false);
-  if (d->bits == 16 && !partials && p16_on_mfma(g, dir, d->path, ws, ws_bytes))
-    return conv_p16(dir, g, d->path, a, sa, b, sb, out, so, ws, st, false);
-  if (so && (rc = launch_scale_reset(so, st)) != DFP_OK) return rc;
-  return launch_conv_valu(dir, g, a, sa, b, sb, out, so, partials, st);
+  return conv_run(dir, d, g, r, a, sa, b, sb, out, so, ws, ws_bytes, partials, (hipStream_t)stream, false);
 }
 
 // Single-chunk DFP-32 output (forward or backward-data): chunk_len must cover
@@ -344,16 +351,11 @@ static dfp_status conv_i32_common(int32_t dir, const dfp_desc* d, const int16_t*
   if (rc != DFP_OK) return rc;
   if (!so) return DFP_ERR_NULL;
   if (d->chunk_len < reduction_len(g, dir)) return DFP_ERR_PARAM;
-  if ((rc = ws_check(g, dir, d->path, d->bits, ws, ws_bytes)) != DFP_OK) return rc;
+  const Route r = route_of(g, dir, d->path, d->bits);
+  if ((rc = ws_check(r, ws, ws_bytes)) != DFP_OK) return rc;
   if (!aligned(so, 16)) return DFP_ERR_ALIGN;
-  hipStream_t st = (hipStream_t)stream;
-  float* outf = reinterpret_cast<float*>(out);
-  if (use_mfma(g, d->path, d->bits, dir))
-    return conv_mfma(dir, g, d->path, a, sa, b, sb, outf, so, ws, nullptr, st, true);
-  if (d->bits == 16 && p16_on_mfma(g, dir, d->path, ws, ws_bytes))
-    return conv_p16(dir, g, d->path, a, sa, b, sb, outf, so, ws, st, true);
-  if ((rc = launch_scale_reset(so, st)) != DFP_OK) return rc;
-  return launch_conv_valu(dir, g, a, sa, b, sb, outf, so, nullptr, st, true);
+  return conv_run(dir, d, g, r, a, sa, b, sb, reinterpret_cast<float*>(out), so, ws, ws_bytes, nullptr,
+                  (hipStream_t)stream, true);
 }
 
 dfp_status dfp_conv_fwd_i32(const dfp_desc* d, const int16_t* x, const dfp_scale* sx, const int16_t* w,
@@ -541,13 +543,18 @@ dfp_status dfp_conv_bwd_weights_noalloc(const dfp_desc* d, const int16_t* x, con
   Geom g;
   dfp_status rc = conv_checks(d, &g, x, sx, dy, sdy, dw);
   if (rc != DFP_OK) return rc;
-  // (P = 16 runs the VALU kernel here, which needs no scratch)
-  // (a wide layer whose scratch is too large runs there as well)
-  const bool mfma = use_mfma(g, d->path, d->bits, DFP_BWD_WT) &&
-                    (!bwdw_mfma_wide(g) || plan_bwdw_mfma(g).bytes <= (int64_t)DFP_NOALLOC_SCRATCH_BYTES);
-  // a layer whose ring-kernel scratch is too large runs the kernels without it
-  const bool ring = mfma && plan_bwdw_mfma(g).bytes <= (int64_t)DFP_NOALLOC_SCRATCH_BYTES;
-  if (mfma && plan_bwdw_mfma(g, ring).bytes > (int64_t)DFP_NOALLOC_SCRATCH_BYTES) return DFP_ERR_SCRATCH_LIMIT;
+  // (P = 16 runs the VALU kernel here, which needs no scratch, and so does a wide
+  // layer whose scratch is too large; another layer whose ring-kernel scratch is
+  // too large runs the kernels without it)
+  constexpr int64_t kScratch = DFP_NOALLOC_SCRATCH_BYTES;
+  BwdwPlan p{};
+  bool mfma = false;
+  if (d->path != DFP_PATH_VALU && d->bits == 15) {
+    p = plan_bwdw_mfma(g);
+    mfma = p.fits || (p.wide && p.bytes <= kScratch);
+    if (p.bytes > kScratch) p = without_ring(p);
+    if (mfma && p.bytes > kScratch) return DFP_ERR_SCRATCH_LIMIT;
+  }
   hipStream_t st = (hipStream_t)stream;
   if (!mfma) return launch_conv_valu(DFP_BWD_WT, g, x, sx, dy, sdy, dw, nullptr, nullptr, st);
   int dev = -1;
@@ -559,7 +566,7 @@ dfp_status dfp_conv_bwd_weights_noalloc(const dfp_desc* d, const int16_t* x, con
   }
   void* ws = scratch_on_device(dev);
   if (!ws) return DFP_ERR_HIP;
-  return launch_bwdw_mfma(g, x, sx, dy, sdy, dw, nullptr, ws, st, ring);
+  return launch_bwdw_mfma(g, p, x, sx, dy, sdy, dw, nullptr, ws, st);
 }
 
 dfp_status dfp_profile_start(int32_t capacity) {

@@ -14,6 +14,14 @@ struct BwdwPlan {
   int64_t band_bytes, smem_bytes;       // LDS band (all channels of a column tile) + offset table
   int64_t ad_bytes, xp_bytes, u_bytes, bytes;
   int64_t sub_bytes;                    // strided 1x1: the subsampled input, at the end of the workspace
+  bool ring;                            // the ring kernel may be used (ad_bytes, xp_bytes, bytes: room for it)
+  int64_t ad_no_ring, xp_no_ring, bytes_no_ring;
+  bool fits;  // any call with the plan's workspace can run on the matrix cores
+  // others that calls without partials can: rows too wide for the general kernel's
+  // LDS band, on kernels that stage no such band (1x1 layers, the ring kernel;
+  // N = 8, 280 -> 40 channels on 63 x 63, 1x1, L = 16: 9.1 ms on the VALU kernel,
+  // 0.10 ms on the ring kernel)
+  bool wide;
 };
 
 struct BwdwArgs {
@@ -35,15 +43,11 @@ struct BwdwArgs {
   uint32_t flat_tab;            // flat-band kernel: byte offset of the selector table after the planes
 };
 
-// ring: whether the ring kernel, whose workspace may be larger, may be used.
-BwdwPlan plan_bwdw_mfma(const Geom& g, bool ring = true);
-// Layers that any call with the plan's workspace can take to the matrix cores.
-bool bwdw_mfma_supported(const Geom& g);
-// Others that calls without partials can: rows too wide for the general kernel's
-// LDS band, on kernels that stage no such band (1x1 layers, the ring kernel).
-bool bwdw_mfma_wide(const Geom& g);
-dfp_status launch_bwdw_mfma(const Geom& g, const int16_t* x, const dfp_scale* sx, const int16_t* dy,
-                            const dfp_scale* sdy, float* dw, int32_t* partials, void* ws, hipStream_t st,
-                            bool ring = true);
+BwdwPlan plan_bwdw_mfma(const Geom& g);
+// The same without the ring kernel, whose workspace may be larger.
+BwdwPlan without_ring(BwdwPlan p);
+// p: the layer's plan, or the same without_ring.
+dfp_status launch_bwdw_mfma(const Geom& g, const BwdwPlan& p, const int16_t* x, const dfp_scale* sx, const int16_t* dy,
+                            const dfp_scale* sdy, float* dw, int32_t* partials, void* ws, hipStream_t st);
 
 }  // namespace dfp

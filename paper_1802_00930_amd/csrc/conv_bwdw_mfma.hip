@@ -19,9 +19,9 @@
 // that band.  A lane owning column (c, r, s) then gathers its 16 operand pairs
 // as band[c][offset(t) + r*Wpad + s], which covers padding, strides and image
 // boundaries with no branches.
-#include <numeric>
 #include <type_traits>
 
+#include "band_rows.h"
 #include "conv_bwdw_mfma.h"
 
 namespace dfp {
@@ -2620,11 +2620,18 @@ static bool ring_wanted(const Geom& g) {
   return ring_layout(g).ok;
 }
 
-BwdwPlan plan_bwdw_mfma(const Geom& g, bool ring) {
+// 1x1 layers whose operands are prepared (or read) without a band of rows; the
+// digit preparation indexes elements with 32 bits.
+static bool direct_1x1(const Geom& g) {
+  return unit_1x1(g) && (g.L % 32) == 0 && (int64_t)g.n * std::max(g.c, g.k) * g.p * g.q < (1ll << 31);
+}
+
+BwdwPlan plan_bwdw_mfma(const Geom& g) {
   if (strided_1x1(g)) {
-    BwdwPlan p = plan_bwdw_mfma(subsampled(g), ring);
+    BwdwPlan p = plan_bwdw_mfma(subsampled(g));
     p.sub_bytes = align256((int64_t)g.n * g.c * g.p * g.q * 2);
     p.bytes += p.sub_bytes;
+    p.bytes_no_ring += p.sub_bytes;
     return p;
   }
   BwdwPlan p{};
@@ -2635,27 +2642,8 @@ BwdwPlan plan_bwdw_mfma(const Geom& g, bool ring) {
   p.Wpad = (g.w + 2 * g.pw + 7) / 8 * 8;
   const int64_t J = (p.T + g.L - 1) / g.L;
   p.nseg = (int32_t)((J + g.G - 1) / g.G);
-  // largest band (padded rows touched by kSBT consecutive indices of a
-  // segment).  Where segments are whole bands, band i starts at index 128 i and
-  // its rows repeat with the period of 128 i mod PQ.
-  const int64_t PQ = (int64_t)g.p * g.q;
-  int64_t rows_max = 0;
-  const int64_t seg_len = (int64_t)g.G * g.L;
-  auto band = [&](int64_t ta, int64_t tb) {  // indices ta .. tb
-    const int64_t za = (ta / PQ) * p.Hpad + ((ta % PQ) / g.q) * g.sh;
-    const int64_t zb = (tb / PQ) * p.Hpad + ((tb % PQ) / g.q) * g.sh + g.r - 1;
-    rows_max = std::max(rows_max, zb - za + 1);
-  };
-  if (seg_len % kSBT == 0 || p.nseg == 1) {
-    const int64_t nbands = (p.T + kSBT - 1) / kSBT, period = PQ / std::gcd(PQ, (int64_t)kSBT);
-    for (int64_t i = 0; i < std::min(nbands, period); ++i) band(i * kSBT, std::min((i + 1) * kSBT, p.T) - 1);
-  } else {
-    for (int64_t s = 0; s < p.nseg; ++s) {
-      const int64_t t0 = s * seg_len, t1 = std::min(t0 + seg_len, p.T);
-      for (int64_t sb = t0 / 32; sb < (t1 + 31) / 32; sb += kSBT / 32)
-        band(std::max(sb * 32, t0), std::min((sb + kSBT / 32) * 32, t1) - 1);
-    }
-  }
+  // largest band (padded rows touched by kSBT consecutive indices of a segment)
+  const int64_t rows_max = band_rows_max({p.T, g.p, g.q, p.Hpad, g.sh, g.r, kSBT}, (int64_t)g.G * g.L);
   const int64_t RS = (int64_t)g.r * g.s;
   p.nch_max = (int32_t)std::min<int64_t>(g.c, (kNT - 1) / RS + 2);
   p.rows_max = (int32_t)rows_max;
@@ -2667,13 +2655,27 @@ BwdwPlan plan_bwdw_mfma(const Geom& g, bool ring) {
   p.xp_bytes = align256((int64_t)g.c * g.n * p.Hpad * (2 * p.Wpad + 16));
   if (unit_1x1(g)) p.xp_bytes = std::max<int64_t>(p.xp_bytes, align256(p.KBT * ((g.c + 63) / 64 * 64) * 64));
   if (flat_geom(g)) p.xp_bytes = std::max<int64_t>(p.xp_bytes, align256(flat_layout(g).bytes));
-  if (ring && ring_wanted(g)) {
+  p.u_bytes = p.nseg > 1 ? align256((int64_t)p.nseg * g.k * g.c * RS * 4) : 0;
+  p.bytes = p.bytes_no_ring = p.ad_bytes + p.xp_bytes + p.u_bytes;
+  p.fits = p.smem_bytes <= 64 * 1024;
+  p.ring = ring_wanted(g);
+  p.wide = !p.fits && (direct_1x1(g) || p.ring);
+  p.ad_no_ring = p.ad_bytes;
+  p.xp_no_ring = p.xp_bytes;
+  if (p.ring) {
     const RingLayout y = ring_layout(g);
     p.ad_bytes = std::max<int64_t>(p.ad_bytes, y.ad_bytes);
     p.xp_bytes = std::max<int64_t>(p.xp_bytes, align256(y.xb_bytes));
+    p.bytes = p.ad_bytes + p.xp_bytes + p.u_bytes;
   }
-  p.u_bytes = p.nseg > 1 ? align256((int64_t)p.nseg * g.k * g.c * RS * 4) : 0;
-  p.bytes = p.ad_bytes + p.xp_bytes + p.u_bytes;
+  return p;
+}
+
+BwdwPlan without_ring(BwdwPlan p) {
+  p.ring = false;
+  p.ad_bytes = p.ad_no_ring;
+  p.xp_bytes = p.xp_no_ring;
+  p.bytes = p.bytes_no_ring;
   return p;
 }
 
@@ -2706,28 +2708,9 @@ static BandLayout band_layout(const Geom& g, const BwdwPlan& p) {
   return bl;
 }
 
-bool bwdw_mfma_supported(const Geom& g) {
-  const BwdwPlan p = plan_bwdw_mfma(g);
-  return p.smem_bytes <= 64 * 1024;
-}
-
-// 1x1 layers whose operands are prepared (or read) without a band of rows; the
-// digit preparation indexes elements with 32 bits.
-static bool direct_1x1(const Geom& g) {
-  return unit_1x1(g) && (g.L % 32) == 0 && (int64_t)g.n * std::max(g.c, g.k) * g.p * g.q < (1ll << 31);
-}
-
-// (N = 8, 280 -> 40 channels on 63 x 63, 1x1, L = 16: 9.1 ms on the VALU kernel,
-// 0.10 ms on the ring kernel)
-bool bwdw_mfma_wide(const Geom& g) {
-  if (strided_1x1(g)) return bwdw_mfma_wide(subsampled(g));
-  return !bwdw_mfma_supported(g) && (direct_1x1(g) || ring_wanted(g));
-}
-
-dfp_status launch_bwdw_mfma(const Geom& g, const int16_t* x, const dfp_scale* sx, const int16_t* dy,
-                            const dfp_scale* sdy, float* dw, int32_t* partials, void* ws, hipStream_t st, bool ring) {
-  if (strided_1x1(g)) {
-    const BwdwPlan p = plan_bwdw_mfma(g, ring);
+dfp_status launch_bwdw_mfma(const Geom& g, const BwdwPlan& p, const int16_t* x, const dfp_scale* sx, const int16_t* dy,
+                            const dfp_scale* sdy, float* dw, int32_t* partials, void* ws, hipStream_t st) {
+  if (p.sub_bytes > 0) {
     int16_t* xs = reinterpret_cast<int16_t*>(reinterpret_cast<uint8_t*>(ws) + (p.bytes - p.sub_bytes));
     const int64_t planes = (int64_t)g.n * g.c;
     const int32_t gx = (g.p * g.q + 255) / 256;
@@ -2735,9 +2718,11 @@ dfp_status launch_bwdw_mfma(const Geom& g, const int16_t* x, const dfp_scale* sx
     DFP_LAUNCH(K_XPREP, k_subsample, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, st, x, xs, planes, g.h, g.w,
                g.p, g.q, g.sh, g.sw);
     // the subsampled plan's workspace ends where xs begins
-    return launch_bwdw_mfma(subsampled(g), xs, sx, dy, sdy, dw, partials, ws, st, ring);
+    BwdwPlan u = p;
+    u.bytes -= p.sub_bytes;
+    u.sub_bytes = 0;
+    return launch_bwdw_mfma(subsampled(g), u, xs, sx, dy, sdy, dw, partials, ws, st);
   }
-  const BwdwPlan p = plan_bwdw_mfma(g, ring);
   uint8_t* base = reinterpret_cast<uint8_t*>(ws);
   uint8_t* ad = base;
   uint16_t* xp = reinterpret_cast<uint16_t*>(base + p.ad_bytes);
@@ -2851,7 +2836,7 @@ dfp_status launch_bwdw_mfma(const Geom& g, const int16_t* x, const dfp_scale* sx
     return DFP_OK;
   }
   const bool l64 = g.L == 64 && (p.T % 64) == 0;  // every segment a whole number of two-block chunks
-  const bool to_ring = ring && !partials && ring_wanted(g);
+  const bool to_ring = p.ring && !partials;
   // runs of 4 and big buffers: the eight-wave kernel only (L = 64, no partials)
   const bool band_ok = bl.big ? (bl.run == 8 && l64 && !partials && safe.w8_big)
                        : bl.run == 8 ? (l64 ? (partials ? safe.skew_t : (safe.w8 || safe.skew_f))
