@@ -79,7 +79,7 @@ typedef enum dfp_status {
                             an element count beyond 2^40                       */
   DFP_ERR_PARAM = 3,     /* bits, rounding, role, chunk_len, seg_chunks or path */
   DFP_ERR_ALIGN = 4,     /* FP32 src not 16-byte aligned or INT16 dst not 8-byte */
-  DFP_ERR_WORKSPACE = 5, /* workspace NULL or smaller than dfp_workspace_bytes() */
+  DFP_ERR_WORKSPACE = 5, /* workspace NULL or too small (dfp_workspace_bytes)   */
   DFP_ERR_HIP = 6,       /* a HIP launch or runtime call failed                 */
   DFP_ERR_SCRATCH_LIMIT = 7 /* dfp_conv_bwd_weights_noalloc: the layer needs more
                                than DFP_NOALLOC_SCRATCH_BYTES of scratch        */
@@ -163,7 +163,8 @@ dfp_status dfp_quantize(const dfp_desc* d, int32_t role, const float* src, int16
  * sy (nullable): receives max|y| in amax_bits and OUTPUT_INF, ready for
  * dfp_downconvert(..., amax_ready = 1).  partials (nullable, for tests):
  * INT32 [J][N*K*P*Q], every chunk partial P_j.  workspace: device scratch of
- * at least dfp_workspace_bytes(d, DFP_FWD) bytes, 256-byte aligned. */
+ * dfp_workspace_bytes(d, DFP_FWD) bytes (less where that function says so),
+ * 256-byte aligned. */
 dfp_status dfp_conv_fwd(const dfp_desc* d, const int16_t* x, const dfp_scale* sx, const int16_t* w,
                         const dfp_scale* sw, float* y, dfp_scale* sy, void* workspace,
                         size_t ws_bytes, int32_t* partials, void* stream);
@@ -249,11 +250,22 @@ dfp_status dfp_downconvert_i32(const dfp_desc* d, int32_t role, const int32_t* s
                                int16_t* dst, dfp_scale* sout, int32_t amax_ready, void* stream);
 
 /* Device workspace needed by a convolution direction (bytes, 0 if none);
- * 0 also for an invalid descriptor.  At P = 16, and for backward-weights
- * layers whose rows are too wide for the general matrix-core kernel (the input
- * rows that 128 output pixels touch, for the channels of 128 filter columns,
- * take more than 64 KiB of INT16), it may be left out (NULL): the call then runs
- * on the VALU kernels, as the latter do when recording partials. */
+ * 0 also for an invalid descriptor.  The number has room for the fastest
+ * kernels, whose operand layouts can take several times the input's size: where
+ * forward's C (backward-data's K) is not a multiple of 32 and the chunk length is
+ * 64, 32, 16 or 8, these may unfold the input (its digits up to R S times, at
+ * most 1 GiB: 24 -> 24 channels, 3 x 3, 64 images of 112 x 112, 411 MB).  Forward
+ * and backward-data calls at P = 15 also take less and then run the general
+ * kernels: from
+ *   64 ceil(T/32) M64 + 32 N Hd Wd ceil(Ci/16) + 8 ceil(T/32)
+ * bytes on, each term rounded up to 256, with T = Ci R S and M64 the output
+ * channels rounded up to 64; forward Ci = C, Hd x Wd = the padded input;
+ * backward-data at unit stride Ci = K, Hd x Wd = (H + R - 1) x (W + S - 1) (at
+ * other strides it has scratch of its own: pass the full number).  At P = 16, and
+ * for backward-weights layers whose rows are too wide for the general matrix-core
+ * kernel (the input rows that 128 output pixels touch, for the channels of 128
+ * filter columns, take more than 64 KiB of INT16), it may be left out (NULL): the
+ * call then runs on the VALU kernels, as the latter do when recording partials. */
 size_t dfp_workspace_bytes(const dfp_desc* d, int32_t direction);
 
 /* Number of chunks J = ceil(T / L) of a direction; -1 for an invalid descriptor. */

@@ -146,8 +146,15 @@ struct Route {
   bool optional_ws;  // but a call without (enough) workspace runs on the VALU
   int64_t mfma_bytes;  // workspace of the MFMA path; at P = 16 the gate's words follow it
   size_t ws_bytes;     // workspace in all (dfp_workspace_bytes)
+  // The least that calls take: forward and backward-data run the general kernels,
+  // without the unfolded operand and the output phases of chunks below 64, where
+  // there is no room for these.
+  size_t least_bytes;
   BwdwPlan wt;         // backward-weights
 };
+
+// The output phases of a strided backward-data run only with the full workspace.
+bool phases_need_room(const Geom& g) { return g.L != 64; }
 
 Route route_of(const Geom& g, int32_t dir, int32_t path, int32_t bits) {
   Route r{};
@@ -157,11 +164,17 @@ Route route_of(const Geom& g, int32_t dir, int32_t path, int32_t bits) {
     r.mfma = r.wt.fits || r.wt.wide;
     r.optional_ws = r.wt.wide;
     r.mfma_bytes = r.wt.bytes;
-  } else {
-    r.mfma = conv_mfma_supported(g, dir);
-    if (r.mfma) r.mfma_bytes = plan_conv_mfma(g, dir).bytes;
-    if (r.mfma && dir == DFP_BWD_DATA)  // room for either route (partials take the general one)
-      r.mfma_bytes = std::max(r.mfma_bytes, std::max(conv_bwd_data_sub_bytes(g), conv_bwd_data_phase_bytes(g)));
+    r.least_bytes = (size_t)r.wt.bytes;
+  } else if (conv_mfma_supported(g, dir)) {
+    r.mfma = true;
+    int64_t least = plan_conv_mfma(g, dir, false).bytes;
+    r.mfma_bytes = plan_conv_mfma(g, dir).bytes;
+    if (dir == DFP_BWD_DATA) {  // room for either route (partials take the general one)
+      const int64_t phases = conv_bwd_data_phase_bytes(g);
+      r.mfma_bytes = std::max(r.mfma_bytes, std::max(conv_bwd_data_sub_bytes(g), phases));
+      least = std::max(least, std::max(conv_bwd_data_sub_bytes(g, false), phases_need_room(g) ? 0 : phases));
+    }
+    r.least_bytes = (size_t)least;
   }
   if (!r.mfma) return Route{};
   r.optional_ws |= bits != 15;
@@ -169,12 +182,10 @@ Route route_of(const Geom& g, int32_t dir, int32_t path, int32_t bits) {
   return r;
 }
 
-bool ws_holds(const Route& r, const void* ws, size_t ws_bytes) {
-  return ws && aligned(ws, 256) && ws_bytes >= r.ws_bytes;
-}
+bool ws_holds(size_t need, const void* ws, size_t ws_bytes) { return ws && aligned(ws, 256) && ws_bytes >= need; }
 
 dfp_status ws_check(const Route& r, const void* ws, size_t ws_bytes) {
-  if (r.ws_bytes == 0 || r.optional_ws || ws_holds(r, ws, ws_bytes)) return DFP_OK;
+  if (r.ws_bytes == 0 || r.optional_ws || ws_holds(r.least_bytes, ws, ws_bytes)) return DFP_OK;
   return DFP_ERR_WORKSPACE;
 }
 
@@ -285,19 +296,19 @@ dfp_status dfp_downconvert(const dfp_desc* d, int32_t role, const float* src, in
   return launch_quant_convert(src, dst, n, s, d->bits, d->rounding, d->seed, (uint32_t)role, st);
 }
 
-// One convolution on the matrix cores.
+// One convolution on the matrix cores; room: the workspace is of dfp_workspace_bytes.
 static dfp_status conv_mfma(int32_t dir, const Geom& g, const Route& r, int32_t path, const int16_t* a,
                             const dfp_scale* sa, const int16_t* b, const dfp_scale* sb, float* out, dfp_scale* so,
-                            void* ws, int32_t* partials, hipStream_t st, bool i32) {
+                            void* ws, bool room, int32_t* partials, hipStream_t st, bool i32) {
   const bool w16 = path == DFP_PATH_MFMA;
-  if (i32) return launch_conv_mfma(dir, g, a, sa, b, sb, out, so, nullptr, ws, st, true);
+  if (i32) return launch_conv_mfma(dir, g, a, sa, b, sb, out, so, nullptr, ws, st, true, false, true, room);
   if (dir == DFP_BWD_WT) return launch_bwdw_mfma(g, r.wt, a, sa, b, sb, out, partials, ws, st);
   if (dir == DFP_BWD_DATA && !partials && conv_bwd_data_sub_bytes(g) > 0)
-    return launch_conv_bwd_data_sub(g, a, sa, b, sb, out, so, ws, st, w16);
-  if (dir == DFP_BWD_DATA && !partials && conv_bwd_data_phase_bytes(g) > 0)
+    return launch_conv_bwd_data_sub(g, a, sa, b, sb, out, so, ws, st, w16, room);
+  if (dir == DFP_BWD_DATA && !partials && (room || !phases_need_room(g)) && conv_bwd_data_phase_bytes(g) > 0)
     return launch_conv_bwd_data_phases(g, a, sa, b, sb, out, so, ws, st, w16);
   // the filter prep kernel clears so before the main kernel raises it
-  return launch_conv_mfma(dir, g, a, sa, b, sb, out, so, partials, ws, st, false, w16);
+  return launch_conv_mfma(dir, g, a, sa, b, sb, out, so, partials, ws, st, false, w16, true, room);
 }
 
 // P = 16: scan, the MFMA path into a scale of its own, the gated VALU launch.
@@ -309,8 +320,8 @@ static dfp_status conv_p16(int32_t dir, const Geom& g, const Route& r, int32_t p
   const int32_t role_b = dir == DFP_BWD_WT ? DFP_ROLE_DY : DFP_ROLE_W;
   dfp_status rc;
   if ((rc = launch_p16_scan(a, role_numel(g, role_a), b, role_numel(g, role_b), so, gate, st)) != DFP_OK) return rc;
-  if ((rc = conv_mfma(dir, g, r, path, a, sa, b, sb, out, so ? p16_mfma_scale(gate) : nullptr, ws, nullptr, st,
-                      i32)) != DFP_OK)
+  if ((rc = conv_mfma(dir, g, r, path, a, sa, b, sb, out, so ? p16_mfma_scale(gate) : nullptr, ws, true, nullptr,
+                      st, i32)) != DFP_OK)
     return rc;
   return launch_conv_valu_gated(dir, g, a, sa, b, sb, out, so, gate, st, i32);
 }
@@ -319,10 +330,11 @@ static dfp_status conv_p16(int32_t dir, const Geom& g, const Route& r, int32_t p
 static dfp_status conv_run(int32_t dir, const dfp_desc* d, const Geom& g, const Route& r, const int16_t* a,
                            const dfp_scale* sa, const int16_t* b, const dfp_scale* sb, float* out, dfp_scale* so,
                            void* ws, size_t ws_bytes, int32_t* partials, hipStream_t st, bool i32) {
+  const bool room = ws_holds(r.ws_bytes, ws, ws_bytes);
   // (calls whose workspace is optional record partials on the VALU)
-  if (r.mfma && (!r.optional_ws || (ws_holds(r, ws, ws_bytes) && !partials))) {
+  if (r.mfma && (!r.optional_ws || (room && !partials))) {
     if (d->bits == 16) return conv_p16(dir, g, r, d->path, a, sa, b, sb, out, so, ws, st, i32);
-    return conv_mfma(dir, g, r, d->path, a, sa, b, sb, out, so, ws, partials, st, i32);
+    return conv_mfma(dir, g, r, d->path, a, sa, b, sb, out, so, ws, room, partials, st, i32);
   }
   dfp_status rc;
   if (so && (rc = launch_scale_reset(so, st)) != DFP_OK) return rc;

@@ -54,7 +54,8 @@ constexpr int32_t kBlockedMaxBlocks = 80;
 // Output rows per workgroup tile of the main kernels (A digits are padded to it).
 constexpr int32_t kMfmaRowTile = 64;
 
-ConvMfmaPlan plan_conv_mfma(const Geom& g, int32_t dir);
+// unfold: whether the unfolded operand, whose workspace may be larger, may be used.
+ConvMfmaPlan plan_conv_mfma(const Geom& g, int32_t dir, bool unfold = true);
 // Picks and launches the main kernel for prepared digit operands (args.L,
 // args.partials and i32 select it); ws_b_bytes is the size of args.xs.
 dfp_status launch_mfma_main(ConvMfmaArgs& args, int64_t ws_b_bytes, int kid, int kid32, bool i32, hipStream_t st);
@@ -63,10 +64,10 @@ bool conv_mfma_supported(const Geom& g, int32_t dir);
 dfp_status launch_conv_mfma(int32_t dir, const Geom& g, const int16_t* a, const dfp_scale* sa, const int16_t* b,
                             const dfp_scale* sb, float* out, dfp_scale* so, int32_t* partials, void* ws,
                             hipStream_t st, bool i32 = false,
-                            bool prefer_w16 = false, bool so_reset = true);
+                            bool prefer_w16 = false, bool so_reset = true, bool unfold = true);
 // Strided 1x1 backward-data without padding through the unit-stride grid:
 // workspace bytes it needs (0 if the layer does not qualify), and the launch.
-int64_t conv_bwd_data_sub_bytes(const Geom& g);
+int64_t conv_bwd_data_sub_bytes(const Geom& g, bool unfold = true);
 // Strided backward-data split by output phase into unit-stride problems over
 // the undilated dy (K a multiple of the chunk length): workspace bytes (0 if
 // the layer does not qualify), and the launch.
@@ -76,6 +77,6 @@ dfp_status launch_conv_bwd_data_phases(const Geom& g, const int16_t* dy, const d
                                        bool prefer_w16);
 dfp_status launch_conv_bwd_data_sub(const Geom& g, const int16_t* dy, const dfp_scale* sdy, const int16_t* w,
                                     const dfp_scale* sw, float* dx, dfp_scale* so, void* ws, hipStream_t st,
-                                    bool prefer_w16);
+                                    bool prefer_w16, bool unfold);
 
 }  // namespace dfp

@@ -2692,7 +2692,7 @@ bool conv_mfma_supported(const Geom& g, int32_t dir) {
 }
 
 // Workspace layout of the forward / backward-data MFMA path.
-ConvMfmaPlan plan_conv_mfma(const Geom& g, int32_t dir) {
+ConvMfmaPlan plan_conv_mfma(const Geom& g, int32_t dir, bool unfold) {
   ConvMfmaPlan p{};
   const bool fwd = dir == DFP_FWD;
   p.M = fwd ? g.k : g.c;
@@ -2722,7 +2722,7 @@ ConvMfmaPlan plan_conv_mfma(const Geom& g, int32_t dir) {
   // 18.6; 352 -> 352 1x1 on 14 x 14, L = 32, 20.6 / 15.5); below 32 they would run
   // the masked kernel.
   p.Tu = (p.T + 63) / 64 * 64;
-  if (conv_w16_eligible(p.Cin, p.T, g.L, false) || !conv_w16_eligible(p.Tu, p.Tu, g.L, false) ||
+  if (!unfold || conv_w16_eligible(p.Cin, p.T, g.L, false) || !conv_w16_eligible(p.Tu, p.Tu, g.L, false) ||
       !(p.Cin % 16 != 0 || g.L < 32) || g.n >= 65535 || (int64_t)g.n * p.Po * p.Qo * p.Tu * 2 > ((int64_t)1 << 30) ||
       (int64_t)g.n * p.Po * p.Qo * p.M >= ((int64_t)1 << 31) || (int64_t)p.Mp * p.Tu >= ((int64_t)1 << 30) ||
       (int64_t)(fwd ? g.h : g.p) * (fwd ? g.w : g.q) >= ((int64_t)1 << 31))  // (an offset in a source plane: 32 bits)
@@ -2738,9 +2738,9 @@ ConvMfmaPlan plan_conv_mfma(const Geom& g, int32_t dir) {
 
 dfp_status launch_conv_mfma(int32_t dir, const Geom& g, const int16_t* a, const dfp_scale* sa, const int16_t* b,
                             const dfp_scale* sb, float* out, dfp_scale* so, int32_t* partials, void* ws,
-                            hipStream_t st, bool i32, bool prefer_w16, bool so_reset) {
+                            hipStream_t st, bool i32, bool prefer_w16, bool so_reset, bool unfold) {
   // fwd: a = x (B source), b = w.  bwd-data: a = dy (B source), b = w.
-  const ConvMfmaPlan p = plan_conv_mfma(g, dir);
+  const ConvMfmaPlan p = plan_conv_mfma(g, dir, unfold);
   const bool fwd = dir == DFP_FWD;
   uint8_t* wsa = reinterpret_cast<uint8_t*>(ws);
   uint8_t* xs = wsa + p.ws_a_bytes;
@@ -3105,21 +3105,22 @@ Geom unit_grid(const Geom& g) {
 }
 }  // namespace
 
-int64_t conv_bwd_data_sub_bytes(const Geom& g) {
+int64_t conv_bwd_data_sub_bytes(const Geom& g, bool unfold) {
   if (g.r != 1 || g.s != 1 || g.ph != 0 || g.pw != 0 || (g.sh == 1 && g.sw == 1)) return 0;
   // k_scatter_strided indexes a plane (and sizes its grid) with 32 bits
   if ((int64_t)g.h * g.w >= (1ll << 31) - 256) return 0;
   const Geom u = unit_grid(g);
   if (!conv_mfma_supported(u, DFP_BWD_DATA)) return 0;
-  return plan_conv_mfma(u, DFP_BWD_DATA).bytes + align256((int64_t)g.n * g.c * g.p * g.q * 4);
+  return plan_conv_mfma(u, DFP_BWD_DATA, unfold).bytes + align256((int64_t)g.n * g.c * g.p * g.q * 4);
 }
 
 dfp_status launch_conv_bwd_data_sub(const Geom& g, const int16_t* dy, const dfp_scale* sdy, const int16_t* w,
                                     const dfp_scale* sw, float* dx, dfp_scale* so, void* ws, hipStream_t st,
-                                    bool prefer_w16) {
+                                    bool prefer_w16, bool unfold) {
   const Geom u = unit_grid(g);
-  float* sub = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(ws) + plan_conv_mfma(u, DFP_BWD_DATA).bytes);
-  dfp_status rc = launch_conv_mfma(DFP_BWD_DATA, u, dy, sdy, w, sw, sub, so, nullptr, ws, st, false, prefer_w16);
+  float* sub = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(ws) + plan_conv_mfma(u, DFP_BWD_DATA, unfold).bytes);
+  dfp_status rc = launch_conv_mfma(DFP_BWD_DATA, u, dy, sdy, w, sw, sub, so, nullptr, ws, st, false, prefer_w16, true,
+                                   unfold);
   if (rc != DFP_OK) return rc;
   const int64_t planes = (int64_t)g.n * g.c;
   const int32_t gx = (g.h * g.w + 255) / 256;
