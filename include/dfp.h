@@ -409,7 +409,9 @@ dfp_status dfp_bn_relu_bwd(const dfp_bn_desc* d, const int16_t* dz, const dfp_sc
                            float* dgamma, float* dbeta, float* dres, int64_t* sums, void* workspace,
                            size_t ws_bytes, void* stream);
 
-/* Workspace bytes of dfp_bn_relu_fwd / _bwd; 0 for an invalid descriptor. */
+/* Workspace bytes of dfp_bn_relu_fwd / _bwd; 0 for an invalid descriptor.
+ * (With few images and channels up to 8 KiB of it are for the max pass; calls
+ * that leave these out run it with fewer workgroups.) */
 size_t dfp_bn_workspace_bytes(const dfp_bn_desc* d);
 
 /* One FP32 SGD step with momentum mu and weight decay wd on n master weights,

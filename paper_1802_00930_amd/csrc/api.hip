@@ -500,9 +500,9 @@ dfp_status dfp_bn_relu_fwd(const dfp_bn_desc* d, const int16_t* y, const dfp_sca
   if (!aligned(y, 16) || !aligned(zq, 16) || (res && !aligned(res, 16)) || (z && !aligned(z, 16)) ||
       !aligned(sy, 16) || !aligned(sz, 16) || (sums && !aligned(sums, 8)))
     return DFP_ERR_ALIGN;
-  if (!workspace || ws_bytes < bn_workspace_bytes(*d) || !aligned(workspace, 256)) return DFP_ERR_WORKSPACE;
+  if (!workspace || ws_bytes < bn_least_bytes(*d) || !aligned(workspace, 256)) return DFP_ERR_WORKSPACE;
   return launch_bn_relu_fwd(*d, y, sy, gamma, beta, res, z, zq, sz, mean, inv_std, sums, workspace,
-                            (hipStream_t)stream);
+                            ws_bytes, (hipStream_t)stream);
 }
 
 dfp_status dfp_bn_relu_bwd(const dfp_bn_desc* d, const int16_t* dz, const dfp_scale* sdz, const int16_t* y,
@@ -518,9 +518,9 @@ dfp_status dfp_bn_relu_bwd(const dfp_bn_desc* d, const int16_t* dz, const dfp_sc
       (dy && !aligned(dy, 16)) || (dres && !aligned(dres, 16)) || !aligned(sdz, 16) || !aligned(sy, 16) ||
       !aligned(sdy, 16) || (sums && !aligned(sums, 8)))
     return DFP_ERR_ALIGN;
-  if (!workspace || ws_bytes < bn_workspace_bytes(*d) || !aligned(workspace, 256)) return DFP_ERR_WORKSPACE;
+  if (!workspace || ws_bytes < bn_least_bytes(*d) || !aligned(workspace, 256)) return DFP_ERR_WORKSPACE;
   return launch_bn_relu_bwd(*d, dz, sdz, y, sy, gamma, beta, res, mean, inv_std, dy, dyq, sdy, dgamma, dbeta, dres,
-                            sums, workspace, (hipStream_t)stream);
+                            sums, workspace, ws_bytes, (hipStream_t)stream);
 }
 
 dfp_status dfp_sgd_quantize(int64_t n, float lr, float mu, float wd, int32_t bits, int32_t rounding, uint64_t seed,

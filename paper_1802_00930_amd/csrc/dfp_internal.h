@@ -158,12 +158,14 @@ dfp_status launch_gemm_valu(int32_t m, int32_t n, int32_t k, int32_t trans_a, in
 // train.hip: the steps either side of the convolutions in a training step.
 dfp_status launch_bn_relu_fwd(const dfp_bn_desc& d, const int16_t* y, const dfp_scale* sy, const float* gamma,
                               const float* beta, const float* res, float* z, int16_t* zq, dfp_scale* sz, float* mean,
-                              float* inv_std, int64_t* sums, void* ws, hipStream_t st);
+                              float* inv_std, int64_t* sums, void* ws, size_t ws_bytes, hipStream_t st);
 dfp_status launch_bn_relu_bwd(const dfp_bn_desc& d, const int16_t* dz, const dfp_scale* sdz, const int16_t* y,
                               const dfp_scale* sy, const float* gamma, const float* beta, const float* res,
                               const float* mean, const float* inv_std, float* dy, int16_t* dyq, dfp_scale* sdy,
-                              float* dgamma, float* dbeta, float* dres, int64_t* sums, void* ws, hipStream_t st);
+                              float* dgamma, float* dbeta, float* dres, int64_t* sums, void* ws,
+                              size_t ws_bytes, hipStream_t st);
 size_t bn_workspace_bytes(const dfp_bn_desc& d);
+size_t bn_least_bytes(const dfp_bn_desc& d);  // what calls take at least
 dfp_status launch_sgd_quantize(int64_t n, float lr, float mu, float wd, int32_t bits, int32_t rounding,
                                uint64_t seed, float* w, float* v, const float* dw, int16_t* wq, dfp_scale* sw,
                                hipStream_t st);

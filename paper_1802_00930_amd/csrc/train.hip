@@ -576,19 +576,6 @@ int32_t bn_splits(const dfp_bn_desc& d) {
   return std::max(1, std::min(want, d.n));
 }
 
-// Workspace: the statistics' partial sums (after the finalize kernel, the max
-// pass's partial maxima) and the per-channel values.
-struct BnWs {
-  int64_t* part;
-  float4* kco;
-  int64_t part_bytes;
-};
-BnWs bn_ws(const dfp_bn_desc& d, void* ws) {
-  const int64_t part = ((int64_t)bn_splits(d) * d.c * 24 + 255) / 256 * 256;
-  uint8_t* w = reinterpret_cast<uint8_t*>(ws);
-  return {reinterpret_cast<int64_t*>(w), reinterpret_cast<float4*>(w + part), part};
-}
-
 // Workgroups of a max pass over `groups` groups of four whose per-workgroup
 // maxima have room for `room`; <= 1 means one workgroup writing the scale
 // directly.
@@ -596,6 +583,33 @@ int32_t max_parts(int64_t groups, int64_t room) {
   int64_t parts = (groups + kBlock - 1) / kBlock;
   parts = std::min<int64_t>(std::min<int64_t>(parts, kMaxParts), room);
   return (int32_t)std::max<int64_t>(parts, 1);
+}
+
+// Workspace: the statistics' partial sums, the per-channel values and, where the
+// sums of few images and channels are too little room for them, the max pass's
+// partial maxima; else these follow the sums in the same place once the finalize
+// kernel has read them.  A workspace without that last part (bn_least_bytes) gets
+// as many workgroups as the sums have room for (N = 1, C = 16, hw = 2^20, with a
+// residual forward 190 and backward 497 us, with 128 workgroups 225 and 559).
+struct BnWs {
+  int64_t* part;
+  float4* kco;
+  uint32_t* maxima;
+  int64_t room;  // words at maxima
+};
+int64_t align256(int64_t v) { return (v + 255) / 256 * 256; }
+int64_t bn_part_bytes(const dfp_bn_desc& d) { return align256((int64_t)bn_splits(d) * d.c * 24); }
+int64_t bn_least(const dfp_bn_desc& d) { return bn_part_bytes(d) + align256((int64_t)d.c * 16); }
+int64_t bn_maxima_bytes(const dfp_bn_desc& d) {  // 0: in the sums' place
+  const int64_t b = align256((int64_t)max_parts(((int64_t)d.n * d.c * d.hw + 3) / 4, kMaxParts) * 4);
+  return b > bn_part_bytes(d) ? b : 0;
+}
+BnWs bn_ws(const dfp_bn_desc& d, void* ws, size_t ws_bytes) {
+  const int64_t part = bn_part_bytes(d), least = bn_least(d), maxima = bn_maxima_bytes(d);
+  uint8_t* w = reinterpret_cast<uint8_t*>(ws);
+  const bool own = maxima > 0 && ws_bytes >= (size_t)(least + maxima);
+  return {reinterpret_cast<int64_t*>(w), reinterpret_cast<float4*>(w + part),
+          reinterpret_cast<uint32_t*>(own ? w + least : w), (own ? maxima : part) / 4};
 }
 
 template <bool BWD, bool RES>
@@ -648,8 +662,8 @@ dfp_status with_src(const Elems& e, F f) {
 // Max pass (k_bn_amax + the max reduce) into s.
 template <bool BWD>
 dfp_status launch_max(const Elems& e, float* out, float* dres, const BnWs& w, dfp_scale* s, hipStream_t st) {
-  const int32_t parts = max_parts((e.total + 3) / 4, w.part_bytes / 4);
-  uint32_t* part = parts > 1 ? reinterpret_cast<uint32_t*>(w.part) : nullptr;
+  const int32_t parts = max_parts((e.total + 3) / 4, w.room);
+  uint32_t* part = parts > 1 ? w.maxima : nullptr;
   dfp_status rc = with_src<BWD>(e, [&](auto hw4, auto src) -> dfp_status {
     DFP_LAUNCH(K_BN_AMAX, (k_bn_amax<BWD, decltype(hw4)::value, decltype(src)::value>), dim3((unsigned)parts),
                dim3(kBlock), 0, st, e, out, dres, part, s);
@@ -692,14 +706,13 @@ dfp_status launch_convert(const Elems& e, float* z, int16_t* dst, dfp_scale* s, 
 
 }  // namespace
 
-size_t bn_workspace_bytes(const dfp_bn_desc& d) {
-  return (size_t)(bn_ws(d, nullptr).part_bytes + ((int64_t)d.c * 16 + 255) / 256 * 256);
-}
+size_t bn_workspace_bytes(const dfp_bn_desc& d) { return (size_t)(bn_least(d) + bn_maxima_bytes(d)); }
+size_t bn_least_bytes(const dfp_bn_desc& d) { return (size_t)bn_least(d); }
 
 dfp_status launch_bn_relu_fwd(const dfp_bn_desc& d, const int16_t* y, const dfp_scale* sy, const float* gamma,
                               const float* beta, const float* res, float* z, int16_t* zq, dfp_scale* sz, float* mean,
-                              float* inv_std, int64_t* sums, void* ws, hipStream_t st) {
-  const BnWs w = bn_ws(d, ws);
+                              float* inv_std, int64_t* sums, void* ws, size_t ws_bytes, hipStream_t st) {
+  const BnWs w = bn_ws(d, ws, ws_bytes);
   dfp_status rc;
   if ((rc = launch_stats<false, false>(d, y, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, sy, w, nullptr,
                                        res ? nullptr : sz, st)) != DFP_OK)
@@ -720,8 +733,9 @@ dfp_status launch_bn_relu_fwd(const dfp_bn_desc& d, const int16_t* y, const dfp_
 dfp_status launch_bn_relu_bwd(const dfp_bn_desc& d, const int16_t* dz, const dfp_scale* sdz, const int16_t* y,
                               const dfp_scale* sy, const float* gamma, const float* beta, const float* res,
                               const float* mean, const float* inv_std, float* dy, int16_t* dyq, dfp_scale* sdy,
-                              float* dgamma, float* dbeta, float* dres, int64_t* sums, void* ws, hipStream_t st) {
-  const BnWs w = bn_ws(d, ws);
+                              float* dgamma, float* dbeta, float* dres, int64_t* sums, void* ws,
+                              size_t ws_bytes, hipStream_t st) {
+  const BnWs w = bn_ws(d, ws, ws_bytes);
   dfp_status rc;
   // with a residual the statistics pass leaves the ReLU mask in dyq
   uint8_t* mask = res && d.hw % 4 == 0 ? reinterpret_cast<uint8_t*>(dyq) : nullptr;
