@@ -19,6 +19,7 @@
 // that band.  A lane owning column (c, r, s) then gathers its 16 operand pairs
 // as band[c][offset(t) + r*Wpad + s], which covers padding, strides and image
 // boundaries with no branches.
+#include <atomic>
 #include <type_traits>
 
 #include "band_rows.h"
@@ -2537,11 +2538,23 @@ static RingLayout ring_layout(const Geom& g) {
   return y;
 }
 
+// Allows a kernel the whole LDS of a CU as dynamic shared memory, once per device
+// (allowed: that kernel's devices so far).
+static dfp_status allow_lds(const void* kernel, std::atomic<bool> (&allowed)[64]) {
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess) return DFP_ERR_HIP;
+  const bool known = dev >= 0 && dev < 64;
+  if (known && allowed[dev].load(std::memory_order_relaxed)) return DFP_OK;
+  if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+    return DFP_ERR_HIP;
+  if (known) allowed[dev].store(true, std::memory_order_relaxed);
+  return DFP_OK;
+}
 template <int CL, int NSUB, int RG>
 static dfp_status launch_ring_kernel(const RingLayout& y, const BwdwArgs& args, dim3 grid, hipStream_t st) {
-  static const bool set = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bwdw_ring<CL, NSUB, RG>),
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess;
-  (void)set;
+  static std::atomic<bool> allowed[64];
+  const dfp_status rc = allow_lds(reinterpret_cast<const void*>(&k_bwdw_ring<CL, NSUB, RG>), allowed);
+  if (rc != DFP_OK) return rc;
   DFP_LAUNCH(K_BWDW_MFMA, (k_bwdw_ring<CL, NSUB, RG>), grid, dim3(256 * RG), y.lds, st, args, y.f);
   return DFP_OK;
 }
