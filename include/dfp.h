@@ -388,9 +388,10 @@ typedef struct dfp_bn_desc {
  * S1, S2.  workspace: dfp_bn_workspace_bytes(d) bytes, 256-byte aligned.
  * Without res the output max comes from each channel's smallest and largest
  * integer (z is monotone in i per channel), so the tensor is read twice;
- * with res a max pass over z runs before the rounding pass and uses zq as
- * scratch.  zq, z must not alias y or res.  Pointers to FP32 and INT16
- * tensors 16-byte aligned, scales 16-byte aligned. */
+ * with res a max pass over z runs before the rounding pass and writes z, which
+ * the rounding pass then reads instead of y and res.  zq, z must not alias y or
+ * res, nor each other.  Pointers to FP32 and INT16 tensors 16-byte aligned,
+ * scales 16-byte aligned. */
 dfp_status dfp_bn_relu_fwd(const dfp_bn_desc* d, const int16_t* y, const dfp_scale* sy, const float* gamma,
                            const float* beta, const float* res, float* z, int16_t* zq, dfp_scale* sz,
                            float* mean, float* inv_std, int64_t* sums, void* workspace, size_t ws_bytes,
@@ -399,10 +400,13 @@ dfp_status dfp_bn_relu_fwd(const dfp_bn_desc* d, const int16_t* y, const dfp_sca
 /* Backward of dfp_bn_relu_fwd: dz (INT16 [n][c][hw], exponent sdz->exp) is
  * the gradient at z; y, sy, gamma, beta, res, mean, inv_std as given to and
  * returned by the forward call.  dyq: INT16 Q_e of the gradient at y, scale
- * in sdy (a max pass first, with dyq as scratch).  dy (nullable): the FP32
- * gradient at y.  dgamma, dbeta: FP32 [c].  dres (nullable): the FP32
- * gradient at res (the masked dz').  sums (nullable): int64 [c][2] = D, Pd.
- * workspace as for the forward call. */
+ * in sdy; with res and hw a multiple of 4 it first holds the ReLU mask, written
+ * across the whole buffer by the first pass, which later passes read beside dz
+ * and y.  dy (nullable): the FP32 gradient at y, from which the rounding pass
+ * then reads.  dgamma, dbeta: FP32 [c].  dres (nullable): the FP32 gradient at
+ * res (the masked dz').  sums (nullable): int64 [c][2] = D, Pd.  dyq, dy and dres
+ * must not alias dz, y or res, nor each other.  workspace as for the forward
+ * call. */
 dfp_status dfp_bn_relu_bwd(const dfp_bn_desc* d, const int16_t* dz, const dfp_scale* sdz, const int16_t* y,
                            const dfp_scale* sy, const float* gamma, const float* beta, const float* res,
                            const float* mean, const float* inv_std, float* dy, int16_t* dyq, dfp_scale* sdy,
