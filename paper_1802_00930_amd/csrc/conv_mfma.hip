@@ -2691,6 +2691,73 @@ bool conv_mfma_supported(const Geom& g, int32_t dir) {
   return 16 * wsrc <= kPrepBElems;
 }
 
+// ------------------------------------------------ estimates for the routes
+// Microseconds of the four-waves-per-SIMD and 16x16-tile kernels and of the
+// routes around them, by which the plans choose between routes whose costs grow
+// with different things.  Fitted to 1080 layers (1 to 64 images, 1 to 512
+// channels, 1x1 to 7x7, 4 to 128 pixels wide), each timed on both sides; off by
+// 15 to 25%.  (For a chip of 256 CUs; a plan must not depend on the device.)
+struct PlaneCost {
+  double us;
+  int64_t launches;
+};
+static PlaneCost plane_cost(int64_t NP, int32_t M, int32_t T, int32_t L) {
+  constexpr int64_t cus = 256;
+  const int64_t KB = T / 32, mtiles = (M + kMT - 1) / kMT;
+  const double chunk = L == 8 ? 1.6 : L == 16 ? 1.0 : L == 32 ? 0.55 : 0.35;  // conversions per block of 32
+  const bool s16 = use_s16(NP, M, (int32_t)mtiles * kMT, (int32_t)KB, false, cus);
+  // tiles a wave takes one after another, and the workgroups' rounds over the chip
+  const int64_t slices = s16 ? (M + kS16Rows - 1) / kS16Rows : mtiles;
+  const int64_t tiles = s16 ? (NP + 15) / 16 : 2 * ((NP + 31) / 32);
+  const int64_t gx = std::max<int64_t>(1, std::min(cus / slices, s16 ? (NP + 127) / 128 : (tiles + kWaves16 - 1) / kWaves16));
+  const int64_t per_wave = (tiles + gx * kWaves16 - 1) / (gx * kWaves16) * ((gx * slices + cus - 1) / cus);
+  return {(s16 ? 0.29 : 0.72) * chunk * (double)(KB * per_wave),
+          s16 ? (KB + kS16MaxKB - 1) / kS16MaxKB : (KB + kW16MaxKB - 1) / kW16MaxKB};
+}
+// The general kernels, whose tiles of 64 x 128 outputs are chains over the
+// reduction: us per block of 32 for as many tiles as run at once.
+static double tile_chain_us(int64_t NP, int32_t M, int64_t KB, double block) {
+  const double tiles = (double)((NP + kNT - 1) / kNT * ((M + kMT - 1) / kMT));
+  return block * (double)KB * std::max(1.0, tiles / 300);
+}
+// Chunks of 16 or 8 over channels in whole groups of 16: the masked kernel on
+// the plain layout, or the four-waves-per-SIMD kernel on the unfolded operand, T
+// / Tu indices a pixel.  Unfolding costs its R S-fold traffic, and gathers with
+// few workgroups where the rows are few.  Masked / unfolded: 32 -> 64 channels 3x3
+// on 112 x 112, N = 64, L = 16, 282 / 382 us; backward-data of 48 -> 176 7x7 on 35 x
+// 35, N = 36, 502 / 762; but 16 -> 256 3x3 stride 2 on 7 x 7 14.5 / 10.1, and
+// backward-data of 16 -> 368 1x1 on 17 x 93, N = 8, 67 / 28.  (Of 658 such layers 139
+// were more than 5% slower unfolded, 30 are by this rule.)
+static bool unfold_pays(const ConvMfmaPlan& p, int32_t n, int32_t L, int32_t Wsrc) {
+  const int64_t NP = (int64_t)n * p.Po * p.Qo;
+  const PlaneCost main = plane_cost(NP, p.M, p.Tu, L);
+  // steps of a thread in the preparations, one workgroup per row
+  const double unfold = (double)(((int64_t)p.Tu / 16 * p.Qo + 255) / 256) * std::max(1.0, (double)n * p.Po / 1800);
+  const double plain = (double)(((int64_t)p.CG * 16 * Wsrc / (Wsrc % 8 == 0 ? 8 : 1) + 255) / 256) *
+                       std::max(1.0, (double)n * p.Hp / 2000);
+  const double unfolded = 6.2 + 1.45 * unfold + main.us + 10.7 * (double)(main.launches - 1) +
+                          0.81e-6 * (double)NP * p.Tu +
+                          2.8 * std::min(p.M, 256) / 64 * std::min(1.0, (double)NP / 2000);
+  const double masked = 7.8 + (Wsrc % 8 == 0 ? 1.0 : 0.3) * plain +
+                        tile_chain_us(NP, p.M, p.KB, L == 8 ? 2.4 : 1.35) + 0.2e-6 * (double)NP * p.KB * 32;
+  return unfolded < masked;
+}
+
+// Whether a layer in the plane layout whose filter has more than kW16MaxKB blocks
+// takes the four-waves-per-SIMD kernels: phases pay their fixed cost once each,
+// so only when there are at least as many 16 x 16 (32 x 32) output tiles per
+// workgroup as it has waves, in each phase.  (Below L = 32 always: the masked
+// kernel is always slower.)
+static bool plane_phases_ok(int64_t NP, int32_t M, int32_t Mp, int32_t KB, int32_t L, bool partials, int cus) {
+  if (KB <= kW16MaxKB || L < 32) return true;
+  if (use_s16(NP, M, Mp, KB, partials, cus)) {
+    const int64_t gx = std::max<int64_t>(1, cus / ((M + kS16Rows - 1) / kS16Rows));
+    return 2 * ((NP + 15) / 16) >= gx * kWaves16 || KB <= kS16MaxKB;
+  }
+  const int64_t gx = std::max<int64_t>(1, cus / (Mp / kMT));
+  return 2 * ((NP + 31) / 32) >= gx * kWaves16;
+}
+
 // Workspace layout of the forward / backward-data MFMA path.
 ConvMfmaPlan plan_conv_mfma(const Geom& g, int32_t dir, bool unfold) {
   ConvMfmaPlan p{};
@@ -2725,7 +2792,8 @@ ConvMfmaPlan plan_conv_mfma(const Geom& g, int32_t dir, bool unfold) {
   if (!unfold || conv_w16_eligible(p.Cin, p.T, g.L, false) || !conv_w16_eligible(p.Tu, p.Tu, g.L, false) ||
       !(p.Cin % 16 != 0 || g.L < 32) || g.n >= 65535 || (int64_t)g.n * p.Po * p.Qo * p.Tu * 2 > ((int64_t)1 << 30) ||
       (int64_t)g.n * p.Po * p.Qo * p.M >= ((int64_t)1 << 31) || (int64_t)p.Mp * p.Tu >= ((int64_t)1 << 30) ||
-      (int64_t)(fwd ? g.h : g.p) * (fwd ? g.w : g.q) >= ((int64_t)1 << 31))  // (an offset in a source plane: 32 bits)
+      (int64_t)(fwd ? g.h : g.p) * (fwd ? g.w : g.q) >= ((int64_t)1 << 31) ||  // (an offset in a source plane: 32 bits)
+      (p.Cin % 16 == 0 && !unfold_pays(p, g.n, g.L, fwd ? g.w : g.q)))
     p.Tu = 0;
   const int32_t KB = std::max(p.KB, p.Tu / 32);
   p.ws_a_bytes = align256((int64_t)KB * p.Mp * 2 * 32);
@@ -2749,21 +2817,8 @@ dfp_status launch_conv_mfma(int32_t dir, const Geom& g, const int16_t* a, const 
   const int32_t tap_row_bytes = rsign * p.Wp * p.CG * 32, tap_col_bytes = rsign * p.CG * 32;
   bool plane = conv_w16_eligible(p.Cin, p.T, g.L, i32) && (int64_t)g.n * p.Po * p.Qo * p.M < (1ll << 31) &&
                p.ws_b_bytes < (1ll << 31);
-  if (plane && p.KB > kW16MaxKB && !prefer_w16 && g.L >= 32) {
-    // (shorter chunks would run the masked kernel, which is always slower)
-    // phases pay the kernel's fixed cost once each: taken only when there are
-    // at least as many 16 x 16 (32 x 32) output tiles per workgroup as it has
-    // waves, in each phase
-    const int cus = device_cus();
-    const int64_t NP = (int64_t)g.n * p.Po * p.Qo;
-    if (use_s16(NP, p.M, p.Mp, p.KB, partials != nullptr, cus)) {
-      const int64_t gx = std::max<int64_t>(1, cus / ((p.M + kS16Rows - 1) / kS16Rows));
-      plane = 2 * ((NP + 15) / 16) >= gx * kWaves16 || p.KB <= kS16MaxKB;
-    } else {
-      const int64_t gx = std::max<int64_t>(1, cus / (p.Mp / kMT));
-      plane = 2 * ((NP + 31) / 32) >= gx * kWaves16;
-    }
-  }
+  if (plane && !prefer_w16)
+    plane = plane_phases_ok((int64_t)g.n * p.Po * p.Qo, p.M, p.Mp, p.KB, g.L, partials != nullptr, device_cus());
   // the filter preparation clears so (unless a previous launch of the same
   // output has already raised it) before the main kernel raises it
   const PrepAArgs pa{b, wsa, p.M, p.Mp, p.Cin, g.r, g.s, p.T, p.KB, fwd ? 0 : 1, g.c, so_reset ? so : nullptr, boff,
