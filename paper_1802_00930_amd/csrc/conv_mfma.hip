@@ -3253,14 +3253,43 @@ __global__ __launch_bounds__(256) void k_scatter_phase(const float* __restrict__
 
 }  // namespace
 
+// Chunks below 64: the output phases, each with a gather of its filter taps, a
+// preparation and a scatter, or one pass over the zero-dilated dy, which the
+// four-waves-per-SIMD (shared-ring) kernels take as well.  The phases save three
+// quarters of the products at stride 2 and cost about 45 us before any of them.
+// 3x3 stride 2, dilated / phases: 128 -> 128 on 28 x 28, N = 8, L = 32, 20 / 57
+// us; 512 -> 64 on 14 x 14, N = 32, 24 / 91; 256 -> 512 on 56 x 56, N = 32, 580 /
+// 341.  (Of 423 such layers 215 were slower in phases, 13 are by this rule.)
+static PlaneCost phase_cost(int64_t NP, int32_t M, int32_t T, int32_t L, double ring_us) {
+  if (plane_phases_ok(NP, M, (M + kMT - 1) / kMT * kMT, T / 32, L, false, 256)) return plane_cost(NP, M, T, L);
+  return {ring_us + tile_chain_us(NP, M, T / 32, 0.69), 0};  // the shared-ring kernel
+}
+static bool phases_pay(const Geom& g, double phases_us, int64_t phases, int64_t launches) {
+  const int64_t NP = (int64_t)g.n * g.h * g.w, T = (int64_t)g.k * g.r * g.s;
+  const double filter = 1e-6 * (double)T * g.c;
+  const double split = phases_us + 11.0 * (double)phases + 6.0 * (double)(launches - phases) + 22 * filter +
+                       4e-6 * (double)NP * g.c + 4e-6 * (double)g.n * g.p * g.q * g.k;
+  const PlaneCost main = phase_cost(NP, g.c, (int32_t)T, g.L, 7);
+  const double dilated =
+      (main.launches ? 1.15 : 1.0) * main.us + 9.5 * (double)main.launches + 1.2e-6 * (double)NP * g.k +
+      1e-6 * (double)NP * g.c + 12 * filter;
+  return split < dilated;
+}
+
 int64_t conv_bwd_data_phase_bytes(const Geom& g) {
   if ((g.sh == 1 && g.sw == 1) || g.L < 1 || g.k % g.L != 0 || conv_bwd_data_sub_bytes(g) > 0) return 0;
   // k_scatter_phase indexes a plane (and sizes its grid) with 32 bits
   if ((int64_t)g.h * g.w >= (1ll << 31) - 256) return 0;
   int64_t conv = 0, wsub = 0, out = 0;
+  double us = 0;
+  int64_t phases = 0, launches = 0;
   for (int32_t idx = 0; idx < g.sh * g.sw; ++idx) {
     const Phase f = phase_of(g, idx);
     if (f.empty) continue;
+    const PlaneCost one = phase_cost((int64_t)g.n * f.g.h * f.g.w, g.c, g.k * f.g.r * f.g.s, g.L, 3);
+    us += one.us;
+    ++phases;
+    launches += std::max<int64_t>(one.launches, 1);
     // every phase on the plane-layout kernels, whose preparation takes any
     // padding; a 1x1 phase without padding must cover dy exactly (the 1x1
     // route reads its input with the output's pixel count)
@@ -3272,7 +3301,8 @@ int64_t conv_bwd_data_phase_bytes(const Geom& g) {
     wsub = std::max(wsub, align256((int64_t)g.k * g.c * f.g.r * f.g.s * 2));
     out = std::max(out, align256((int64_t)g.n * g.c * f.g.h * f.g.w * 4));
   }
-  return conv > 0 ? conv + wsub + out : 0;
+  if (conv == 0 || (g.L < 64 && !phases_pay(g, us, phases, launches))) return 0;
+  return conv + wsub + out;
 }
 
 dfp_status launch_conv_bwd_data_phases(const Geom& g, const int16_t* dy, const dfp_scale* sdy, const int16_t* w,

@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
     (3, 20, 9, 11, 24, 1, 1, 2, 0, 64, dfp.FWD, 23552),
     (2, 40, 9, 9, 24, 1, 1, 2, 0, 64, dfp.BWD_DATA, 15872),     # on the unit-stride grid
     (1, 88, 14, 14, 90, 3, 3, 1, 1, 32, dfp.BWD_DATA, 262400),
-    (2, 256, 14, 14, 32, 3, 3, 2, 1, 16, dfp.BWD_DATA, 180480)])  # output phases
+    (4, 512, 56, 56, 128, 3, 3, 2, 1, 8, dfp.BWD_DATA, 4624896)])  # output phases
 def test_least_workspace(n, c, h, w, k, r, s, st, pd, L, direction, least):
     gl = GpuLayer(n, c, h, w, k, r, s, st, pd, L=L)
     assert dfp.workspace_bytes(gl.d, direction) > least

@@ -1,6 +1,6 @@
 """Which route forward and backward-data take, by the workspace they ask for (no
-GPU): layers measured faster with the unfolded operand ask for more than the
-general kernels', layers measured slower do not."""
+GPU): layers measured faster with the unfolded operand or the output phases ask
+for more than the general kernels', layers measured slower do not."""
 import pytest
 
 from paper_1802_00930_amd import build, dfp
@@ -33,3 +33,12 @@ def test_unfolded_operand(layer, direction, general, unfolded):
     plain = need(*layer[:-1], 24, direction)
     assert (need(*layer, direction) > plain) == (unfolded < general)
 
+
+# us of backward-data: one dilated pass / output phases
+@pytest.mark.parametrize("layer,dilated,phases", [
+    ((8, 128, 28, 28, 128, 3, 2, 1, 32), 20, 57), ((32, 512, 14, 14, 64, 3, 2, 1, 32), 24, 91),
+    ((8, 512, 28, 28, 64, 3, 2, 1, 16), 33, 74), ((1, 512, 14, 14, 64, 3, 2, 1, 8), 45, 55),
+    ((32, 512, 56, 56, 64, 5, 2, 2, 8), 1192, 587), ((32, 512, 56, 56, 64, 5, 2, 2, 32), 409, 323)])
+def test_output_phases(layer, dilated, phases):
+    plain = need(*layer[:-1], 24, dfp.BWD_DATA)
+    assert (need(*layer, dfp.BWD_DATA) > plain) == (phases < dilated)
