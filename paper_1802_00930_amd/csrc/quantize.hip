@@ -399,6 +399,10 @@ __global__ __launch_bounds__(kBlock) void k_i32_convert(const int32_t* __restric
 // workgroup reports to the one scale at about the same time, and atomics on one
 // address queue: 1000 x 2048 in blocks of 128 took 16-18 us with 1024 workgroups of
 // 4 waves and two atomics each, 9 us with one workgroup of 16 waves per CU and one.
+// Hence at most 256 workgroups, of as few waves (1 to 16) as give every wave its
+// blocks in one round: few large blocks are few waves, each a chain over its block,
+// and belong on a CU each (64 blocks of 65536: 90 us in workgroups of 4 waves, 293
+// of 16, 75 of one).
 // s->flags starts at ZERO_TENSOR (k_blocked_init); the workgroup whose max is
 // the first above zero clears it.
 constexpr int kBlockedThreads = 1024;
@@ -411,7 +415,7 @@ __global__ void k_blocked_init(dfp_scale* s) {
   }
 }
 
-template <int MODE, bool SAT, bool VEC4>
+template <int MODE, bool SAT, bool VEC4, bool KEEP>
 __global__ __launch_bounds__(kBlockedThreads) void k_quant_blocked(
     const float* __restrict__ src, int16_t* __restrict__ dst, int8_t* __restrict__ exps, int64_t rows, int64_t cols,
     int64_t B, int64_t nb, dfp_scale* s, int32_t bits, uint32_t key0, uint32_t key1, uint32_t role, int32_t seg_log2,
@@ -422,10 +426,11 @@ __global__ __launch_bounds__(kBlockedThreads) void k_quant_blocked(
   const int S = 1 << seg_log2;
   const int sl = lane & (S - 1);
   const int64_t nblk = rows * nb;
-  const int64_t stride = ((int64_t)gridDim.x * (kBlockedThreads / 64)) << (6 - seg_log2);
+  const int32_t wg_waves = blockDim.x >> 6;
+  const int64_t stride = ((int64_t)gridDim.x * wg_waves) << (6 - seg_log2);
   uint32_t wmax = 0u;
   bool f_nonfinite = false, f_clamped = false, f_sat = false;
-  for (int64_t wave_first = ((int64_t)blockIdx.x * (kBlockedThreads / 64) + (threadIdx.x >> 6)) << (6 - seg_log2);
+  for (int64_t wave_first = ((int64_t)blockIdx.x * wg_waves + (threadIdx.x >> 6)) << (6 - seg_log2);
        wave_first < nblk; wave_first += stride) {  // uniform per wave
     const int64_t blk = wave_first + (lane >> seg_log2);
     const bool valid = blk < nblk;
@@ -439,11 +444,14 @@ __global__ __launch_bounds__(kBlockedThreads) void k_quant_blocked(
     uint4 first = make_uint4(0u, 0u, 0u, 0u);  // this lane's first group
     if (VEC4) {
       int64_t c = c0 + 4 * sl;
-      if (c < c1) {
-        first = *reinterpret_cast<const uint4*>(s32 + c);
-        mb = abs_max4(first);
+      if (KEEP) {
+        if (c < c1) {
+          first = *reinterpret_cast<const uint4*>(s32 + c);
+          mb = abs_max4(first);
+        }
+        c += 4 * S;
       }
-      for (c += 4 * S; c < c1; c += 4 * S) {
+      for (; c < c1; c += 4 * S) {
         const uint4 v = *reinterpret_cast<const uint4*>(s32 + c);
         mb = max(mb, max(max(v.x & 0x7fffffffu, v.y & 0x7fffffffu), max(v.z & 0x7fffffffu, v.w & 0x7fffffffu)));
       }
@@ -475,7 +483,7 @@ __global__ __launch_bounds__(kBlockedThreads) void k_quant_blocked(
     };
     if (VEC4) {
       for (int64_t c = c0 + 4 * sl; c < c1; c += 4 * S) {
-        const uint4 v = c == c0 + 4 * sl ? first : *reinterpret_cast<const uint4*>(s32 + c);
+        const uint4 v = KEEP && c == c0 + 4 * sl ? first : *reinterpret_cast<const uint4*>(s32 + c);
         const uint64_t g = (uint64_t)(base + c) >> 2;
         uint4 rw = make_uint4(0u, 0u, 0u, 0u);
         if (MODE == DFP_ROUND_STOCHASTIC)
@@ -518,7 +526,7 @@ __global__ __launch_bounds__(kBlockedThreads) void k_quant_blocked(
   __syncthreads();
   if (threadIdx.x == 0) {
     uint32_t m = red_max[0], f = red_flags[0];
-    for (int i = 1; i < kBlockedThreads / 64; ++i) {
+    for (int i = 1; i < wg_waves; ++i) {
       m = max(m, red_max[i]);
       f |= red_flags[i];
     }
@@ -547,15 +555,18 @@ static dfp_status launch_blocked_mode(const float* src, int16_t* dst, int8_t* ex
   int32_t seg_log2 = 0;
   while (seg_log2 < 6 && ((int64_t)1 << seg_log2) < lanes) ++seg_log2;
   const int64_t waves = (rows * nb + (64 >> seg_log2) - 1) >> (6 - seg_log2);
-  // one workgroup of 16 waves per CU: each reports once, so the scale sees few atomics
-  const dim3 grid((unsigned)std::min<int64_t>(256, (waves + kBlockedThreads / 64 - 1) / (kBlockedThreads / 64)));
+  const int64_t wg_waves = std::min<int64_t>(kBlockedThreads / 64, (waves + 255) / 256);
+  const dim3 grid((unsigned)std::min<int64_t>(256, (waves + wg_waves - 1) / wg_waves)), block((unsigned)(64 * wg_waves));
   const FastDiv nb_div = rows * nb < ((int64_t)1 << 32) ? make_fastdiv((uint32_t)nb) : FastDiv{0u, 64u};
-  if (vec4)
-    DFP_LAUNCH(K_QUANT_BLOCKED, (k_quant_blocked<MODE, SAT, true>), grid, dim3(kBlockedThreads), 0, st, src, dst,
-               exps, rows, cols, B, nb, s, bits, k0, k1, role, seg_log2, nb_div);
-  else
-    DFP_LAUNCH(K_QUANT_BLOCKED, (k_quant_blocked<MODE, SAT, false>), grid, dim3(kBlockedThreads), 0, st, src, dst,
-               exps, rows, cols, B, nb, s, bits, k0, k1, role, seg_log2, nb_div);
+#define DFP_QB(VEC4, KEEP)                                                                                          \
+  DFP_LAUNCH(K_QUANT_BLOCKED, (k_quant_blocked<MODE, SAT, VEC4, KEEP>), grid, block, 0, st, src, dst, exps, rows, \
+             cols, B, nb, s, bits, k0, k1, role, seg_log2, nb_div)
+  // (keeping the first group costs the long loops their unrolling: 5000 x 2048 in
+  // one block a row 22 us without it, 26 with)
+  if (vec4 && B <= ((int64_t)8 << seg_log2)) DFP_QB(true, true);
+  else if (vec4) DFP_QB(true, false);
+  else DFP_QB(false, false);
+#undef DFP_QB
   return DFP_OK;
 }
 
