@@ -112,8 +112,9 @@ typedef enum dfp_direction { DFP_FWD = 0, DFP_BWD_DATA = 1, DFP_BWD_WT = 2 } dfp
  * four-waves-per-SIMD kernel in phases only when the layer has enough output
  * pixels), MFMA takes that kernel whenever its operand layout fits.  P = 16
  * convolutions take the matrix cores too when they are given a workspace of
- * dfp_workspace_bytes (without one, or recording partials, the VALU kernels);
- * operands with integers above 32639 are recomputed on the VALU on the device. */
+ * dfp_workspace_bytes (without one, or recording partials, the VALU kernels, and
+ * under AUTO also where a small layer is estimated to be faster there); operands
+ * with integers above 32639 are recomputed on the VALU on the device. */
 typedef enum dfp_path {
   DFP_PATH_AUTO = 0, /* byte-split int8 MFMA, kernel by shape and work size     */
   DFP_PATH_MFMA = 1, /* byte-split int8 MFMA, four-waves-per-SIMD kernel first  */

@@ -2,6 +2,7 @@
 // runs before the first HIP call, so an invalid call enqueues nothing.
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <mutex>
 #include <vector>
 
@@ -189,6 +190,37 @@ dfp_status ws_check(const Route& r, const void* ws, size_t ws_bytes) {
   return DFP_ERR_WORKSPACE;
 }
 
+// P = 16, path AUTO: whether a small layer keeps the VALU kernel, one launch and a
+// chain over the reduction per output, where the matrix cores take three or more
+// launches and a pass over the operands first.  Estimates in us, fitted to 500
+// layers of up to 4e8 products on both sides (off by 20%): on the VALU 250, 230
+// and 85 of them were more than 5% faster forward, backward-data and
+// backward-weights; 16 -> 16 channels 1x1 on 7 x 7, backward-weights, L = 16,
+// 9 us on the VALU and 13.5; 8 -> 8 7x7 on 4 x 4, N = 4, L = 7, forward 43 and 97;
+// but 256 -> 256 3x3 on 14 x 14, N = 32, L = 16, 5950 us a layer step and 300.
+bool p16_valu_pays(const Geom& g, int32_t dir, bool i32) {
+  const double T = (double)reduction_len(g, dir), L = i32 ? 32.0 * std::ceil(T / 32) : (double)g.L;
+  const int32_t M = dir == DFP_BWD_DATA ? g.c : g.k, Cin = dir == DFP_FWD ? g.c : g.k;
+  const double cols = dir == DFP_FWD        ? (double)g.n * g.p * g.q
+                      : dir == DFP_BWD_DATA ? (double)g.n * g.h * g.w
+                                            : (double)g.c * g.r * g.s;
+  const double tiles = std::ceil(cols / 128) * std::ceil(M / 64.0), KB = std::ceil(T / 32);
+  const bool planes = g.L == 64 || g.L == 32 || g.L == 16 || g.L == 8;
+  const double ends = std::min(32.0 / L, 32.0);  // chunk ends per block of 32
+  if (dir == DFP_BWD_WT) {
+    const double valu = 4.5 + 0.134 * T * std::max(1.0, cols * M / 1.83e5);
+    const double mfma = 15.6 + (planes ? 0.4 : 1.3 + 0.64 * ends) * std::min(KB, 128.0) *
+                                   std::max(1.0, tiles * std::ceil(T / 4096) / 300) +
+                        2.1e-6 * ((double)role_numel(g, DFP_ROLE_X) + role_numel(g, DFP_ROLE_DY));
+    return valu < 0.93 * mfma;
+  }
+  const double valu = 8.8 + 0.114 * T * std::max(1.0, cols * M / 2.3e5);
+  const bool whole = Cin % 16 == 0, unmasked = std::fmod(L, 32) == 0;
+  const double block = planes && !i32 ? 0.63 : whole ? (unmasked ? 0.5 : 0.6 + 0.52 * ends) : 4.7 + 0.46 * ends;
+  const double mfma = (planes && !i32 ? 15.6 : 11.5) + block * KB * std::max(1.0, tiles / 300) + 1e-6 * cols * T;
+  return valu < mfma;
+}
+
 // GEMM descriptor and flat-tensor checks.
 dfp_status gemm_desc_check(const dfp_gemm_desc* d) {
   if (!d) return DFP_ERR_NULL;
@@ -332,7 +364,8 @@ static dfp_status conv_run(int32_t dir, const dfp_desc* d, const Geom& g, const 
                            void* ws, size_t ws_bytes, int32_t* partials, hipStream_t st, bool i32) {
   const bool room = ws_holds(r.ws_bytes, ws, ws_bytes);
   // (calls whose workspace is optional record partials on the VALU)
-  if (r.mfma && (!r.optional_ws || (room && !partials))) {
+  const bool valu = d->bits == 16 && d->path == DFP_PATH_AUTO && p16_valu_pays(g, dir, i32);
+  if (r.mfma && !valu && (!r.optional_ws || (room && !partials))) {
     if (d->bits == 16) return conv_p16(dir, g, r, d->path, a, sa, b, sb, out, so, ws, st, i32);
     return conv_mfma(dir, g, r, d->path, a, sa, b, sb, out, so, ws, room, partials, st, i32);
   }
