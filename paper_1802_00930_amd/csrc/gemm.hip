@@ -409,10 +409,10 @@ template <int RT, bool BLOCKED>
 static dfp_status launch_split(const SplitArgs& a, bool araw, bool braw, hipStream_t st) {
   const dim3 grid((unsigned)((a.n + 15) / 16), (unsigned)((a.m + 16 * RT - 1) / (16 * RT))), block(64 * kSplitWaves);
   const int kid = BLOCKED ? K_GEMM_BLOCKED : K_GEMM;
-  if (BLOCKED || (araw && braw)) DFP_LAUNCH(kid, (k_gemm_split<RT, true, true, BLOCKED>), grid, block, 0, st, a);
-  else if (araw) DFP_LAUNCH(kid, (k_gemm_split<RT, true, false, false>), grid, block, 0, st, a);
-  else if (braw) DFP_LAUNCH(kid, (k_gemm_split<RT, false, true, false>), grid, block, 0, st, a);
-  else DFP_LAUNCH(kid, (k_gemm_split<RT, false, false, false>), grid, block, 0, st, a);
+  if (araw && braw) DFP_LAUNCH(kid, (k_gemm_split<RT, true, true, BLOCKED>), grid, block, 0, st, a);
+  else if (araw) DFP_LAUNCH(kid, (k_gemm_split<RT, true, false, BLOCKED>), grid, block, 0, st, a);
+  else if (braw) DFP_LAUNCH(kid, (k_gemm_split<RT, false, true, BLOCKED>), grid, block, 0, st, a);
+  else DFP_LAUNCH(kid, (k_gemm_split<RT, false, false, BLOCKED>), grid, block, 0, st, a);
   return DFP_OK;
 }
 
@@ -425,7 +425,9 @@ dfp_status launch_gemm_mfma(int32_t m, int32_t n, int32_t k, int32_t trans_a, in
   uint8_t* xs = wsa + p.a_bytes;
   int2* boff = reinterpret_cast<int2*>(xs + p.b_bytes);
   const int32_t rt = split_rt(m, n, k, L, partials != nullptr);
-  const bool araw = rt && !trans_a, braw = rt && trans_b;  // read as INT16, no preparation
+  // read as INT16, no preparation: the reduction contiguous and every row 4-byte aligned
+  auto rows_aligned = [&](const int16_t* x) { return k % 2 == 0 && (reinterpret_cast<uintptr_t>(x) & 3) == 0; };
+  const bool araw = rt && !trans_a && rows_aligned(a), braw = rt && trans_b && rows_aligned(b);
   if (araw && braw) {
     if (so) {
       const dfp_status rc = launch_scale_reset(so, st);
@@ -444,9 +446,9 @@ dfp_status launch_gemm_mfma(int32_t m, int32_t n, int32_t k, int32_t trans_a, in
   if (rt) {
     const SplitArgs sp{a, b, wsa, xs, sa, sb, exa, exb, d, so, m, n, k, L, (k + L - 1) / L, p.Mp, p.G16, bk};
     if (exa)
-      return rt == 1   ? launch_split<1, true>(sp, true, true, st)
-             : rt == 2 ? launch_split<2, true>(sp, true, true, st)
-                       : launch_split<4, true>(sp, true, true, st);
+      return rt == 1   ? launch_split<1, true>(sp, araw, braw, st)
+             : rt == 2 ? launch_split<2, true>(sp, araw, braw, st)
+                       : launch_split<4, true>(sp, araw, braw, st);
     return rt == 1   ? launch_split<1, false>(sp, araw, braw, st)
            : rt == 2 ? launch_split<2, false>(sp, araw, braw, st)
                      : launch_split<4, false>(sp, araw, braw, st);
