@@ -10,6 +10,7 @@
 // a multiple of 32) and runs the convolution's main kernels on them.  The
 // VALU kernel below serves P = 16 and path = VALU.
 #include <algorithm>
+#include <cmath>
 
 #include "dfp_internal.h"
 #include "conv_mfma.h"
@@ -396,13 +397,30 @@ GemmPlan plan_gemm(int32_t m, int32_t n, int32_t k) {
 // while the 16 x 16 tiles are few (252: 11.8 / 12.0 / 17.0 us for 1 / 2 / 4),
 // more where they are many, since each workgroup re-reads its operands (512:
 // 17.7 / 15.6 / 17.1; 1008: 27 / 21 / 19).
-static int32_t split_rt(int32_t m, int32_t n, int32_t k, int32_t L, bool partials) {
-  const int64_t J = ((int64_t)k + L - 1) / L;
-  const int64_t tiles = (int64_t)((m + 63) / 64) * ((n + 127) / 128);
-  if (partials || (L != 32 && L % 64 != 0) || J < 2 || tiles > 96) return 0;
+// Between them by estimates in us, fitted to 450 products (1 to 5800 rows, 2 to
+// 8200 columns, k to 10000) on both sides, off by 7% tiled and 20% split: few
+// chunks leave most of a split workgroup's 16 waves idle, and Blocked-DFP
+// gathers a chunk's exponents per output (533 x 1046 x 64 at L = 32 10.8 us tiled
+// and 15.9 split, blocked 11.3 and 35).
+static int32_t split_rt(int32_t m, int32_t n) {
   const int64_t t16 = (int64_t)((m + 15) / 16) * ((n + 15) / 16);
   const int32_t rt = t16 <= 320 ? 1 : t16 <= 600 ? 2 : 4;
   return m <= 16 ? 1 : m <= 32 ? std::min(rt, 2) : rt;
+}
+// araw, braw: the operand would be read as INT16.
+static bool split_pays(int32_t m, int32_t n, int32_t k, int32_t L, int32_t rt, bool blocked, bool araw, bool braw) {
+  const int64_t J = ((int64_t)k + L - 1) / L;
+  const int64_t tiles = (int64_t)((m + 63) / 64) * ((n + 127) / 128);
+  if ((L != 32 && L % 64 != 0) || J < 2 || tiles > 96) return false;
+  const double KB = (k + 31) / 32, A = 1e-6 * (double)m * k, B = 1e-6 * (double)n * k, D = 1e-6 * (double)m * n;
+  const double wgs = (double)((n + 15) / 16) * ((m + 16 * rt - 1) / (16 * rt));
+  const double rounds = (double)((J + kSplitWaves - 1) / kSplitWaves) * std::max(1.0, wgs / 110);
+  const double groups = std::max(1, L / 64) * std::sqrt((double)rt);
+  const double prep = (araw ? 0 : A) + (braw ? 0 : B);
+  const double tiled = blocked ? 7.5 + 0.73 * KB + 1.9 * (A + B) + 3.6 * D : 7.4 + 0.62 * KB + 1.7 * (A + B) + 4.3 * D;
+  const double split = blocked ? 7.1 + rounds * (0.29 + groups) + 0.5 * prep + 1.7 * wgs / 256 * rt
+                               : 7.5 + rounds * (0.83 + 0.42 * groups) + prep + 0.09 * wgs / 256 * rt;
+  return split < tiled;
 }
 
 template <int RT, bool BLOCKED>
@@ -424,10 +442,17 @@ dfp_status launch_gemm_mfma(int32_t m, int32_t n, int32_t k, int32_t trans_a, in
   uint8_t* wsa = reinterpret_cast<uint8_t*>(ws);
   uint8_t* xs = wsa + p.a_bytes;
   int2* boff = reinterpret_cast<int2*>(xs + p.b_bytes);
-  const int32_t rt = split_rt(m, n, k, L, partials != nullptr);
-  // read as INT16, no preparation: the reduction contiguous and every row 4-byte aligned
-  auto rows_aligned = [&](const int16_t* x) { return k % 2 == 0 && (reinterpret_cast<uintptr_t>(x) & 3) == 0; };
-  const bool araw = rt && !trans_a && rows_aligned(a), braw = rt && trans_b && rows_aligned(b);
+  // Split kernel: an operand whose reduction is contiguous is read as INT16, with
+  // no preparation, where every row is 4-byte aligned or, since unaligned loads
+  // split, one workgroup reads it (1 x 2934 x 9175 33 us so and 68 prepared; 37 x 80
+  // x 7999, whose operands 5 and 3 workgroups read, 56 and 14).
+  int32_t rt = split_rt(m, n);
+  auto aligned_rows = [&](const int16_t* x) { return k % 2 == 0 && (reinterpret_cast<uintptr_t>(x) & 3) == 0; };
+  bool araw = !trans_a && (aligned_rows(a) || n <= 16), braw = trans_b && (aligned_rows(b) || m <= 16 * rt);
+  if (partials || !split_pays(m, n, k, L, rt, exa != nullptr, araw, braw)) {
+    rt = 0;
+    araw = braw = false;
+  }
   if (araw && braw) {
     if (so) {
       const dfp_status rc = launch_scale_reset(so, st);
