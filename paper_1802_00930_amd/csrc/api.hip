@@ -236,7 +236,8 @@ dfp_status gemm_desc_check(const dfp_gemm_desc* d) {
 bool gemm_use_mfma(const dfp_gemm_desc* d) {
   // grid rows of 64-row tiles must fit a launch dimension; reductions of 2^30 and
   // more are beyond the kernels' 32-bit offsets into a column and chunk positions
-  return d->path != DFP_PATH_VALU && d->bits == 15 && (d->m + 63) / 64 <= 65535 && d->k < (1 << 30);
+  return d->path != DFP_PATH_VALU && d->bits == 15 && ((int64_t)d->m + 63) / 64 <= 65535 &&
+         d->k < (1 << 30);
 }
 // Blocked-DFP GEMM on matrix cores: P = 15, chunks of whole 32-blocks, the
 // workgroup's exponent tables small enough for LDS, 32-bit output indices.
