@@ -214,7 +214,8 @@ bool p16_valu_pays(const Geom& g, int32_t dir, bool i32) {
                         2.1e-6 * ((double)role_numel(g, DFP_ROLE_X) + role_numel(g, DFP_ROLE_DY));
     return valu < 0.93 * mfma;
   }
-  const double valu = 8.8 + 0.114 * T * std::max(1.0, cols * M / 2.3e5);
+  // (an output's indices and store, besides its products, count where outputs are many)
+  const double valu = 8.8 + 0.114 * T * std::max(1.0, cols * M / 2.3e5) + 4e-6 * cols * M;
   const bool whole = Cin % 16 == 0, unmasked = std::fmod(L, 32) == 0;
   const double block = planes && !i32 ? 0.63 : whole ? (unmasked ? 0.5 : 0.6 + 0.52 * ends) : 4.7 + 0.46 * ends;
   const double mfma = (planes && !i32 ? 15.6 : 11.5) + block * KB * std::max(1.0, tiles / 300) + 1e-6 * cols * T;
