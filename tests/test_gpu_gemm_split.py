@@ -1,8 +1,8 @@
 """Split-chunk GEMM (small outputs, no partials) against the oracle: both
 operands raw, either or both prepared (the four transpose settings), reductions
 of one lane piece to several rounds of 16 chunks and ends inside a piece, odd
-row strides, 1 / 2 / 4 row subtiles with rows and columns cut by the edge,
-chunks of 32, 64 and 192, operands at 2-byte alignment; the Blocked-DFP form."""
+row strides, one row subtile with rows and columns cut by the edge, chunks of
+32, 64 and 192, operands at 2-byte alignment; the Blocked-DFP form."""
 import numpy as np
 import pytest
 import torch

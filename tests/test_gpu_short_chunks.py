@@ -1,7 +1,7 @@
 """Forward and backward-data at chunk lengths 8, 16 and 32 on the
 four-waves-per-SIMD kernel: one filter phase (2 to 36 blocks), several phases,
-row tiles cut by the output channels, tiles cut by the pixels, stride 2 and
-its phases backward, with and without partials, against the oracle."""
+row tiles cut by the output channels, tiles cut by the pixels, stride 2, with
+and without partials, against the oracle."""
 import pytest
 
 from paper_1802_00930_amd import dfp
@@ -15,7 +15,7 @@ SHAPES = [
     (2, 32, 9, 11, 64, 4, 4, 1, 2),    # 16 blocks, 4x4 taps
     (1, 128, 6, 6, 96, 3, 3, 1, 1),    # 36 blocks
     (1, 256, 7, 7, 72, 3, 3, 1, 1),    # two phases, a cut row tile
-    (2, 64, 9, 9, 128, 3, 3, 2, 1),    # stride 2: phases of the backward pass
+    (2, 64, 9, 9, 128, 3, 3, 2, 1),    # stride 2: backward over the dilated gradient
 ]
 
 
