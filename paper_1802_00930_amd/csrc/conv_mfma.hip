@@ -2786,8 +2786,8 @@ ConvMfmaPlan plan_conv_mfma(const Geom& g, int32_t dir, bool unfold) {
   // it.  Multiples of 16 at L = 64 and 32 keep the shared-ring kernels, about even
   // in total (call us, ring / unfolded: 48 -> 48 3x3 on 28 x 28, N = 16, 18.6 /
   // 25.3; 32 -> 32 on 56 x 56, N = 32, 33.1 / 43.3; 80 -> 112 on 14 x 14 23.5 /
-  // 18.6; 352 -> 352 1x1 on 14 x 14, L = 32, 20.6 / 15.5); below 32 they would run
-  // the masked kernel.
+  // 18.6; 352 -> 352 1x1 on 14 x 14, L = 32, 20.6 / 15.5); below 32, where they
+  // would run the masked kernel, unfold_pays estimates both.
   p.Tu = (p.T + 63) / 64 * 64;
   if (!unfold || conv_w16_eligible(p.Cin, p.T, g.L, false) || !conv_w16_eligible(p.Tu, p.Tu, g.L, false) ||
       !(p.Cin % 16 != 0 || g.L < 32) || g.n >= 65535 || (int64_t)g.n * p.Po * p.Qo * p.Tu * 2 > ((int64_t)1 << 30) ||

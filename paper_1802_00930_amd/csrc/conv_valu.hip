@@ -8,8 +8,9 @@
 //   backward-data    t = (r*S + s)*K + k
 //   backward-weights t = (n*P + p)*Q + q   (segments of G chunks)
 // and handles every shape, stride and chunk length.  It is the measured
-// alternative to the MFMA path, not the default; at P = 16 it also stands
-// behind the MFMA path for tensors that path cannot represent (see Gate).
+// alternative to the MFMA path, the default only for small layers at P = 16,
+// where it also stands behind the MFMA path for tensors that path cannot
+// represent (see Gate).
 #include <algorithm>
 
 #include "dfp_internal.h"
@@ -27,7 +28,7 @@ constexpr int kBlock = 256;
 // k_p16_scan, which notes whether any operand element lies beyond, and a gated
 // launch of the VALU kernel, which recomputes the whole output if one does and
 // returns at once otherwise (a step of ResNet-50's res4 3x3 layer, N = 32,
-// L = 16: 5950 us with the VALU kernels alone, 569 us so; a tensor beyond the
+// L = 16: 5950 us with the VALU kernels alone, 303 us so; a tensor beyond the
 // digits costs the MFMA kernels on top of the VALU ones).
 constexpr int kScanWgs = 256;
 struct Gate {

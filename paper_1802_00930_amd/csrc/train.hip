@@ -21,9 +21,9 @@
 //             k_bn_finalize -> k_bn_amax (writes dy / dres if asked) -> max
 //             reduce -> k_bn_convert (or, with dy, the tensor quantiser)
 // 64 x 256 x 56 x 56 with a residual, z and dres (26 B per element at least):
-// forward stats 20, max pass + z 88, quantiser 59 us; backward stats 105, max
-// pass 74, convert 65 us (742 -> 429 us in all; copies run at 5.1 TB/s, the
-// passes at 3.9 to 5.7).
+// forward stats 21, max pass + z 89, quantiser 62 us; backward stats 110, max
+// pass 74, convert 67 us, the four small kernels 20 (746 -> 446 us a call; copies
+// run at 5.1 TB/s, the passes at 3.9 to 5.9).
 //   SGD       k_sgd (update + max) -> max reduce -> the tensor quantiser
 // Without a residual the forward output is a monotone function of the input
 // integer within a channel (ReLU of an affine map evaluated with monotone
