@@ -1,7 +1,8 @@
 """Blocked quantiser over numbers of waves around the steps of its workgroup size
 (one wave per block of 256 elements, 1 to 16 waves a workgroup, at most 256
-workgroups) and block lengths around the two-groups-per-lane line: integers,
-exponents, max and flags equal the oracle's."""
+workgroups), last rounds around the three quarters of 4096 waves below which they
+are dealt over the workgroups, and block lengths around the two-groups-per-lane
+line: integers, exponents, max and flags equal the oracle's."""
 import numpy as np
 import pytest
 import torch
@@ -15,7 +16,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shape,B", [((1, 256), 256), ((255, 256), 256), ((257, 256), 256), ((513, 256), 256),
-                                     ((3841, 256), 256), ((4097, 256), 256), ((3, 1536), 512), ((5, 2064), 516),
+                                     ((3841, 256), 256), ((4097, 256), 256), ((7168, 256), 256), ((7169, 256), 256),
+                                     ((8191, 256), 256), ((4300, 63), 63), ((7200, 63), 63), ((3, 1536), 512), ((5, 2064), 516),
                                      ((2, 70000), 70000), ((3, 4999), 4999), ((7, 33), 5)])
 @pytest.mark.parametrize("rounding", ["nearest", "stochastic"])
 def test_quantize_blocked_waves(shape, B, rounding):
