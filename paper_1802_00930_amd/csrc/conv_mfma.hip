@@ -1672,7 +1672,7 @@ constexpr int32_t kW16MaxKB = 36;
 // conversions alone take 27 us of every SIMD's VALU).
 template <bool PARTIALS, bool I32 = false, bool PHASED = false, int CL = 64>
 __global__ __launch_bounds__(kThreads16, 1) void k_conv_mfma_w16(ConvMfmaArgs a) {
-  static_assert(CL == 64 || ((CL == 32 || CL == 16 || CL == 8) && !I32), "chunk lengths");
+  static_assert(CL == 64 || ((CL == 32 || CL == 16 || CL == 8) && !I32 && !PARTIALS), "chunk lengths");
   constexpr int kZeroA = kW16MaxKB * kStageA;  // the zero piece
   __shared__ __align__(16) uint8_t sA[kZeroA + (CL < 32 ? 16 : 0)];
   __shared__ __align__(8) int32_t s_boff[kW16MaxKB];
@@ -2815,8 +2815,12 @@ dfp_status launch_conv_mfma(int32_t dir, const Geom& g, const int16_t* a, const 
   int2* boff = reinterpret_cast<int2*>(xs + p.ws_b_bytes);
   const int32_t rsign = fwd ? 1 : -1;
   const int32_t tap_row_bytes = rsign * p.Wp * p.CG * 32, tap_col_bytes = rsign * p.CG * 32;
-  bool plane = conv_w16_eligible(p.Cin, p.T, g.L, i32) && (int64_t)g.n * p.Po * p.Qo * p.M < (1ll << 31) &&
-               p.ws_b_bytes < (1ll << 31);
+  // (Partials at chunks below 64 keep the masked and shared-ring kernels: as many
+  // stores as products do not fit four waves per SIMD.  64 -> 128 channels 3x3
+  // stride 2 on 28 x 28, N = 8, L = 8, 123 us there and 859 here; 128 -> 128, N =
+  // 32, L = 32, 59 and 201.)
+  bool plane = conv_w16_eligible(p.Cin, p.T, g.L, i32) && !(partials && g.L < 64) &&
+               (int64_t)g.n * p.Po * p.Qo * p.M < (1ll << 31) && p.ws_b_bytes < (1ll << 31);
   if (plane && !prefer_w16)
     plane = plane_phases_ok((int64_t)g.n * p.Po * p.Qo, p.M, p.Mp, p.KB, g.L, partials != nullptr, device_cus());
   // the filter preparation clears so (unless a previous launch of the same
@@ -3068,21 +3072,18 @@ dfp_status launch_mfma_main(ConvMfmaArgs& args, int64_t ws_b_bytes, int kid, int
       args.kb0 = 2 * c0;
       args.kbn = 2 * (c1 - c0);
       args.phase_flags = (ph == 0 ? 1 : 0) | (ph == nph - 1 ? 2 : 0);
-#define DFP_W16(CL)                                                                                          \
-  do {                                                                                                       \
-    if (nph == 1 && partials)                                                                                \
-      DFP_LAUNCH(kid, (k_conv_mfma_w16<true, false, false, CL>), grid16, dim3(kThreads16), 0, st, args);     \
-    else if (nph == 1)                                                                                       \
-      DFP_LAUNCH(kid, (k_conv_mfma_w16<false, false, false, CL>), grid16, dim3(kThreads16), 0, st, args);    \
-    else if (partials)                                                                                       \
-      DFP_LAUNCH(kid, (k_conv_mfma_w16<true, false, true, CL>), grid16, dim3(kThreads16), 0, st, args);      \
-    else                                                                                                     \
-      DFP_LAUNCH(kid, (k_conv_mfma_w16<false, false, true, CL>), grid16, dim3(kThreads16), 0, st, args);     \
+#define DFP_W16(PARTIALS, CL)                                                                                     \
+  do {                                                                                                            \
+    if (nph == 1)                                                                                                 \
+      DFP_LAUNCH(kid, (k_conv_mfma_w16<PARTIALS, false, false, CL>), grid16, dim3(kThreads16), 0, st, args);      \
+    else                                                                                                          \
+      DFP_LAUNCH(kid, (k_conv_mfma_w16<PARTIALS, false, true, CL>), grid16, dim3(kThreads16), 0, st, args);       \
   } while (0)
-      if (args.L == 64) DFP_W16(64);
-      else if (args.L == 32) DFP_W16(32);
-      else if (args.L == 16) DFP_W16(16);
-      else DFP_W16(8);
+      if (partials) DFP_W16(true, 64);
+      else if (args.L == 64) DFP_W16(false, 64);
+      else if (args.L == 32) DFP_W16(false, 32);
+      else if (args.L == 16) DFP_W16(false, 16);
+      else DFP_W16(false, 8);
 #undef DFP_W16
     }
     return DFP_OK;

@@ -1,7 +1,7 @@
 """Forward and backward-data at chunk lengths 8, 16 and 32 on the
 four-waves-per-SIMD kernel: one filter phase (2 to 36 blocks), several phases,
-row tiles cut by the output channels, tiles cut by the pixels, stride 2, with
-and without partials, against the oracle."""
+row tiles cut by the output channels, tiles cut by the pixels, stride 2, and with
+partials (on the masked and shared-ring kernels), against the oracle."""
 import pytest
 
 from paper_1802_00930_amd import dfp
